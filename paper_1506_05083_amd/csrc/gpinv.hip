@@ -45,8 +45,9 @@ namespace mfs {
 void qr_form_u(const MatDesc *descs, const std::vector<MatDesc> &h, int maxrank, hipStream_t s,
                bool from_identity = false, int nb = kQRNB);
 void launch_zero(double2 *p, long n, hipStream_t s);
+// halves: matrices 2 i and 2 i + 1 share the cutoff's scale
 void jac_sort(const MatDesc *descs, const std::vector<MatDesc> &h, double rel_cutoff, hipStream_t s,
-              std::vector<int> &ranks);
+              std::vector<int> &ranks, bool halves = false);
 void qrcp_blocked(const MatDesc *descs, const std::vector<MatDesc> &h, double *norms, int *piv, int ld,
                   hipStream_t s);
 
@@ -701,7 +702,8 @@ static bool use_cod(bool equilibrate, bool pivot, int n2max) {
 // W = D P R^{-1} are formed and true is returned.  Otherwise (some matrix of
 // the batch may need truncating) nothing is kept and false is returned.
 static bool direct_pinv(GradedPinv &g, const std::vector<int> &n2, int nmax, double rel_cutoff,
-                        const double *cscl, const std::vector<MatDesc> &in, hipStream_t s, bool keep_reflectors) {
+                        const double *cscl, const std::vector<MatDesc> &in, hipStream_t s, bool keep_reflectors,
+                        bool halves) {
   const int W = (int)n2.size();
   const int n2max = *std::max_element(n2.begin(), n2.end());
   int *flags = g.small.as<int>();
@@ -734,12 +736,14 @@ static bool direct_pinv(GradedPinv &g, const std::vector<int> &n2, int nmax, dou
   std::vector<double2> hn((size_t)W * n2max);
   HIP_CHECK(hipMemcpyAsync(hn.data(), nrm.p, hn.size() * sizeof(double2), hipMemcpyDeviceToHost, s));
   HIP_CHECK(hipStreamSynchronize(s));
+  double sr = 0.0, sx = 0.0;
   for (int w = 0; w < W; ++w) {
-    double sr = 0.0, sx = 0.0;
+    if (!(halves && w % 2)) sr = sx = 0.0;
     for (int j = 0; j < n2[w]; ++j) {
       sr += hn[(size_t)w * n2max + j].x;
       sx += hn[(size_t)w * n2max + j].y;
     }
+    if (halves && w % 2 == 0) continue;   // the bound of both halves together
     const double bound = std::sqrt(sr) * std::sqrt(sx);
     if (!std::isfinite(bound) || !(bound * rel_cutoff < 1.0)) return false;
   }
@@ -787,8 +791,9 @@ static bool direct_pinv(GradedPinv &g, const std::vector<int> &n2, int nmax, dou
 }
 
 void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutoff, int pivot_min_cols,
-                 hipStream_t s, bool equilibrate, bool keep_reflectors) {
+                 hipStream_t s, bool equilibrate, bool keep_reflectors, bool halves) {
   const int W = (int)in.size();
+  MFS_REQUIRE(!halves || W % 2 == 0, "graded pseudoinverse: halves come in pairs");
   int nmax = 0, mmax = 0;
   for (auto &d : in) { nmax = std::max(nmax, d.n); mmax = std::max(mmax, d.m); }
   g.direct = false;
@@ -865,7 +870,9 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
   }
   const double *cscl = equilibrate ? g.colscale.as<double>() : nullptr;
   const int n2max = *std::max_element(n2.begin(), n2.end());
-  const bool pivot = n2max >= pivot_min_cols;
+  int nwhole = n2max;   // columns of the widest whole matrix
+  for (int w = 0; halves && w < W; w += 2) nwhole = std::max(nwhole, n2[w] + n2[w + 1]);
+  const bool pivot = nwhole >= pivot_min_cols;
   g.pivoted = pivot;
   // 2. QR without pivoting of the selected, ordered columns
   g.h_qc.resize(W);
@@ -935,7 +942,7 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     HIP_CHECK(hipMemcpyAsync(g.piv.p, ident.data(), ident.size() * sizeof(int), hipMemcpyHostToDevice, s));
     HIP_CHECK(hipStreamSynchronize(s));
   }
-  if (equilibrate && direct_pinv(g, n2, nmax, rel_cutoff, cscl, in, s, keep_reflectors)) return;
+  if (equilibrate && direct_pinv(g, n2, nmax, rel_cutoff, cscl, in, s, keep_reflectors, halves)) return;
   if (pivot) {
     g.h_rq.resize(W);
     {
@@ -1020,10 +1027,11 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
   // complete orthogonal decomposition: keep the rows of the pivoted triangle
   // until the trailing block's Frobenius norm is at most rel_cutoff times the
   // largest singular value (the rank-revealing counterpart of the SVD cut)
-  const bool cod = use_cod(equilibrate, pivot, n2max);
+  const bool cod = use_cod(equilibrate, pivot, nwhole);
   g.cod = cod;
   if (cod) {
-    const std::vector<double> s1 = tri_sigma1(tri, n2, n2max, s);
+    std::vector<double> s1 = tri_sigma1(tri, n2, n2max, s);
+    for (int w = 0; halves && w < W; w += 2) s1[w] = s1[w + 1] = std::max(s1[w], s1[w + 1]);
     for (int w = 0; w < W; ++w) {
       const double thr = rel_cutoff * s1[w];
       double suf = 0.0;
@@ -1116,7 +1124,7 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     g.jacobi_bytes = js.bytes;
     g.jacobi_flops = js.flops;
     g.jacobi_unconverged = js.unconverged;
-    jac_sort(g.d_lq.as<MatDesc>(), g.h_lq, rel_cutoff, s, g.kept);
+    jac_sort(g.d_lq.as<MatDesc>(), g.h_lq, rel_cutoff, s, g.kept, halves);
   }
   // 5. explicit factors
   int kmax = 0;

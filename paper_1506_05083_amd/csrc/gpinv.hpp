@@ -63,11 +63,14 @@ struct GradedPinv {
 // column size; W then holds D V S^+ and the pseudoinverse is D (A D)^+.
 // keep_reflectors: when every singular value is kept (the direct form), U =
 // Q_1 is not formed; the QR's reflectors stay for launch_qh_apply (g.reflect).
+// halves: matrices 2 i and 2 i + 1 are the diagonal blocks of one matrix; its
+// largest singular value, condition bound and column count decide for both.
 void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutoff, int pivot_min_cols,
-                 hipStream_t s, bool equilibrate = false, bool keep_reflectors = false);
+                 hipStream_t s, bool equilibrate = false, bool keep_reflectors = false, bool halves = false);
 
-// Widest periodizer triangle factored without the pivoted QR (measured:
-// 1257 columns at k = 10 gain nothing from it, 9701 at k = 2 pi 13 gain 30%).
+// Widest periodizer triangle (columns of both halves together) factored
+// without the pivoted QR (measured unsplit: 1257 columns at k = 10 gain
+// nothing from it, 9701 at k = 2 pi 13 gain 30%).
 constexpr int kQPivotMinCols = 2048;
 
 }  // namespace mfs

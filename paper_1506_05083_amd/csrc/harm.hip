@@ -24,20 +24,21 @@ namespace {
 
 constexpr int MAXP = 96;
 
-__device__ void sph_bessel(int p, double x, double *j, double *jp) {
+// j_l(x) and its derivative, l = 0..p, into j[l * ld], jp[l * ld]
+__device__ void sph_bessel(int p, double x, double *j, double *jp, size_t ld) {
   const int L = p + 32 + (int)x;
   double fnext = 0.0, f = 1e-200;
   for (int l = L; l >= 1; --l) {
     const double fprev = (2.0 * l + 1.0) / x * f - fnext;   // f_{l-1}
     fnext = f;
     f = fprev;
-    if (l - 1 <= p) j[l - 1] = f;
-    if (l <= p) j[l] = fnext;
+    if (l - 1 <= p) j[(l - 1) * ld] = f;
+    if (l <= p) j[l * ld] = fnext;
     if (fabs(f) > 1e250) {
       f *= 1e-250;
       fnext *= 1e-250;
       for (int i = l - 1; i <= p; ++i)
-        if (i >= 0) j[i] *= 1e-250;
+        if (i >= 0) j[i * ld] *= 1e-250;
     }
   }
   double s, c;
@@ -46,10 +47,10 @@ __device__ void sph_bessel(int p, double x, double *j, double *jp) {
   const double j1 = s / (x * x) - c / x;
   double scale;
   if (fabs(j0) >= fabs(j1)) scale = j0 / j[0];
-  else scale = j1 / j[1];
-  for (int l = 0; l <= p; ++l) j[l] *= scale;
-  jp[0] = -j[1];
-  for (int l = 1; l <= p; ++l) jp[l] = j[l - 1] - (l + 1.0) / x * j[l];
+  else scale = j1 / j[ld];
+  for (int l = 0; l <= p; ++l) j[l * ld] *= scale;
+  jp[0] = -j[ld];
+  for (int l = 1; l <= p; ++l) jp[l * ld] = j[(l - 1) * ld] - (l + 1.0) / x * j[l * ld];
 }
 
 // Spherical coordinates of a point and the frame vectors.
@@ -67,165 +68,173 @@ __device__ inline Sph sph_of(double x, double y, double z) {
   return o;
 }
 
-// Visit every (l, m >= 0): calls f(l, m, P_l^m, dP_l^m/dth).
+// Visit l = m..p of one m >= 0: calls f(l, P_l^m, dP_l^m/dth).
 template <class F>
-__device__ inline void legendre_visit(int p, double ct, double st, F f) {
+__device__ inline void legendre_visit(int p, int m, double ct, double st, F f) {
   double pmm = 0.28209479177387814;   // 1/sqrt(4 pi)
-  for (int m = 0; m <= p; ++m) {
-    if (m > 0) pmm = -sqrt((2.0 * m + 1.0) / (2.0 * m)) * st * pmm;
-    double p2 = 0.0, p1 = pmm;   // P_{l-2}, P_{l-1}
-    // l = m
-    {
-      const double dth = (m * ct * pmm) / st;
-      f(m, m, pmm, dth);
+  for (int i = 1; i <= m; ++i) pmm = -sqrt((2.0 * i + 1.0) / (2.0 * i)) * st * pmm;
+  double p2 = 0.0, p1 = pmm;   // P_{l-2}, P_{l-1}
+  f(m, pmm, (m * ct * pmm) / st);
+  for (int l = m + 1; l <= p; ++l) {
+    double pl;
+    if (l == m + 1) pl = sqrt(2.0 * m + 3.0) * ct * pmm;
+    else {
+      const double a = sqrt((4.0 * l * l - 1.0) / ((double)l * l - (double)m * m));
+      const double b = sqrt(((l - 1.0) * (l - 1.0) - (double)m * m) / (4.0 * (l - 1.0) * (l - 1.0) - 1.0));
+      pl = a * (ct * p1 - b * p2);
     }
-    for (int l = m + 1; l <= p; ++l) {
-      double pl;
-      if (l == m + 1) pl = sqrt(2.0 * m + 3.0) * ct * pmm;
-      else {
-        const double a = sqrt((4.0 * l * l - 1.0) / ((double)l * l - (double)m * m));
-        const double b = sqrt(((l - 1.0) * (l - 1.0) - (double)m * m) / (4.0 * (l - 1.0) * (l - 1.0) - 1.0));
-        pl = a * (ct * p1 - b * p2);
-      }
-      const double dth = (l * ct * pl - sqrt((2.0 * l + 1.0) / (2.0 * l - 1.0)) *
-                                            sqrt((double)l * l - (double)m * m) * p1) / st;
-      f(l, m, pl, dth);
-      p2 = p1;
-      p1 = pl;
-    }
+    const double dth = (l * ct * pl - sqrt((2.0 * l + 1.0) / (2.0 * l - 1.0)) *
+                                          sqrt((double)l * l - (double)m * m) * p1) / st;
+    f(l, pl, dth);
+    p2 = p1;
+    p1 = pl;
   }
-}
-
-// Value and Cartesian gradient of H_lm for m >= 0 and its m < 0 partner,
-// given j, jp, P, dP/dth at a point.
-struct HVal {
-  double2 h, gx, gy, gz;
-};
-__device__ inline void harm_pair(int l, int m, double P, double dP, const double *j,
-                                 const double *jp, double k, const Sph &s, HVal &pos, HVal &neg) {
-  // e^{i m phi} by angle addition on (cp, sp)
-  const double phi = atan2(s.sp, s.cp);
-  double sm, cm;
-  sincos(m * phi, &sm, &cm);
-  const double2 e = cz(cm, sm);
-  const double jl = j[l];
-  const double dr = k * jp[l] * P;           // d/dr of the real radial-polar part
-  const double dth = jl * dP / s.r;          // (1/r) d/dth
-  const double dph = jl * P / (s.r * s.st);  // times (i m e) below
-  // r^, th^, ph^
-  const double rx = s.st * s.cp, ry = s.st * s.sp, rz = s.ct;
-  const double tx = s.ct * s.cp, ty = s.ct * s.sp, tz = -s.st;
-  const double px = -s.sp, py = s.cp;
-  const double ax = dr * rx + dth * tx, ay = dr * ry + dth * ty, az = dr * rz + dth * tz;
-  // grad = e * (a) + i m e * dph * ph^
-  const double2 ime = cz(-m * e.y * dph, m * e.x * dph);
-  pos.h = cscale(e, jl * P);
-  pos.gx = cadd(cscale(e, ax), cscale(ime, px));
-  pos.gy = cadd(cscale(e, ay), cscale(ime, py));
-  pos.gz = cscale(e, az);
-  // Y_l^{-m} = (-1)^m conj(Y_l^m); the radial factor is real
-  const double sg = (m & 1) ? -1.0 : 1.0;
-  neg.h = cscale(cconj(pos.h), sg);
-  neg.gx = cscale(cconj(pos.gx), sg);
-  neg.gy = cscale(cconj(pos.gy), sg);
-  neg.gz = cscale(cconj(pos.gz), sg);
 }
 
 __device__ inline int lm_col(int l, int m) { return l * l + l + m; }
 
-// One thread per (unit, node): units LR, FB (pairs of walls) and T, D; each
-// writes two rows of Q: value and normal-derivative (discrepancy or Cauchy).
-__global__ __launch_bounds__(64) void qfill_s_kernel(const QFillArgs *__restrict__ args) {
-  const QFillArgs a = args[blockIdx.y];   // one incidence per grid row
-  const int M1sq = a.M1 * a.M1;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= 4 * M1sq) return;
-  const int unit = idx / M1sq, i = idx % M1sq;
-  double j1[MAXP + 1], jp1[MAXP + 1], j2[MAXP + 1], jp2[MAXP + 1];
-  // walls SoA: R L F B T D
-  auto wall = [&](int w, int c) { return a.wall[(size_t)(3 * w + c) * M1sq + i]; };
-  int w1, w2;
-  double2 ph;
-  int comp;   // gradient component of the normal
-  if (unit == 0) { w1 = 0; w2 = 1; ph = a.alpha; comp = 0; }
-  else if (unit == 1) { w1 = 2; w2 = 3; ph = a.beta; comp = 1; }
-  else if (unit == 2) { w1 = 4; w2 = -1; ph = cz(0.0, 0.0); comp = 2; }
-  else { w1 = 5; w2 = -1; ph = cz(0.0, 0.0); comp = 2; }
-  const Sph s1 = sph_of(wall(w1, 0), wall(w1, 1), wall(w1, 2));
-  sph_bessel(a.p, a.k * s1.r, j1, jp1);
-  Sph s2 = s1;
-  if (w2 >= 0) {
-    s2 = sph_of(wall(w2, 0), wall(w2, 1), wall(w2, 2));
-    sph_bessel(a.p, a.k * s2.r, j2, jp2);
-  }
-  const int rowv = (2 * unit) * M1sq + i, rowd = (2 * unit + 1) * M1sq + i;
-  auto put = [&](int col, const HVal &h1, const HVal *h2) {
-    double2 v = h1.h;
-    double2 g = comp == 0 ? h1.gx : (comp == 1 ? h1.gy : h1.gz);
-    if (h2) {
-      v = csub(v, cmul(ph, h2->h));
-      const double2 g2 = comp == 0 ? h2->gx : (comp == 1 ? h2->gy : h2->gz);
-      g = csub(g, cmul(ph, g2));
+// j_l(k r), j_l'(k r) of n points (SoA x, y, z; y null: 0) into j, jp [p+1][n]
+__global__ __launch_bounds__(64) void bessel_table_kernel(int n, int p, double k, const double *x, const double *y,
+                                                          const double *z, double *j, double *jp) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  sph_bessel(p, k * sph_of(x[i], y ? y[i] : 0.0, z[i]).r, j + i, jp + i, n);
+}
+
+// S block of both halves of Q (QHalf in internal.hpp) for every wave: one
+// thread per (node, m).  Bound by its stores (16 B x 4 (p + 1 - m) per wave):
+// what a node contributes does not depend on the wave except for the Bloch
+// phase, so a thread evaluates its harmonics once and writes them for all
+// waves.  The nodes of a wall pair share radius, polar angle and, mirrored,
+// azimuth: H_lm on L is (-1)^m conj(H_lm on R), on B conj(H_lm on F), and
+// the normal derivatives change sign as well, so each pair is one evaluation.
+// 8 waves of the k = 10 lattice (16 halves of 2304 x 650, 383 MB): 211 us, 28 us
+// the table of Bessel functions before it; 1.88 ms with one thread per node
+// and wave looping over all (l, m), both walls evaluated.
+__global__ __launch_bounds__(64) void qfill_s_kernel(int W, int p, int M1, double k, const double *__restrict__ nodes,
+                                                     const double *__restrict__ jt, const double *__restrict__ jpt,
+                                                     const QFillArgs *__restrict__ args) {
+  const int M1sq = M1 * M1, H = M1sq / 2, nn = 2 * M1sq;
+  const int i = blockIdx.x * blockDim.x + threadIdx.x, m = blockIdx.y;
+  if (i >= nn) return;
+  const int unit = i < H ? 0 : (i < 2 * H ? 1 : 2);   // R/L, F/B, T/D
+  const int rowv = unit == 0 ? i : (unit == 1 ? i + H : i + 2 * H);
+  const int rowd = rowv + (unit == 2 ? M1sq : H);
+  const Sph s = sph_of(nodes[i], nodes[nn + i], nodes[2 * nn + i]);
+  double sm, cm;
+  sincos(m * atan2(s.sp, s.cp), &sm, &cm);
+  const double sg = (m & 1) ? -1.0 : 1.0;
+  const double rt2 = 1.4142135623730951;
+  // components of r^, th^, ph^ along the wall normal
+  const double nr = unit == 0 ? s.st * s.cp : (unit == 1 ? s.st * s.sp : s.ct);
+  const double nt = unit == 0 ? s.ct * s.cp : (unit == 1 ? s.ct * s.sp : -s.st);
+  const double np = unit == 0 ? -s.sp : (unit == 1 ? s.cp : 0.0);
+  const double msg = unit == 0 ? sg : 1.0;   // the mirrored wall: msg conj(.)
+  legendre_visit(p, m, s.ct, s.st, [&](int l, double P, double dP) {
+    const double jl = jt[(size_t)l * nn + i], jlp = jpt[(size_t)l * nn + i];
+    // value e^{im phi} hv, derivative e^{im phi} (ga + i gb)
+    const double hv = rt2 * jl * P;
+    const double ga = rt2 * (k * jlp * P * nr + jl * dP / s.r * nt), gb = rt2 * m * jl * P / (s.r * s.st) * np;
+    const double2 h = cz(hv * cm, hv * sm), g = cz(ga * cm - gb * sm, ga * sm + gb * cm);
+    const int par = (l + m) & 1;
+    const int base = par ? l * (l - 1) / 2 : l * (l + 1) / 2;
+    const int cp = base + (l + m - par) / 2, cn = base + (l - m - par) / 2;
+    for (int w = 0; w < W; ++w) {
+      const QFillArgs a = args[w];
+      double2 *Q = a.Q[par];
+      double2 v = h, d = g, vn = cscale(cconj(h), sg), dn = cscale(cconj(g), sg);   // m and -m
+      if (unit < 2) {
+        const double2 ph = cscale(unit == 0 ? a.alpha : a.beta, msg);
+        const double2 mv = cmul(ph, cconj(v)), md = cmul(ph, cconj(d));
+        const double2 mvn = cmul(ph, cconj(vn)), mdn = cmul(ph, cconj(dn));
+        v = csub(v, mv);
+        d = cadd(d, md);
+        vn = csub(vn, mvn);
+        dn = cadd(dn, mdn);
+      }
+      Q[(size_t)cp * a.ldq + rowv] = v;
+      Q[(size_t)cp * a.ldq + rowd] = d;
+      if (m > 0) {
+        Q[(size_t)cn * a.ldq + rowv] = vn;
+        Q[(size_t)cn * a.ldq + rowd] = dn;
+      }
     }
-    a.Q[(size_t)col * a.ldq + rowv] = v;
-    a.Q[(size_t)col * a.ldq + rowd] = g;
-  };
-  if (w2 < 0) {
-    legendre_visit(a.p, s1.ct, s1.st, [&](int l, int m, double P, double dP) {
-      HVal hp, hn;
-      harm_pair(l, m, P, dP, j1, jp1, a.k, s1, hp, hn);
-      put(lm_col(l, m), hp, nullptr);
-      if (m > 0) put(lm_col(l, -m), hn, nullptr);
-    });
-  } else {
-    // both points share l, m; evaluate the second point's Legendre functions
-    // in the same order by a second pass that adds into Q
-    legendre_visit(a.p, s1.ct, s1.st, [&](int l, int m, double P, double dP) {
-      HVal hp, hn;
-      harm_pair(l, m, P, dP, j1, jp1, a.k, s1, hp, hn);
-      put(lm_col(l, m), hp, nullptr);
-      if (m > 0) put(lm_col(l, -m), hn, nullptr);
-    });
-    legendre_visit(a.p, s2.ct, s2.st, [&](int l, int m, double P, double dP) {
-      HVal hp, hn;
-      harm_pair(l, m, P, dP, j2, jp2, a.k, s2, hp, hn);
-      auto sub = [&](int col, const HVal &h2) {
-        const double2 g2 = comp == 0 ? h2.gx : (comp == 1 ? h2.gy : h2.gz);
-        double2 *qv = &a.Q[(size_t)col * a.ldq + rowv];
-        double2 *qd = &a.Q[(size_t)col * a.ldq + rowd];
-        *qv = csub(*qv, cmul(ph, h2.h));
-        *qd = csub(*qd, cmul(ph, g2));
-      };
-      sub(lm_col(l, m), hp);
-      if (m > 0) sub(lm_col(l, -m), hn);
-    });
+  });
+}
+
+// -W block of both halves: on T the plane waves (value -e, derivative
+// -i kappa_z e), the same in the even and the odd half; zero on the side walls.
+__global__ void qfill_w_kernel(int p, int M1, const double *__restrict__ nodes, const QFillArgs *__restrict__ args) {
+  const QFillArgs a = args[blockIdx.y];   // one incidence per grid row
+  const int M1sq = M1 * M1, H = M1sq / 2, nn = 2 * M1sq, rows = 4 * M1sq;
+  const long total = (long)rows * a.nrb;
+  for (long idx = (long)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
+       idx += (long)gridDim.x * blockDim.x) {
+    const int o = (int)(idx / rows);
+    const int row = (int)(idx % rows);
+    double2 v = cz(0.0, 0.0);
+    if (row >= 4 * H) {
+      const int t = (row - 4 * H) % M1sq;
+      double s, c;
+      sincos(a.kx[o] * nodes[2 * H + t] + a.ky[o] * nodes[nn + 2 * H + t], &s, &c);
+      v = cz(-c, -s);
+      if (row - 4 * H >= M1sq) v = cmul(cz(-a.kz[o].y, a.kz[o].x), v);
+    }
+    a.Q[0][(size_t)((p + 1) * (p + 2) / 2 + o) * a.ldq + row] = v;
+    a.Q[1][(size_t)(p * (p + 1) / 2 + o) * a.ldq + row] = v;
   }
 }
 
-// -W blocks: rows of T (value, d/dz) for the a_mn columns and of D for b_mn.
-__global__ void qfill_w_kernel(const QFillArgs *__restrict__ args) {
-  const QFillArgs a = args[blockIdx.y];   // one incidence per grid row
-  const int M1sq = a.M1 * a.M1;
-  const int NH = (a.p + 1) * (a.p + 1);
-  const long total = (long)4 * M1sq * a.nrb;
-  for (long idx = (long)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-       idx += (long)gridDim.x * blockDim.x) {
-    const int o = (int)(idx / (4 * M1sq));
-    const int rr = (int)(idx % (4 * M1sq));
-    const int blk = rr / M1sq, i = rr % M1sq;     // 0 T val, 1 T dz, 2 D val, 3 D dz
-    const int w = blk < 2 ? 4 : 5;
-    const double x = a.wall[(size_t)(3 * w) * M1sq + i], y = a.wall[(size_t)(3 * w + 1) * M1sq + i];
-    double s, c;
-    sincos(a.kx[o] * x + a.ky[o] * y, &s, &c);
-    const double2 e = cz(c, s);
-    const double2 ikz = cz(-a.kz[o].y, a.kz[o].x);     // i kappa_z
+// The wall sums (target groups of walls_plan, pad targets each) as right-hand
+// sides of the two halves: out[2 w + par][row], rows_h rows, those past
+// 4 M1^2 zero.
+__global__ void split_walls_kernel(int nw, int M1, const double2 *__restrict__ in, double2 *__restrict__ out,
+                                   int rows_h) {
+  const int M1sq = M1 * M1, H = M1sq / 2, pad = (M1sq + 63) / 64 * 64;
+  const long n = (long)nw * rows_h;
+  const double rh = 0.70710678118654752;
+  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
+    const int w = (int)(i / rows_h), row = (int)(i % rows_h);
+    const double2 *src = in + (size_t)w * 12 * pad;
+    double2 x = cz(0.0, 0.0), y = x;   // the node and its image under z -> -z
+    double sg = 1.0;                   // the even half adds sg times the image
+    if (row < 4 * H) {
+      const int blk = row / H, e = row % H;
+      const int t = e / (M1 / 2) * M1 + M1 / 2 + e % (M1 / 2);
+      const int u = t / M1 * M1 + (M1 - 1 - t % M1);
+      x = cadd(src[(2 * blk) * pad + t], src[(2 * blk + 1) * pad + t]);
+      y = cadd(src[(2 * blk) * pad + u], src[(2 * blk + 1) * pad + u]);
+    } else if (row < 4 * M1sq) {
+      const int t = row - 4 * H, der = t >= M1sq ? 1 : 0;
+      x = src[(8 + der) * pad + t - der * M1sq];
+      y = src[(10 + der) * pad + t - der * M1sq];
+      sg = der ? -1.0 : 1.0;
+    }
+    out[(size_t)(2 * w) * rows_h + row] = cz(rh * (x.x + sg * y.x), rh * (x.y + sg * y.y));
+    out[(size_t)(2 * w + 1) * rows_h + row] = cz(rh * (x.x - sg * y.x), rh * (x.y - sg * y.y));
+  }
+}
+
+// xi[w] in the column order of Q (harmonics l^2 + l + m, a, b) from the two
+// halves' coefficients xh[2 w + par] (ldh apart)
+__global__ void merge_xi_kernel(int nw, int p, const int *__restrict__ nrb, const double2 *__restrict__ xh, int ldh,
+                                double2 *__restrict__ xi, int ldx) {
+  const int w = blockIdx.y, NH = (p + 1) * (p + 1), nr = nrb[w];
+  const double2 *e = xh + (size_t)(2 * w) * ldh, *o = e + ldh;
+  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < NH + 2 * nr; c += gridDim.x * blockDim.x) {
     double2 v;
-    if (blk == 0 || blk == 2) v = cz(-e.x, -e.y);
-    else if (blk == 1) v = cscale(cmul(ikz, e), -1.0);
-    else v = cmul(ikz, e);
-    const int row = (4 + blk) * M1sq + i;
-    const int col = NH + (blk < 2 ? 0 : a.nrb) + o;
-    a.Q[(size_t)col * a.ldq + row] = v;
+    if (c < NH) {
+      int l = (int)sqrt((double)c);
+      if (l * l > c) --l;
+      if ((l + 1) * (l + 1) <= c) ++l;
+      const int lm = c - l * l;   // l + m
+      v = (lm & 1) ? o[l * (l - 1) / 2 + (lm - 1) / 2] : e[l * (l + 1) / 2 + lm / 2];
+    } else {
+      const int q = (c - NH) % nr;
+      const double2 ev = e[(p + 1) * (p + 2) / 2 + q], ov = o[p * (p + 1) / 2 + q];
+      v = cscale(c - NH < nr ? cadd(ev, ov) : csub(ev, ov), 0.70710678118654752);
+    }
+    xi[(size_t)w * ldx + c] = v;
   }
 }
 
@@ -234,20 +243,21 @@ __global__ void zero_kernel(double2 *p, long n) {
     p[i] = cz(0.0, 0.0);
 }
 
-// dH_lm/dn at (rho_i, 0, z_i) with normal (nrho_i, 0, nz_i): out[lm][i].
+// dH_lm/dn (value = 0) or H_lm at (rho_i, 0, z_i) with normal (nrho_i, 0,
+// nz_i): out[lm][i], one thread per (point, m); j, jp [p+1][M]
 __global__ __launch_bounds__(64) void bfill_kernel(int M, int p, double k, const double *rho,
                                                    const double *z, const double *nrho,
-                                                   const double *nz, double2 *out, int value) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+                                                   const double *nz, const double *__restrict__ j,
+                                                   const double *__restrict__ jp, double2 *out, int value) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x, m = blockIdx.y;
   if (i >= M) return;
-  double j[MAXP + 1], jp[MAXP + 1];
   const Sph s = sph_of(rho[i], 0.0, z[i]);
-  sph_bessel(p, k * s.r, j, jp);
-  const double nr = nrho[i], nzz = nz[i];
-  legendre_visit(p, s.ct, s.st, [&](int l, int m, double P, double dP) {
-    const double dr = k * jp[l] * P, dth = j[l] * dP / s.r;
+  const double nr = value ? 0.0 : nrho[i], nzz = value ? 0.0 : nz[i];
+  legendre_visit(p, m, s.ct, s.st, [&](int l, double P, double dP) {
+    const double jl = j[(size_t)l * M + i];
+    const double dr = k * jp[(size_t)l * M + i] * P, dth = jl * dP / s.r;
     // d/drho = st d/dr + ct/r d/dth ; d/dz = ct d/dr - st/r d/dth  (phi = 0)
-    const double v = value ? j[l] * P : nr * (s.st * dr + s.ct * dth) + nzz * (s.ct * dr - s.st * dth);
+    const double v = value ? jl * P : nr * (s.st * dr + s.ct * dth) + nzz * (s.ct * dr - s.st * dth);
     out[(size_t)lm_col(l, m) * M + i] = cz(v, 0.0);
     if (m > 0) out[(size_t)lm_col(l, -m) * M + i] = cz((m & 1) ? -v : v, 0.0);
   });
@@ -279,64 +289,125 @@ __global__ void bapply_kernel(int nrhs, int P, int M, int p, const double2 *__re
   }
 }
 
-// u[r][t] += sum_lm H_lm(x_t) d[r][lm]
-__global__ __launch_bounds__(64) void harm_field_kernel(int nrhs, int nt, const double *xyz, int p,
+// u[r][t] += sum_lm H_lm(x_t) d[r][lm]: one workgroup per target, one thread
+// per m (a thread per target left all but one of the chip's wavefronts idle:
+// 1.68 ms for 44 targets and 8 waves, 0.10 ms now for 32)
+constexpr int HF = 128, HFR = 16;   // MAXP < HF
+__global__ __launch_bounds__(HF) void harm_field_kernel(int nrhs, int nt, const double *xyz, int p,
                                                         double k, const double2 *d, int ldd,
                                                         double2 *out) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nt) return;
-  double j[MAXP + 1], jp[MAXP + 1];
+  const int t = blockIdx.x, m = threadIdx.x;
+  __shared__ double j[MAXP + 1], jp[MAXP + 1];
+  __shared__ double2 red[HF / 64][HFR];
   const Sph s = sph_of(xyz[3 * t], xyz[3 * t + 1], xyz[3 * t + 2]);
-  sph_bessel(p, k * s.r, j, jp);
-  const double phi = atan2(s.sp, s.cp);
-  for (int r = 0; r < nrhs; ++r) {
-    double2 acc = cz(0.0, 0.0);
-    legendre_visit(p, s.ct, s.st, [&](int l, int m, double P, double dP) {
-      double sm, cm;
-      sincos(m * phi, &sm, &cm);
-      const double2 hv = cz(j[l] * P * cm, j[l] * P * sm);
-      cfma(acc, hv, d[(size_t)r * ldd + lm_col(l, m)]);
-      if (m > 0) {
-        const double sg = (m & 1) ? -1.0 : 1.0;
-        cfma(acc, cscale(cconj(hv), sg), d[(size_t)r * ldd + lm_col(l, -m)]);
-      }
-    });
-    out[(size_t)r * nt + t] = cadd(out[(size_t)r * nt + t], acc);
+  if (m == 0) sph_bessel(p, k * s.r, j, jp, 1);
+  __syncthreads();
+  double sm, cm;
+  sincos(m * atan2(s.sp, s.cp), &sm, &cm);
+  const double sg = (m & 1) ? -1.0 : 1.0;
+  for (int r0 = 0; r0 < nrhs; r0 += HFR) {
+    const int nr = min(HFR, nrhs - r0);
+    double2 acc[HFR];
+#pragma unroll
+    for (int r = 0; r < HFR; ++r) acc[r] = cz(0.0, 0.0);
+    if (m <= p)
+      legendre_visit(p, m, s.ct, s.st, [&](int l, double P, double) {
+        const double2 hv = cz(j[l] * P * cm, j[l] * P * sm), hn = cscale(cconj(hv), sg);
+#pragma unroll
+        for (int r = 0; r < HFR; ++r)
+          if (r < nr) {
+            const double2 *dr = d + (size_t)(r0 + r) * ldd + lm_col(l, 0);
+            cfma(acc[r], hv, dr[m]);
+            if (m > 0) cfma(acc[r], hn, dr[-m]);
+          }
+      });
+#pragma unroll
+    for (int r = 0; r < HFR; ++r) {
+      const double2 v = wave_sum(acc[r]);
+      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][r] = v;
+    }
+    __syncthreads();
+    if (m < nr) {
+      double2 *o = out + (size_t)(r0 + m) * nt + t;
+      *o = cadd(*o, cadd(red[0][m], red[1][m]));
+    }
+    __syncthreads();
   }
 }
 
 }  // namespace
 
-void launch_qfill(const std::vector<QFillArgs> &h, hipStream_t s) {
+// Nodes of the half system: R then F on the half z > 0 (b >= M1/2 of node
+// (a, b)), then T; SoA x, y, z [2 M1^2] each, from the walls' SoA.
+void half_nodes(int M1, const std::vector<double> &wall, std::vector<double> &out) {
+  const int M1sq = M1 * M1, H = M1sq / 2, nn = 2 * M1sq;
+  out.assign((size_t)3 * nn, 0.0);
+  for (int c = 0; c < 3; ++c) {
+    for (int e = 0; e < H; ++e) {
+      const int t = e / (M1 / 2) * M1 + M1 / 2 + e % (M1 / 2);
+      out[(size_t)c * nn + e] = wall[(size_t)c * M1sq + t];
+      out[(size_t)c * nn + H + e] = wall[(size_t)(6 + c) * M1sq + t];
+    }
+    for (int t = 0; t < M1sq; ++t) out[(size_t)c * nn + 2 * H + t] = wall[(size_t)(12 + c) * M1sq + t];
+  }
+}
+
+static void bessel_table(int n, int p, double k, const double *x, const double *y, const double *z, DevBuf &jt,
+                         hipStream_t s) {
+  jt.alloc((size_t)2 * (p + 1) * n * sizeof(double));
+  double *j = jt.as<double>();
+  hipLaunchKernelGGL(bessel_table_kernel, dim3(cdiv(n, 64)), dim3(64), 0, s, n, p, k, x, y, z, j,
+                     j + (size_t)(p + 1) * n);
+}
+
+void launch_qfill(const std::vector<QFillArgs> &h, int p, int M1, int rows_h, double k, const double *nodes,
+                  hipStream_t s) {
   const int W = (int)h.size();
   if (W == 0) return;
-  const int M1sq = h[0].M1 * h[0].M1;
+  MFS_REQUIRE(p <= MAXP, "harmonic degree p exceeds 96");
+  const int nn = 2 * M1 * M1, rows = 4 * M1 * M1;
   int nrbmax = 0;
   for (const auto &a : h) {
-    MFS_REQUIRE(a.p <= MAXP, "harmonic degree p exceeds 96");
-    MFS_REQUIRE(a.M1 == h[0].M1 && a.p == h[0].p, "one wall grid and degree per batch");
     nrbmax = std::max(nrbmax, a.nrb);
-    const long n = (long)a.ldq * ((a.p + 1) * (a.p + 1) + 2 * a.nrb);
-    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)std::min<long>(4096, (n + 255) / 256)), dim3(256), 0, s,
-                       a.Q, n);
+    if (rows_h == rows) continue;
+    for (int par = 0; par < 2; ++par) {   // more columns than rows: zero rows below (every other row is written)
+      const long n = (long)a.ldq * ((par ? p * (p + 1) / 2 : (p + 1) * (p + 2) / 2) + a.nrb);
+      hipLaunchKernelGGL(zero_kernel, dim3((unsigned)std::min<long>(4096, (n + 255) / 256)), dim3(256), 0, s,
+                         a.Q[par], n);
+    }
   }
-  DevBuf args(h.size() * sizeof(QFillArgs));
+  DevBuf args(h.size() * sizeof(QFillArgs)), jt;
   HIP_CHECK(hipMemcpyAsync(args.p, h.data(), h.size() * sizeof(QFillArgs), hipMemcpyHostToDevice, s));
-  // every incidence in one grid: the harmonics of a wall node are a long
-  // serial evaluation per thread, so the incidences side by side fill the chip
-  hipLaunchKernelGGL(qfill_s_kernel, dim3(cdiv(4 * M1sq, 64), W), dim3(64), 0, s, args.as<QFillArgs>());
-  const long nw = (long)4 * M1sq * nrbmax;
+  bessel_table(nn, p, k, nodes, nodes + nn, nodes + 2 * nn, jt, s);
+  hipLaunchKernelGGL(qfill_s_kernel, dim3(cdiv(nn, 64), p + 1), dim3(64), 0, s, W, p, M1, k, nodes, jt.as<double>(),
+                     jt.as<double>() + (size_t)(p + 1) * nn, args.as<QFillArgs>());
+  const long nw = (long)rows * nrbmax;
   if (nw > 0)
-    hipLaunchKernelGGL(qfill_w_kernel, dim3((unsigned)std::min<long>(4096, (nw + 255) / 256), W), dim3(256), 0, s,
-                       args.as<QFillArgs>());
+    hipLaunchKernelGGL(qfill_w_kernel, dim3((unsigned)std::min<long>(4096, (nw + 255) / 256), W), dim3(256), 0, s, p,
+                       M1, nodes, args.as<QFillArgs>());
   HIP_CHECK(hipGetLastError());
   HIP_CHECK(hipStreamSynchronize(s));   // the argument array is released on return
 }
 
+void launch_split_walls(int nw, int M1, const double2 *in, double2 *out, int rows_h, hipStream_t s) {
+  const long n = (long)nw * rows_h;
+  hipLaunchKernelGGL(split_walls_kernel, dim3((unsigned)std::min<long>(1024, (n + 255) / 256)), dim3(256), 0, s, nw,
+                     M1, in, out, rows_h);
+  HIP_CHECK(hipGetLastError());
+}
+
+void launch_merge_xi(int nw, int p, int nqmax, const int *nrb, const double2 *xh, int ldh, double2 *xi, int ldx,
+                     hipStream_t s) {
+  hipLaunchKernelGGL(merge_xi_kernel, dim3(cdiv(nqmax, 256), nw), dim3(256), 0, s, nw, p, nrb, xh, ldh, xi, ldx);
+  HIP_CHECK(hipGetLastError());
+}
+
 void launch_bfill(int M, int p, double k, const double *rho, const double *z, const double *nrho,
                   const double *nz, double2 *out, hipStream_t s, int value) {
-  MFS_REQUIRE(p <= MAXP, "harmonic degree p exceeds 96");
-  hipLaunchKernelGGL(bfill_kernel, dim3(cdiv(M, 64)), dim3(64), 0, s, M, p, k, rho, z, nrho, nz, out, value);
+  DevBuf jt;
+  bessel_table(M, p, k, rho, nullptr, z, jt, s);
+  hipLaunchKernelGGL(bfill_kernel, dim3(cdiv(M, 64), p + 1), dim3(64), 0, s, M, p, k, rho, z, nrho, nz,
+                     jt.as<double>(), jt.as<double>() + (size_t)(p + 1) * M, out, value);
   HIP_CHECK(hipGetLastError());
 }
 
@@ -352,8 +423,7 @@ void launch_bapply(int nrhs, int P, int M, int p, const double2 *B, const double
 void launch_harm_field(int nrhs, int nt, const double *xyz, int p, double k, const double2 *d,
                        int ldd, double2 *out, hipStream_t s) {
   MFS_REQUIRE(p <= MAXP, "harmonic degree p exceeds 96");
-  hipLaunchKernelGGL(harm_field_kernel, dim3(cdiv(nt, 64)), dim3(64), 0, s, nrhs, nt, xyz, p, k, d, ldd,
-                     out);
+  hipLaunchKernelGGL(harm_field_kernel, dim3(nt), dim3(HF), 0, s, nrhs, nt, xyz, p, k, d, ldd, out);
   HIP_CHECK(hipGetLastError());
 }
 

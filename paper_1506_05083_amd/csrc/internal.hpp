@@ -270,19 +270,40 @@ void lowrank_apply(const NearLowRank &lr, int nrhs, const double2 *sigma, const 
                    size_t ldo, void *work, hipStream_t s);
 
 // ----------------------------------------------------------- harmonics
-// Fill rows of Q (S block and -W blocks) for one wave.
+// Q = [S, -W] in two halves.  The unit cell is its own mirror image under
+// z -> -z (Gauss nodes on the walls, T onto D), H_lm has the parity
+// (-1)^(l+m), and the Rayleigh-Bloch columns a_o on T and b_o on D are
+// exchanged.  In the orthonormal bases (row(z) +- row(-z)) / sqrt 2 of the
+// rows (the z derivative on T and D with the opposite sign) and
+// (a_o +- b_o) / sqrt 2 of the columns, Q is block diagonal: the even half has
+// the harmonics of even l + m and the sums, the odd half the odd ones and the
+// differences; column norms and singular values are those of Q.  The QR takes a
+// quarter of the flops and U half the bytes (8 waves, 4608 x 1275: the
+// periodizer's 44 ms are 18, an apply of Q^+ 190 us are 105).  Each half has
+// 4 M1^2 rows, R - alpha L value and derivative at z > 0 (M1^2 / 2 rows each),
+// F - beta B likewise, T value and derivative (M1^2 each), and the columns
+// (l, m) in order of l and m, then the orders.
 struct QFillArgs {
-  double k, ex, ey, z0;
-  int p, M1, nrb;
+  int nrb;
   double2 alpha, beta;
-  const double *wall;     // SoA x y z of the 6 walls: R L F B T D, each M1^2
   const double *kx, *ky;  // [nrb]
   const double2 *kz;      // [nrb]
-  double2 *Q;             // column-major [8 M1^2][ldq]
+  double2 *Q[2];          // the even and the odd half, column-major, ldq
   int ldq;
 };
-// Q of every incidence of a batch (same wall grid and degree), zeroed then filled
-void launch_qfill(const std::vector<QFillArgs> &h, hipStream_t s);
+inline int half_cols(int p, int par) { return par ? p * (p + 1) / 2 : (p + 1) * (p + 2) / 2; }
+// nodes of the half system, SoA [2 M1^2] (R, F at z > 0, T)
+void half_nodes(int M1, const std::vector<double> &wall, std::vector<double> &out);
+// both halves of Q of every incidence of a batch (same wall grid and degree);
+// rows_h >= 4 M1^2: rows past 4 M1^2 are zero
+void launch_qfill(const std::vector<QFillArgs> &h, int p, int M1, int rows_h, double k, const double *nodes,
+                  hipStream_t s);
+// wall sums (walls_plan groups) to the halves' right-hand sides [2 nw][rows_h]
+void launch_split_walls(int nw, int M1, const double2 *in, double2 *out, int rows_h, hipStream_t s);
+// the halves' coefficients xh [2 nw][ldh] to xi [nw][ldx] in Q's column order
+// (harmonics, a, b); nrb: orders of every wave (device)
+void launch_merge_xi(int nw, int p, int nqmax, const int *nrb, const double2 *xh, int ldh, double2 *xi, int ldx,
+                     hipStream_t s);
 // Btilde: values dH_lm/dn (value = 0) or H_lm (value = 1) at the surface
 // rings (phi = 0): out [NH][M]
 void launch_bfill(int M, int p, double k, const double *rho, const double *z, const double *nrho,

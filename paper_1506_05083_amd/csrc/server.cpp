@@ -46,11 +46,11 @@ struct Finished {
 struct Slot {
   int state = 0;   // 0 free, 1 admitting, 2 factored (joins at the next iteration), 3 iterating
   Request req;
-  MatDesc qd{};   // Q^+ factors in the slot's own storage (slot_fac)
+  MatDesc qd[2]{};   // Q^+ factors of both halves in the slot's own storage (slot_fac)
   cplx al = 1.0, be = 1.0;
   double kv[3] = {0.0, 0.0, 0.0};
   std::vector<RBOrder> orders;
-  int qrank = 0;
+  int qrank[2] = {0, 0};
   bool q_converged = true;   // the Jacobi SVD of the wave's Q (if one ran) converged
   // GMRES
   int j = 0;
@@ -72,11 +72,12 @@ struct mfs_server {
   hipStream_t s_it = nullptr, s_ad = nullptr;
   std::unique_ptr<mfs::Solver> it;      // the slot pool: plans, near field, B~, bases, work
   mfs::DevBuf qd, zero;                 // Q^+ descriptors of the slots; zeros for empty ones
-  // every slot's Q^+ factors, U (rows x NQb, leading dimension ldq) then W
-  // (round_up(NQb, 16) x NQb), and the slots' kept ranks: allocated with the
-  // server, so the factors of the waves in flight never add memory
+  // every slot's Q^+ factors, for each half U (rows_h x NQh, leading dimension
+  // ldq) then W (round_up(NQh, 16) x NQh), and the halves' kept ranks:
+  // allocated with the server, so the factors of the waves in flight never add
+  // memory
   mfs::DevBuf slot_fac, slot_rank;
-  size_t slot_stride = 0;
+  size_t half_stride = 0;
   std::vector<mfs::MatDesc> hq;
   std::vector<mfs::Slot> slots;
   std::mutex mu;
@@ -100,7 +101,7 @@ namespace {
 MatDesc empty_desc(mfs_server *sv) {
   MatDesc e{};
   e.m = 0;
-  e.n = sv->it->NQmax;
+  e.n = sv->it->NQh;
   e.lda = 1;
   e.ldg = 1;
   e.u = sv->zero.as<double2>();
@@ -159,16 +160,16 @@ void admit(mfs_server *sv, const std::vector<int> &ks, const std::vector<Request
   A.gp.release_work();
   // the factors move into the slots' own storage; the group's arenas go
   // when A does, at the end of this call
-  std::vector<MatDesc> sq(g);
-  for (int i = 0; i < g; ++i) {
+  std::vector<MatDesc> sq(2 * g);
+  for (int i = 0; i < 2 * g; ++i) {
     const MatDesc &f = A.gp.h_fin[i];
-    const int kept = A.qrank[i];
-    char *base = static_cast<char *>(sv->slot_fac.p) + (size_t)ks[i] * sv->slot_stride;
+    const int kept = A.qrank[i], h = 2 * ks[i / 2] + i % 2;
+    char *base = static_cast<char *>(sv->slot_fac.p) + (size_t)h * sv->half_stride;
     MatDesc d = f;
     d.u = reinterpret_cast<double2 *>(base);
-    d.w = reinterpret_cast<double2 *>(base + (size_t)f.lda * sv->it->NQmax * sizeof(double2));
-    d.rank = sv->slot_rank.as<int>() + ks[i];
-    MFS_REQUIRE(f.lda == sv->it->ldq && f.ldg <= round_up(sv->it->NQmax, 16) && kept <= sv->it->NQmax,
+    d.w = reinterpret_cast<double2 *>(base + (size_t)sv->it->ldq * sv->it->NQh * sizeof(double2));
+    d.rank = sv->slot_rank.as<int>() + h;
+    MFS_REQUIRE(f.lda <= sv->it->ldq && f.ldg <= round_up(sv->it->NQh, 16) && kept <= sv->it->NQh,
                 "server: factors larger than a slot's storage");
     if (kept > 0) {
       HIP_CHECK(hipMemcpyAsync(d.u, f.u, (size_t)f.lda * kept * sizeof(double2), hipMemcpyDeviceToDevice, s));
@@ -204,12 +205,14 @@ void admit(mfs_server *sv, const std::vector<int> &ks, const std::vector<Request
   std::lock_guard<std::mutex> lk(sv->mu);
   for (int i = 0; i < g; ++i) {
     Slot &sl = sv->slots[ks[i]];
-    sl.qd = sq[i];
+    for (int h = 0; h < 2; ++h) {
+      sl.qd[h] = sq[2 * i + h];
+      sl.qrank[h] = A.qrank[2 * i + h];
+    }
     sl.al = A.al[i];
     sl.be = A.be[i];
     for (int c = 0; c < 3; ++c) sl.kv[c] = A.kv[3 * i + c];
     sl.orders = A.orders[i];
-    sl.qrank = A.qrank[i];
     sl.q_converged = A.gp.jacobi_unconverged == 0;
     sl.j = 0;
     sl.beta0 = beta0[i];
@@ -301,8 +304,10 @@ void iter_loop(mfs_server *sv) {
             S.be[k] = sl.be;
             for (int c = 0; c < 3; ++c) S.kv[3 * k + c] = sl.kv[c];
             S.orders[k] = sl.orders;
-            S.qrank[k] = sl.qrank;
-            sv->hq[k] = sl.qd;
+            for (int h = 0; h < 2; ++h) {
+              S.qrank[2 * k + h] = sl.qrank[h];
+              sv->hq[2 * k + h] = sl.qd[h];
+            }
             joined = true;
           }
           if (sl.state == 3) act.push_back(k);
@@ -310,7 +315,8 @@ void iter_loop(mfs_server *sv) {
       }
       if (joined || descs_dirty) {
         S.upload_weights();
-        upload(sv->qd.p, sv->hq.data(), W * sizeof(MatDesc), s);
+        S.upload_orders();
+        upload(sv->qd.p, sv->hq.data(), 2 * W * sizeof(MatDesc), s);
         descs_dirty = false;
       }
       // current vector of every iterating slot (zero elsewhere) -> operator
@@ -433,7 +439,7 @@ void iter_loop(mfs_server *sv) {
         for (auto &p : out) sv->done[p.first] = std::move(p.second);
         for (int k : fin) {
           sv->slots[k].state = 0;
-          sv->hq[k] = empty_desc(sv);
+          sv->hq[2 * k] = sv->hq[2 * k + 1] = empty_desc(sv);
         }
         descs_dirty = true;
         sv->cv_ad.notify_all();
@@ -484,39 +490,35 @@ mfs_status mfs_server_create(mfs_ctx *ctx, const mfs_op *op, int32_t body, const
     const int W = cfg->slots;
     // widest Q of any incidence: (p+1)^2 harmonics + 2 x the Rayleigh-Bloch
     // orders, at most the lattice points of a disc of radius pi N0
-    const int NH = (lat->p + 1) * (lat->p + 1);
     const int ob = ((int)std::ceil(lat->N0 * lat->ex) + 3) * ((int)std::ceil(lat->N0 * lat->ey) + 3);
-    const int NQb = NH + 2 * ob;
-    const double rows = 8.0 * lat->M1 * lat->M1;
-    sv->wave_work_bytes = (4.0 * rows * NQb + 8.0 * (double)NQb * NQb) * sizeof(double2);
+    sv->it.reset(new Solver(op, b, *lat, W, cfg->maxit, sv->s_it));
+    Solver &S = *sv->it;
+    S.size_halves(ob);
+    sv->wave_work_bytes = 2.0 * (4.0 * S.rows_h * S.NQh + 8.0 * (double)S.NQh * S.NQh) * sizeof(double2);
     const double basis = (double)W * (cfg->maxit + 1) * b.P * b.rows * sizeof(double2);
-    const int ldq = round_up((int)rows, 16);
-    sv->slot_stride = ((size_t)ldq * NQb + (size_t)round_up(NQb, 16) * NQb) * sizeof(double2);
-    const double need = basis + (double)W * sv->slot_stride + sv->wave_work_bytes;
+    sv->half_stride = ((size_t)S.ldq * S.NQh + (size_t)round_up(S.NQh, 16) * S.NQh) * sizeof(double2);
+    const double need = basis + 2.0 * W * sv->half_stride + sv->wave_work_bytes;
     if ((double)cfg->hbm_budget < need)
       MFS_THROW(MFS_ENOMEM, "server: hbm_budget below the slots' storage and one wave's factorisation");
     size_t in0 = 0, in1 = 0;
     pool_stats(ctx->device, &in0, nullptr, nullptr);
-    sv->it.reset(new Solver(op, b, *lat, W, cfg->maxit, sv->s_it));
-    Solver &S = *sv->it;
-    S.NQmax = NQb;
     S.al.assign(W, 1.0);
     S.be.assign(W, 1.0);
     S.kv.assign(3 * W, 0.0);
     S.orders.assign(W, {});
-    S.qrank.assign(W, 0);
+    S.qrank.assign(2 * W, 0);
     S.near_limit = (size_t)std::max(0.0, (double)cfg->hbm_budget - need);
     S.setup_bvals();
     S.setup_sums();
     S.time_nsum = false;
-    sv->slot_fac.alloc((size_t)W * sv->slot_stride);
-    sv->slot_rank.alloc((size_t)W * sizeof(int));
+    sv->slot_fac.alloc((size_t)2 * W * sv->half_stride);
+    sv->slot_rank.alloc((size_t)2 * W * sizeof(int));
     sv->zero.alloc(4096);
     HIP_CHECK(hipMemsetAsync(sv->zero.p, 0, 4096, sv->s_it));
-    sv->qd.alloc((size_t)W * sizeof(MatDesc));
-    sv->hq.assign(W, empty_desc(sv));
+    sv->qd.alloc((size_t)2 * W * sizeof(MatDesc));
+    sv->hq.assign(2 * W, empty_desc(sv));
     S.qdesc = sv->qd.as<MatDesc>();
-    upload(sv->qd.p, sv->hq.data(), W * sizeof(MatDesc), sv->s_it);
+    upload(sv->qd.p, sv->hq.data(), 2 * W * sizeof(MatDesc), sv->s_it);
     HIP_CHECK(hipStreamSynchronize(sv->s_it));
     // held for the server's life: what the set-up above allocated (measured;
     // at least the bases, the slots' storage and the stored near field), and
@@ -524,7 +526,7 @@ mfs_status mfs_server_create(mfs_ctx *ctx, const mfs_op *op, int32_t body, const
     // forms their amplitudes and fields: eta, the q_field-node strengths and
     // the target sums with up to 51 partial slices)
     pool_stats(ctx->device, &in1, nullptr, nullptr);
-    const double listed = basis + (double)W * sv->slot_stride + (double)S.psurf.dense_bytes +
+    const double listed = basis + 2.0 * W * sv->half_stride + (double)S.psurf.dense_bytes +
                           (double)S.pwalls.dense_bytes;
     const double ntp = (double)round_up(std::max(cfg->ntargets, 1), 64);
     const double recover = 16.0 * W * ((double)b.P * b.rows + (double)cfg->q_field * b.N + 51.0 * ntp) +

@@ -23,26 +23,24 @@ void launch_dft_ld(int nr, int P, int X, const double2 *in, size_t ld_in, double
 
 using cplx = std::complex<double>;
 
-struct QStore {
-  DevBuf a, fac;
-  MatDesc d{};
-};
-
 struct Solver {
   const mfs_op *op;
   BodyData &b;
   mfs_lattice lat;
-  int W, P, M, N, MP, NH, rows, ldq, NQmax, maxit;
+  int W, P, M, N, MP, NH, NQmax, maxit;
+  // the two halves of Q (internal.hpp): rows (4 M1^2, more where a half would
+  // have more columns than that; zero rows then), leading dimension, columns
+  int rows_h, ldq, NQh;
   int Mr, Nc;   // per-mode system rows and columns (2M x 2N for transmission)
   hipStream_t s;
   std::vector<cplx> al, be;
   std::vector<double> kv;
   std::vector<std::vector<RBOrder>> orders;
   // periodizer
-  std::vector<QStore> Q;
-  DevBuf qflags, qdescs, Bvals, Bvals_v, walls_soa;
+  std::vector<DevBuf> Q;            // both halves of a wave's Q, one after the other
+  DevBuf qflags, Bvals, Bvals_v, qnodes, qnrb;
   std::vector<MatDesc> h_qdescs;
-  std::vector<int> qrank;
+  std::vector<int> qrank;           // kept rank of every half [2 W]
   GradedPinv gp;
   bool qreflect = false;            // let a full-rank Q keep its QR's reflectors instead of forming U = Q_1
   DevBuf QHW;                       // work of the reflector apply
@@ -55,7 +53,7 @@ struct Solver {
   std::shared_ptr<NearLowRank> lowrank;
   DevBuf LRW;
   // work
-  DevBuf V, Z, XIN, C, SIG, GS, GH, WR, CY, XI, PART, PART2, YW, H1, SC;
+  DevBuf V, Z, XIN, C, SIG, GS, GH, WR, CY, XIH, XI, PART, PART2, YW, H1, SC;
   int nsplit_s = 1, nsplit_w = 1;
   // timing: events around every neighbour-sum launch, the dense bytes each streamed
   std::vector<hipEvent_t> nsum_ev;
@@ -71,39 +69,53 @@ struct Solver {
       : op(o), b(body), lat(l), W(nw), maxit(mi), s(st) {
     P = b.P; M = b.M; N = b.N; Mr = b.rows; Nc = b.cols; MP = P * Mr;
     NH = (lat.p + 1) * (lat.p + 1);
-    rows = 8 * lat.M1 * lat.M1;
-    ldq = round_up(rows, 16);
+    NQmax = NQh = rows_h = ldq = 0;
+  }
+  // sizes of the halves for waves of at most nrb Rayleigh-Bloch orders
+  void size_halves(int nrb) {
+    NQmax = NH + 2 * nrb;
+    NQh = half_cols(lat.p, 0) + nrb;
+    rows_h = std::max(4 * lat.M1 * lat.M1, NQh);
+    ldq = round_up(rows_h, 16);
   }
   ~Solver() {
     for (auto e : nsum_ev) (void)hipEventDestroy(e);
   }
 
   void setup_periodizer(double rel_cutoff) {
-    // walls
-    std::vector<double> wall;
+    std::vector<double> wall, nodes;
     wall_nodes(lat, wall);
-    walls_soa.alloc(wall.size() * sizeof(double));
-    upload(walls_soa.p, wall.data(), wall.size() * sizeof(double), s);
-    qflags.alloc((size_t)2 * W * sizeof(int));
+    half_nodes(lat.M1, wall, nodes);
+    qnodes.alloc(nodes.size() * sizeof(double));
+    upload(qnodes.p, nodes.data(), nodes.size() * sizeof(double), s);
+    const int NM = 2 * W;
+    qflags.alloc((size_t)2 * NM * sizeof(int));
     int *flags = qflags.as<int>();
     Q.resize(W);
-    h_qdescs.resize(W);
-    NQmax = 0;
+    h_qdescs.resize(NM);
+    int nrbmax = 0;
+    for (int w = 0; w < W; ++w) {
+      const int nrb = (int)orders[w].size();
+      nrbmax = std::max(nrbmax, nrb);
+      MFS_REQUIRE(NH + 2 * nrb <= 8 * lat.M1 * lat.M1, "periodizer: Q has more columns than rows (raise M1)");
+    }
+    size_halves(nrbmax);
     std::vector<DevBuf> ordbufs(W);
     std::vector<QFillArgs> qargs(W);
     for (int w = 0; w < W; ++w) {
       const int nrb = (int)orders[w].size();
-      const int NQ = NH + 2 * nrb;
-      NQmax = std::max(NQmax, NQ);
-      MFS_REQUIRE(NQ <= rows, "periodizer: Q has more columns than rows (raise M1)");
-      QStore &q = Q[w];
-      q.a.alloc((size_t)ldq * NQ * sizeof(double2));
-      MatDesc &d = q.d;
-      d = MatDesc{};
-      d.a = q.a.as<double2>(); d.m = rows; d.n = NQ; d.lda = ldq;
-      d.flag = flags + w;
-      d.rank = flags + W + w;
-      h_qdescs[w] = d;
+      const int nc[2] = {half_cols(lat.p, 0) + nrb, half_cols(lat.p, 1) + nrb};
+      Q[w].alloc((size_t)ldq * (nc[0] + nc[1]) * sizeof(double2));
+      QFillArgs a{};
+      for (int par = 0; par < 2; ++par) {
+        MatDesc d{};
+        d.a = Q[w].as<double2>() + (par ? (size_t)ldq * nc[0] : 0);
+        d.m = rows_h; d.n = nc[par]; d.lda = ldq;
+        d.flag = flags + 2 * w + par;
+        d.rank = flags + NM + 2 * w + par;
+        h_qdescs[2 * w + par] = d;
+        a.Q[par] = d.a;
+      }
       // Rayleigh-Bloch data
       std::vector<double> kx(nrb), ky(nrb);
       std::vector<double2> kz(nrb);
@@ -113,34 +125,28 @@ struct Solver {
         kz[o] = cz(orders[w][o].kz.real(), orders[w][o].kz.imag());
       }
       ordbufs[w].alloc((size_t)std::max(1, nrb) * (2 * sizeof(double) + sizeof(double2)));
-      double *kxd = ordbufs[w].as<double>();
+      double2 *kzd = ordbufs[w].as<double2>();
+      double *kxd = reinterpret_cast<double *>(kzd + nrb);
       double *kyd = kxd + nrb;
-      double2 *kzd = reinterpret_cast<double2 *>(kyd + nrb);
       if (nrb > 0) {
         upload(kxd, kx.data(), nrb * sizeof(double), s);
         upload(kyd, ky.data(), nrb * sizeof(double), s);
         upload(kzd, kz.data(), nrb * sizeof(double2), s);
       }
-      QFillArgs a{};
-      a.k = b.k; a.ex = lat.ex; a.ey = lat.ey; a.z0 = lat.z0;
-      a.p = lat.p; a.M1 = lat.M1; a.nrb = nrb;
+      a.nrb = nrb;
       a.alpha = cz(al[w].real(), al[w].imag());
       a.beta = cz(be[w].real(), be[w].imag());
-      a.wall = walls_soa.as<double>();
       a.kx = kxd; a.ky = kyd; a.kz = kzd;
-      a.Q = d.a; a.ldq = ldq;
+      a.ldq = ldq;
       qargs[w] = a;
     }
-    launch_qfill(qargs, s);
-    qdescs.alloc(W * sizeof(MatDesc));
-    upload(qdescs.p, h_qdescs.data(), W * sizeof(MatDesc), s);
-    HIP_CHECK(hipStreamSynchronize(s));   // ordbufs are released on return
-    progress("periodizer: Q filled for %d waves, %d x %d at most; factoring", W, rows, NQmax);
+    launch_qfill(qargs, lat.p, lat.M1, rows_h, b.k, qnodes.as<double>(), s);
+    progress("periodizer: Q filled for %d waves, two halves of %d x %d at most; factoring", W, rows_h, NQh);
     // Q's columns equilibrated: the harmonics of high degree are smaller than
     // the low ones by far more than the cutoff on the walls, and would
     // otherwise be dropped whatever their use
-    graded_pinv(gp, h_qdescs, rel_cutoff, kQPivotMinCols, s, true, qreflect);
-    if (gp.reflect) QHW.alloc(qh_apply_work(W, rows, rows));
+    graded_pinv(gp, h_qdescs, rel_cutoff, kQPivotMinCols, s, true, qreflect, true);
+    if (gp.reflect) QHW.alloc(qh_apply_work(NM, rows_h, rows_h));
     qrank = gp.kept;
     progress("periodizer: factored (%s; Jacobi %.0f ms, %d launches)",
              gp.direct ? "full rank, no SVD"
@@ -219,35 +225,47 @@ struct Solver {
     GS.alloc((size_t)W * psurf.ntarget_pad * sizeof(double2));
     GH.alloc((size_t)W * MP * sizeof(double2));
     WR.alloc((size_t)W * pwalls.ntarget_pad * sizeof(double2));
-    CY.alloc((size_t)W * rows * sizeof(double2));
+    CY.alloc((size_t)2 * W * rows_h * sizeof(double2));
+    XIH.alloc((size_t)2 * W * NQh * sizeof(double2));
     XI.alloc((size_t)W * NQmax * sizeof(double2));
+    qnrb.alloc((size_t)W * sizeof(int));
+    upload_orders();
     const size_t part = std::max((size_t)nsplit_s * W * psurf.ntarget_pad, (size_t)nsplit_w * W * pwalls.ntarget_pad);
     PART.alloc(part * sizeof(double2));
     // the wall sums' slices when they run in the surface sums' launch
     if (nsum_pair_fusable(psurf, pwalls, b.k, b.src_P.as<double>(), P * N, W))
       PART2.alloc((size_t)nsplit_w * W * pwalls.ntarget_pad * sizeof(double2));
-    YW.alloc(std::max((size_t)b.nd * 2 * W * Nc, (size_t)W * NQmax) * sizeof(double2));
+    YW.alloc(std::max((size_t)b.nd * 2 * W * Nc, (size_t)2 * W * NQh) * sizeof(double2));
     H1.alloc((size_t)W * (maxit + 2) * 2 * sizeof(double2));
     SC.alloc((size_t)W * sizeof(double));
   }
 
   const MatDesc *qpinv_descs() const { return qdesc ? qdesc : gp.apply_descs(); }
 
-  // XI = Q^+ CY for every wave: U^H then W, or, when the factorisation kept
-  // the QR's reflectors in place of U = Q_1 (the direct form), Q^H from the
-  // reflectors panel by panel, then W
-  void apply_qpinv() {
+  // number of Rayleigh-Bloch orders of every wave (after a wave changes)
+  void upload_orders() {
+    std::vector<int> n(W);
+    for (int w = 0; w < W; ++w) n[w] = (int)orders[w].size();
+    upload(qnrb.p, n.data(), W * sizeof(int), s);
+  }
+
+  // XI = Q^+ of the wall sums WR for every wave, half by half: U^H then W, or,
+  // when the factorisation kept the QR's reflectors in place of U = Q_1 (the
+  // direct form), Q^H from the reflectors panel by panel, then W
+  void walls_to_xi() {
+    launch_split_walls(W, lat.M1, WR.as<double2>(), CY.as<double2>(), rows_h, s);
     PinvJob j{};
-    j.mode = 1; j.nmat = W; j.P = P; j.nrhs = 1; j.ldx = rows; j.ldo = NQmax; j.maxcols = 1;
-    j.maxr = NQmax; j.maxm = rows; j.maxn = NQmax;
-    j.descs = qpinv_descs(); j.x = CY.as<double2>(); j.out = XI.as<double2>(); j.ywork = YW.as<double2>();
+    j.mode = 1; j.nmat = 2 * W; j.P = P; j.nrhs = 1; j.ldx = rows_h; j.ldo = NQh; j.maxcols = 1;
+    j.maxr = NQh; j.maxm = rows_h; j.maxn = NQh;
+    j.descs = qpinv_descs(); j.x = CY.as<double2>(); j.out = XIH.as<double2>(); j.ywork = YW.as<double2>();
     if (!qdesc && gp.reflect) {
-      launch_qh_apply(gp.qr_descs(), W, rows, NQmax, gp.qr_nb, CY.as<double2>(), rows, QHW.as<double2>(),
-                      YW.as<double2>(), NQmax, s);
+      launch_qh_apply(gp.qr_descs(), 2 * W, rows_h, NQh, gp.qr_nb, CY.as<double2>(), rows_h, QHW.as<double2>(),
+                      YW.as<double2>(), NQh, s);
       launch_pinv_apply_w(j, s);
     } else {
       launch_pinv_apply(j, s);
     }
+    launch_merge_xi(W, lat.p, NQmax, qnrb.as<int>(), XIH.as<double2>(), NQh, XI.as<double2>(), NQmax, s);
   }
 
   // phase weights of the neighbour sums from al, be (after a wave changes)
@@ -330,7 +348,7 @@ struct Solver {
   void amplitudes(int w, const double2 *xw, mfs_result &r) const {
     const auto &o = orders[w];
     const int nrb = (int)o.size();
-    r.q_rank = qrank.empty() ? 0 : qrank[w];
+    r.q_rank = qrank.empty() ? 0 : qrank[2 * w] + qrank[2 * w + 1];
     r.nq_cols = NH + 2 * nrb;
     double flux = 0.0, kz00 = 0.0;
     for (int i = 0; i < nrb; ++i) {
@@ -423,8 +441,7 @@ struct Solver {
   void c_then_qpinv(const double2 *cmodes) {
     launch_point_strengths(W, P, P, N, cmodes, SIG.as<double2>(), s, Nc);
     nsum(pwalls, wwalls, WR.as<double2>());
-    launch_combine_walls(W, lat.M1 * lat.M1, WR.as<double2>(), CY.as<double2>(), s);
-    apply_qpinv();
+    walls_to_xi();
   }
 
   // out = (I + A_else A_0^+ - B Q^+ C A_0^+) x
@@ -449,8 +466,7 @@ struct Solver {
     launch_axpby_op(W, MP, x, GH.as<double2>(), nullptr, out, s);
     // the wall rows reuse SIG computed above
     if (!fused) nsum(pwalls, wwalls, WR.as<double2>());
-    launch_combine_walls(W, lat.M1 * lat.M1, WR.as<double2>(), CY.as<double2>(), s);
-    apply_qpinv();
+    walls_to_xi();
     if (!b.trans()) {
       launch_bapply(W, P, M, lat.p, Bvals.as<double2>(), XI.as<double2>(), NQmax, out, s, M);
     } else {

@@ -616,6 +616,20 @@ __global__ __launch_bounds__(256) void jac_sort_kernel(const MatDesc *__restrict
   if (threadIdx.x == 0) d.rank[0] = rank;
 }
 
+// Kept ranks of a matrix given as two diagonal blocks (descs 2 i, 2 i + 1):
+// both are cut at rel_cutoff times the larger of their largest singular values.
+__global__ __launch_bounds__(256) void joint_rank_kernel(const MatDesc *__restrict__ descs, double rel_cutoff) {
+  const MatDesc a = descs[blockIdx.x & ~1], b = descs[blockIdx.x | 1], d = descs[blockIdx.x];
+  const double smax = fmax(a.n > 0 ? a.sv[0] : 0.0, b.n > 0 ? b.sv[0] : 0.0);
+  __shared__ int rank;
+  if (threadIdx.x == 0) rank = 0;
+  __syncthreads();
+  for (int i = threadIdx.x; i < d.n; i += blockDim.x)
+    if (d.sv[i] > rel_cutoff * smax) atomicAdd(&rank, 1);
+  __syncthreads();
+  if (threadIdx.x == 0) d.rank[0] = rank;
+}
+
 }  // namespace
 
 namespace {
@@ -761,12 +775,13 @@ JacStats jac_run(const MatDesc *descs, const std::vector<MatDesc> &h, int init_m
 }
 
 void jac_sort(const MatDesc *descs, const std::vector<MatDesc> &h, double rel_cutoff, hipStream_t s,
-              std::vector<int> &ranks) {
+              std::vector<int> &ranks, bool halves) {
   const int nmat = (int)h.size();
   int nmax = 0;
   for (const auto &d : h) nmax = std::max(nmax, d.n);
   hipLaunchKernelGGL(jac_sort_kernel, dim3(nmat), dim3(256), (size_t)std::max(nmax, 1) * sizeof(double), s,
                      descs, rel_cutoff);
+  if (halves) hipLaunchKernelGGL(joint_rank_kernel, dim3(nmat), dim3(256), 0, s, descs, rel_cutoff);
   HIP_CHECK(hipGetLastError());
   ranks.assign(nmat, 0);
   HIP_CHECK(hipMemcpyAsync(ranks.data(), h[0].rank, nmat * sizeof(int), hipMemcpyDeviceToHost, s));
