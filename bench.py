@@ -425,7 +425,15 @@ def main():
     near_alg = float(np.median([t["near_alg_bytes"] for t in tms]))
     near_modes = sorted({int(t["near_mode"]) for t in tms})
     nsum_share = float(np.median([t["nsum_avg"] * t["nsum_launches"] for t in tms])) / ms_step
-    if near_bytes > 0:
+    if near_modes[-1] == 4:
+        # expansions: every application reads the waves' matrices once
+        gbs = near_alg / (nsum_avg * 1e-3) / 1e9
+        roof_nsum = {"bound": "hbm", "kernel": "exp_gemv_kernel with the moments before it (A_else surface sums and C "
+                                               "wall sums by spherical-wave expansions; all waves, mean over launches)",
+                     "achieved": gbs, "peak": PEAK_HBM, "unit": "GB/s", "frac": gbs / PEAK_HBM, "traffic": None,
+                     "launch_ms": nsum_avg, "bytes_per_launch": near_alg,
+                     "fill_ms": float(np.median([t["near_fill_ms"] for t in tms])), "share_of_step": nsum_share}
+    elif near_bytes > 0:
         # stored near field: every launch streams the kernel values the
         # method needs once (the padding of the last 64-target tile of each
         # group is not counted; strengths and outputs are under 0.1%)
@@ -462,7 +470,7 @@ def main():
                "post_qr_ms": float(np.median([t["q_post_ms"] for t in tms])),
                "jacobi_ms": float(np.median([t["jacobi_ms"] for t in tms]))}
     # the dominant single kernel: the stored-near-field sum when it is used
-    if near_bytes > 0 or roof_nsum["share_of_step"] >= roof_qr["share_of_step"]:
+    if near_modes[-1] in (1, 2) or roof_nsum["share_of_step"] >= roof_qr["share_of_step"]:
         roofline, other = roof_nsum, roof_qr
     else:
         roofline, other = roof_qr, roof_nsum
@@ -487,7 +495,7 @@ def main():
         "batch_solve_ms_p99": float(np.percentile(solve_ms, 99)),
         "step_ms_max": float(max(1e3 * r[4] for r in recs)),
         "near_field": {0: "on the fly (budget 0)", 1: "stored", 2: "on the fly (did not fit)",
-                       3: "low-rank image blocks (did not fit)"}[near_modes[-1]],
+                       3: "low-rank image blocks (did not fit)", 4: "spherical-wave expansions"}[near_modes[-1]],
         "stage_ms": {k: float(np.median([t[k] for t in tms])) for k in ("rhs", "periodizer", "gmres", "recover")},
         "gmres_iters": [r.iters for r in res],
         "eps_flux_max": float(max(r.eps_flux for r in res)),

@@ -149,7 +149,7 @@ typedef struct {
                              of every task, and the rotation product applied
                              to G and V by the tasks that rotated             */
   double near_fill_ms;    /* filling the dense near field (0 if on the fly)  */
-  double near_bytes;      /* mean dense near-field bytes streamed by one of
+  double near_bytes;      /* mean near-field bytes streamed by one of
                              those launches (0 if evaluated on the fly)       */
   double near_alg_bytes;  /* the same without the padding of the last 64-target
                              tile of each group: the values the method needs */
@@ -160,7 +160,9 @@ typedef struct {
                              low-rank factors of the image blocks (the wall
                              sums on the fly); near_fill_ms is then the time
                              to build the factors (0 if an earlier solve on
-                             the same lattice built them)                    */
+                             the same lattice built them); 4: spherical-wave
+                             expansions, near_bytes then the bytes of the
+                             waves' matrices one application reads           */
   double q_qr_ms;         /* blocked Householder QR of the waves' Q (one batch) */
   double q_qr_flops;      /* its algorithmic flops, sum of 8 m n^2 - 8 n^3 / 3  */
   double q_post_ms;       /* the rest of Q^+: triangle inverse (or the SVD path)
@@ -365,6 +367,12 @@ mfs_status mfs_field_interior(const mfs_op *op, int32_t body, int32_t nrhs, int3
  * max_bytes bounds that storage: 0 evaluates the sums on the fly every
  * iteration; the default (UINT64_MAX) stores them whenever they fit with
  * 2 GiB of device memory to spare.  Results agree to rounding either way.
+ * Where the sources' and the surface's bounding spheres leave room between
+ * neighbouring copies and the body is large enough for it to pay, a solve
+ * keeps per wave the matrices of spherical-wave expansions of the sums
+ * instead, cut at 1e-15 of a source's field and bounded by max_bytes as well
+ * (the environment variable MFS_NEAR_EXPANSION: 0 never, 1 by that rule, 2
+ * wherever they converge; read at every solve).
  * Both forms split the sources of every 64-target tile into slices (one
  * workgroup each, at least 256 sources a slice) aiming at 6144 workgroups
  * per sum; the environment variable MFS_NSUM_WORKGROUPS, read once per

@@ -244,11 +244,12 @@ __global__ void zero_kernel(double2 *p, long n) {
 }
 
 // dH_lm/dn (value = 0) or H_lm at (rho_i, 0, z_i) with normal (nrho_i, 0,
-// nz_i): out[lm][i], one thread per (point, m); j, jp [p+1][M]
+// nz_i): out[lm][i], or, given, out_re[l (l + 1) / 2 + m][i] for m >= 0;
+// one thread per (point, m); j, jp [p+1][M]
 __global__ __launch_bounds__(64) void bfill_kernel(int M, int p, double k, const double *rho,
                                                    const double *z, const double *nrho,
                                                    const double *nz, const double *__restrict__ j,
-                                                   const double *__restrict__ jp, double2 *out, int value) {
+                                                   const double *__restrict__ jp, double2 *out, double *out_re, int value) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x, m = blockIdx.y;
   if (i >= M) return;
   const Sph s = sph_of(rho[i], 0.0, z[i]);
@@ -258,6 +259,10 @@ __global__ __launch_bounds__(64) void bfill_kernel(int M, int p, double k, const
     const double dr = k * jp[(size_t)l * M + i] * P, dth = jl * dP / s.r;
     // d/drho = st d/dr + ct/r d/dth ; d/dz = ct d/dr - st/r d/dth  (phi = 0)
     const double v = value ? jl * P : nr * (s.st * dr + s.ct * dth) + nzz * (s.ct * dr - s.st * dth);
+    if (out_re) {
+      out_re[((size_t)l * (l + 1) / 2 + m) * M + i] = v;
+      return;
+    }
     out[(size_t)lm_col(l, m) * M + i] = cz(v, 0.0);
     if (m > 0) out[(size_t)lm_col(l, -m) * M + i] = cz((m & 1) ? -v : v, 0.0);
   });
@@ -402,13 +407,21 @@ void launch_merge_xi(int nw, int p, int nqmax, const int *nrb, const double2 *xh
   HIP_CHECK(hipGetLastError());
 }
 
-void launch_bfill(int M, int p, double k, const double *rho, const double *z, const double *nrho,
-                  const double *nz, double2 *out, hipStream_t s, int value) {
+static void bfill(int M, int p, double k, const double *rho, const double *z, const double *nrho, const double *nz,
+                  double2 *out, double *out_re, hipStream_t s, int value) {
   DevBuf jt;
   bessel_table(M, p, k, rho, nullptr, z, jt, s);
   hipLaunchKernelGGL(bfill_kernel, dim3(cdiv(M, 64), p + 1), dim3(64), 0, s, M, p, k, rho, z, nrho, nz,
-                     jt.as<double>(), jt.as<double>() + (size_t)(p + 1) * M, out, value);
+                     jt.as<double>(), jt.as<double>() + (size_t)(p + 1) * M, out, out_re, value);
   HIP_CHECK(hipGetLastError());
+}
+void launch_bfill(int M, int p, double k, const double *rho, const double *z, const double *nrho,
+                  const double *nz, double2 *out, hipStream_t s, int value) {
+  bfill(M, p, k, rho, z, nrho, nz, out, nullptr, s, value);
+}
+void launch_bfill_real(int M, int p, double k, const double *rho, const double *z, const double *nrho,
+                       const double *nz, double *out, hipStream_t s, int value) {
+  bfill(M, p, k, rho, z, nrho, nz, nullptr, out, s, value);
 }
 
 void launch_bapply(int nrhs, int P, int M, int p, const double2 *B, const double2 *d, int ldd,

@@ -269,6 +269,44 @@ size_t lowrank_work_bytes(const NearLowRank &lr, int nrhs);
 void lowrank_apply(const NearLowRank &lr, int nrhs, const double2 *sigma, const double2 *w, double2 *out,
                    size_t ldo, void *work, hipStream_t s);
 
+// ------------------------------------------- near field by expansions
+// (multipole.hip).  Per wave one matrix per parity of l + m, column-major:
+// rows [0, row0) give the regular coefficients on the central copy (degree
+// pt), rows row0.. the periodizer half's wall rows; columns are the moments
+// (degree ps for the former, pw for the rows of R/L, F/B and T/D).
+constexpr int kExpMaxDegree = 64;
+struct ExpShape {
+  int ps, pt, pw[3], M1, row0, ldg;
+};
+struct ExpWave {
+  double2 alpha, beta;
+  double2 *G[2];   // null: an idle slot
+};
+struct NearExpansion {
+  ExpShape x;
+  int P, M, N, pm, pq, rows, ldx;   // pm: degree of the moments, pq: of the periodizer's harmonics
+  size_t wave_elems;                // entries of one wave's two matrices
+  double bytes_read;                // of them, bytes one product reads
+  double k, ex, ey;
+  DevBuf nodes, src_tab, tab, tab2, hdist, hank;
+  // degrees and sizes; false if the expansions do not converge fast enough
+  bool plan(const BodyData &b, const mfs_lattice &lat);
+  // the wave-independent tables.  Blocking.
+  void setup(const BodyData &b, const mfs_lattice &lat, hipStream_t s);
+  // the matrices of the waves h (G: wave_elems entries, even half first).  Blocking.
+  void build(const std::vector<ExpWave> &h, hipStream_t s) const;
+  // moments [2 W][ldx] of mode coefficients c [W][P][ldc]
+  void moments(int W, const double2 *c, int ldc, double2 *out, hipStream_t s) const;
+  // out [2 W][ldo >= rows] = G x; part: splits(W) times as much when that is above 1
+  int splits(int W) const;
+  void apply(int W, const ExpWave *waves, const double2 *xm, double2 *out, int ldo, double2 *part,
+             hipStream_t s) const;
+  // out = xin + the field of the regular coefficients Lc less the periodizer's
+  // xi (both in halves [2 W][..]) on the surface rings, [W][P][rows per mode]
+  void local(int W, const double2 *Lc, int ldl, const double2 *xi, int ldxi, const double2 *xin, double2 *out,
+             hipStream_t s) const;
+};
+
 // ----------------------------------------------------------- harmonics
 // Q = [S, -W] in two halves.  The unit cell is its own mirror image under
 // z -> -z (Gauss nodes on the walls, T onto D), H_lm has the parity
@@ -278,8 +316,8 @@ void lowrank_apply(const NearLowRank &lr, int nrhs, const double2 *sigma, const 
 // (a_o +- b_o) / sqrt 2 of the columns, Q is block diagonal: the even half has
 // the harmonics of even l + m and the sums, the odd half the odd ones and the
 // differences; column norms and singular values are those of Q.  The QR takes a
-// quarter of the flops and U half the bytes (8 waves, 4608 x 1275: the
-// periodizer's 44 ms are 18, an apply of Q^+ 190 us are 105).  Each half has
+// quarter of the flops and U half the bytes (8 waves, 4608 x 1275, with the
+// operator's build and the solve: 119 -> 92 ms; U^H x 137 -> 65 us).  Each half has
 // 4 M1^2 rows, R - alpha L value and derivative at z > 0 (M1^2 / 2 rows each),
 // F - beta B likewise, T value and derivative (M1^2 each), and the columns
 // (l, m) in order of l and m, then the orders.
@@ -308,6 +346,9 @@ void launch_merge_xi(int nw, int p, int nqmax, const int *nrb, const double2 *xh
 // rings (phi = 0): out [NH][M]
 void launch_bfill(int M, int p, double k, const double *rho, const double *z, const double *nrho,
                   const double *nz, double2 *out, hipStream_t s, int value = 0);
+// the same for m >= 0 only, real: out [(l (l + 1) / 2 + m)][M]
+void launch_bfill_real(int M, int p, double k, const double *rho, const double *z, const double *nrho,
+                       const double *nz, double *out, hipStream_t s, int value);
 // out[r][bin][m] -= sum_{(l,mm): mm = bin mod P} B[(l,mm)][m] d[r][(l,mm)] ; d stride ldd;
 // out has ldo entries per bin (M, or 2M with the value rows first)
 void launch_bapply(int nrhs, int P, int M, int p, const double2 *B, const double2 *d, int ldd,

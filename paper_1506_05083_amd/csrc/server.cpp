@@ -178,6 +178,7 @@ void admit(mfs_server *sv, const std::vector<int> &ks, const std::vector<Request
     HIP_CHECK(hipMemcpyAsync(d.rank, &A.qrank[i], sizeof(int), hipMemcpyHostToDevice, s));
     sq[i] = d;
   }
+  if (sv->it->ex) sv->it->build_expansion(ks, A.al, A.be, s);   // read-only tables, the slots' own matrices
   // right-hand sides and the first Krylov vector of every wave in its slot
   Solver &P = *sv->it;
   const int MP = P.MP;
@@ -316,6 +317,11 @@ void iter_loop(mfs_server *sv) {
       if (joined || descs_dirty) {
         S.upload_weights();
         S.upload_orders();
+        if (S.ex) {
+          std::vector<char> live(W, 0);
+          for (int k : act) live[k] = 1;
+          S.upload_expansion(live);
+        }
         upload(sv->qd.p, sv->hq.data(), 2 * W * sizeof(MatDesc), s);
         descs_dirty = false;
       }
@@ -509,7 +515,7 @@ mfs_status mfs_server_create(mfs_ctx *ctx, const mfs_op *op, int32_t body, const
     S.qrank.assign(2 * W, 0);
     S.near_limit = (size_t)std::max(0.0, (double)cfg->hbm_budget - need);
     S.setup_bvals();
-    S.setup_sums();
+    S.setup_sums(false);
     S.time_nsum = false;
     sv->slot_fac.alloc((size_t)2 * W * sv->half_stride);
     sv->slot_rank.alloc((size_t)2 * W * sizeof(int));

@@ -151,7 +151,7 @@ extern "C" mfs_status mfs_solve_incident(mfs_ctx *ctx, const mfs_op *op, int32_t
     S.setup_periodizer(rel_cutoff);
     HIP_CHECK(hipEventRecord(ev[2], s));
     S.setup_sums();
-    progress("near sums ready (%s)", S.psurf.dense.p ? "stored" : "on the fly");
+    progress("near sums ready (%s)", S.ex ? "expansions" : S.psurf.dense.p ? "stored" : "on the fly");
 
     // ---------------- GMRES (unrestarted, CGS2, lockstep over waves)
     const int MP = S.MP;

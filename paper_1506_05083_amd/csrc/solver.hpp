@@ -23,6 +23,14 @@ void launch_dft_ld(int nr, int P, int X, const double2 *in, size_t ld_in, double
 
 using cplx = std::complex<double>;
 
+// Expansions from this many times the bytes of one wave's matrices in stored
+// kernel values on.  Where the line lies, the small body (N = 40, P = 24,
+// M1 = 20; 255 MB stored against 59 MB a wave): a solve of 1, 2, 8 and 16 waves
+// takes 11.7, 11.0, 16.7 and 22.8 ms with expansions, 13.2, 12.6, 16.5 and
+// 21.4 ms with stored values; from k = 10 on (16 GB against 72 MB) 17 against
+// 60 ms for one wave, 42 against 92 ms for eight.
+constexpr double kExpMinRatio = 4.0;
+
 struct Solver {
   const mfs_op *op;
   BodyData &b;
@@ -52,6 +60,12 @@ struct Solver {
   // low-rank image blocks of the surface sums (when their stored values do not fit)
   std::shared_ptr<NearLowRank> lowrank;
   DevBuf LRW;
+  // near field by spherical-wave expansions: tables, the waves' matrices G
+  // and their descriptors, moments, products (regular coefficients, then the
+  // right-hand sides of Q^+) and partial products
+  std::unique_ptr<NearExpansion> ex;
+  DevBuf EG, EW, EM, EO, EP;
+  int ldo = 0;
   // work
   DevBuf V, Z, XIN, C, SIG, GS, GH, WR, CY, XIH, XI, PART, PART2, YW, H1, SC;
   int nsplit_s = 1, nsplit_w = 1;
@@ -60,7 +74,8 @@ struct Solver {
   std::vector<double> nsum_bytes, nsum_alg_bytes;
   // where the neighbour sums' kernel values come from: 0 evaluated on the fly
   // (near-field budget 0), 1 stored, 2 on the fly because the stored field
-  // did not fit the budget or the free device memory
+  // did not fit the budget or the free device memory, 3 low-rank image blocks,
+  // 4 expansions
   int near_mode = 0;
   bool time_nsum = true;
   double near_fill_ms = 0.0;
@@ -146,7 +161,7 @@ struct Solver {
     // the low ones by far more than the cutoff on the walls, and would
     // otherwise be dropped whatever their use
     graded_pinv(gp, h_qdescs, rel_cutoff, kQPivotMinCols, s, true, qreflect, true);
-    if (gp.reflect) QHW.alloc(qh_apply_work(NM, rows_h, rows_h));
+    
     qrank = gp.kept;
     progress("periodizer: factored (%s; Jacobi %.0f ms, %d launches)",
              gp.direct ? "full rank, no SVD"
@@ -156,7 +171,81 @@ struct Solver {
     setup_bvals();
   }
 
-  void setup_sums() {
+  // Take the near field from expansions where they converge and the point
+  // sums are long enough for them to pay.  The choice rests on the body and
+  // the lattice only, not on the number of waves, so that a wave's results are
+  // the same alone and in any batch.  MFS_NEAR_EXPANSION: 0 never, 1 by this
+  // rule (default), 2 wherever they converge.
+  bool setup_expansion() {
+    const char *e = std::getenv("MFS_NEAR_EXPANSION"), *lr = std::getenv("MFS_NEAR_LOWRANK");
+    const int mode = e ? std::atoi(e) : 1;
+    const uint64_t budget = std::min<uint64_t>(op->near_budget, (uint64_t)near_limit);
+    if (mode == 0 || budget == 0 || (lr && std::atoi(lr) == 2)) return false;
+    std::unique_ptr<NearExpansion> x(new NearExpansion);
+    if (!x->plan(b, lat)) return false;
+    // values a stored near field would read per iteration (mirror pairs once)
+    const double S = (double)P * N;
+    const double stored = 16.0 * S * (4.0 * MP + 30.0 * lat.M1 * lat.M1);
+    if (mode == 1 && stored < kExpMinRatio * x->bytes_read) return false;
+    const size_t need = (size_t)W * x->wave_elems * sizeof(double2);
+    if (need > budget || need + ((size_t)2 << 30) > device_free_bytes()) return false;
+    ex = std::move(x);
+    return true;
+  }
+
+  // the matrices of the waves ks (slots of this solver), phases al, be
+  void build_expansion(const std::vector<int> &ks, const std::vector<cplx> &a, const std::vector<cplx> &bb,
+                       hipStream_t st) const {
+    std::vector<ExpWave> h;
+    for (size_t i = 0; i < ks.size(); ++i) h.push_back(exp_wave(ks[i], a[i], bb[i]));
+    ex->build(h, st);
+  }
+  ExpWave exp_wave(int k, cplx a, cplx bb) const {
+    ExpWave v{};
+    v.alpha = cz(a.real(), a.imag());
+    v.beta = cz(bb.real(), bb.imag());
+    v.G[0] = EG.as<double2>() + (size_t)k * ex->wave_elems;
+    v.G[1] = v.G[0] + (size_t)ex->x.ldg * half_cols(ex->pm, 0);
+    return v;
+  }
+  // descriptors of the waves an iteration applies (live[w] = 0: skipped)
+  void upload_expansion(const std::vector<char> &live) {
+    std::vector<ExpWave> h(W);
+    for (int w = 0; w < W; ++w)
+      if (live[w]) h[w] = exp_wave(w, al[w], be[w]);
+    upload(EW.p, h.data(), W * sizeof(ExpWave), s);
+  }
+
+  void setup_sums(bool build_waves = true) {
+    if (setup_expansion()) {
+      hipEvent_t f0, f1;
+      HIP_CHECK(hipEventCreate(&f0));
+      HIP_CHECK(hipEventCreate(&f1));
+      HIP_CHECK(hipEventRecord(f0, s));
+      ex->setup(b, lat, s);
+      ldo = ex->x.row0 + rows_h;
+      EG.alloc((size_t)W * ex->wave_elems * sizeof(double2));
+      EW.alloc((size_t)W * sizeof(ExpWave));
+      EM.alloc((size_t)2 * W * ex->ldx * sizeof(double2));
+      EO.alloc((size_t)2 * W * ldo * sizeof(double2));
+      if (ex->splits(W) > 1) EP.alloc((size_t)ex->splits(W) * 2 * W * ldo * sizeof(double2));
+      if (build_waves) {
+        std::vector<int> ks(W);
+        for (int w = 0; w < W; ++w) ks[w] = w;
+        build_expansion(ks, al, be, s);
+      }
+      upload_expansion(std::vector<char>(W, build_waves ? 1 : 0));
+      HIP_CHECK(hipEventRecord(f1, s));
+      HIP_CHECK(hipEventSynchronize(f1));
+      float ms = 0.f;
+      HIP_CHECK(hipEventElapsedTime(&ms, f0, f1));
+      near_fill_ms = ms;
+      near_mode = 4;
+      (void)hipEventDestroy(f0);
+      (void)hipEventDestroy(f1);
+      work_buffers();
+      return;
+    }
     surface_plan(b, psurf, s);
     walls_plan(lat, b.P, b.N, pwalls, s);
     std::vector<double2> w1, w2;
@@ -216,25 +305,29 @@ struct Solver {
         }
       }
     }
-    // work buffers
-    V.alloc((size_t)W * (maxit + 1) * MP * sizeof(double2));
-    Z.alloc((size_t)W * MP * sizeof(double2));
-    XIN.alloc((size_t)W * MP * sizeof(double2));
-    C.alloc((size_t)W * P * Nc * sizeof(double2));
+    // work buffers of the point sums
     SIG.alloc((size_t)W * P * N * sizeof(double2));
     GS.alloc((size_t)W * psurf.ntarget_pad * sizeof(double2));
     GH.alloc((size_t)W * MP * sizeof(double2));
     WR.alloc((size_t)W * pwalls.ntarget_pad * sizeof(double2));
     CY.alloc((size_t)2 * W * rows_h * sizeof(double2));
-    XIH.alloc((size_t)2 * W * NQh * sizeof(double2));
-    XI.alloc((size_t)W * NQmax * sizeof(double2));
-    qnrb.alloc((size_t)W * sizeof(int));
-    upload_orders();
     const size_t part = std::max((size_t)nsplit_s * W * psurf.ntarget_pad, (size_t)nsplit_w * W * pwalls.ntarget_pad);
     PART.alloc(part * sizeof(double2));
     // the wall sums' slices when they run in the surface sums' launch
     if (nsum_pair_fusable(psurf, pwalls, b.k, b.src_P.as<double>(), P * N, W))
       PART2.alloc((size_t)nsplit_w * W * pwalls.ntarget_pad * sizeof(double2));
+    work_buffers();
+  }
+
+  void work_buffers() {
+    V.alloc((size_t)W * (maxit + 1) * MP * sizeof(double2));
+    Z.alloc((size_t)W * MP * sizeof(double2));
+    XIN.alloc((size_t)W * MP * sizeof(double2));
+    C.alloc((size_t)W * P * Nc * sizeof(double2));
+    XIH.alloc((size_t)2 * W * NQh * sizeof(double2));
+    XI.alloc((size_t)W * NQmax * sizeof(double2));
+    qnrb.alloc((size_t)W * sizeof(int));
+    upload_orders();
     YW.alloc(std::max((size_t)b.nd * 2 * W * Nc, (size_t)2 * W * NQh) * sizeof(double2));
     H1.alloc((size_t)W * (maxit + 2) * 2 * sizeof(double2));
     SC.alloc((size_t)W * sizeof(double));
@@ -249,27 +342,56 @@ struct Solver {
     upload(qnrb.p, n.data(), W * sizeof(int), s);
   }
 
-  // XI = Q^+ of the wall sums WR for every wave, half by half: U^H then W, or,
+  // XIH = Q^+ y for every wave, half by half (y [2 W][ldy]): U^H then W, or,
   // when the factorisation kept the QR's reflectors in place of U = Q_1 (the
   // direct form), Q^H from the reflectors panel by panel, then W
-  void walls_to_xi() {
-    launch_split_walls(W, lat.M1, WR.as<double2>(), CY.as<double2>(), rows_h, s);
+  void apply_qpinv(const double2 *y, int ldy) {
     PinvJob j{};
-    j.mode = 1; j.nmat = 2 * W; j.P = P; j.nrhs = 1; j.ldx = rows_h; j.ldo = NQh; j.maxcols = 1;
+    j.mode = 1; j.nmat = 2 * W; j.P = P; j.nrhs = 1; j.ldx = ldy; j.ldo = NQh; j.maxcols = 1;
     j.maxr = NQh; j.maxm = rows_h; j.maxn = NQh;
-    j.descs = qpinv_descs(); j.x = CY.as<double2>(); j.out = XIH.as<double2>(); j.ywork = YW.as<double2>();
+    j.descs = qpinv_descs(); j.x = y; j.out = XIH.as<double2>(); j.ywork = YW.as<double2>();
     if (!qdesc && gp.reflect) {
-      launch_qh_apply(gp.qr_descs(), 2 * W, rows_h, NQh, gp.qr_nb, CY.as<double2>(), rows_h, QHW.as<double2>(),
-                      YW.as<double2>(), NQh, s);
+      if (!QHW.p) QHW.alloc(qh_apply_work(2 * W, rows_h, ldy));
+      // the reflector apply's work follows the input's stride
+      launch_qh_apply(gp.qr_descs(), 2 * W, rows_h, NQh, gp.qr_nb, y, ldy, QHW.as<double2>(), YW.as<double2>(), NQh,
+                      s);
       launch_pinv_apply_w(j, s);
     } else {
       launch_pinv_apply(j, s);
     }
+  }
+  void merge_xi() {
     launch_merge_xi(W, lat.p, NQmax, qnrb.as<int>(), XIH.as<double2>(), NQh, XI.as<double2>(), NQmax, s);
+  }
+  // XI = Q^+ of the wall sums WR
+  void walls_to_xi() {
+    launch_split_walls(W, lat.M1, WR.as<double2>(), CY.as<double2>(), rows_h, s);
+    apply_qpinv(CY.as<double2>(), rows_h);
+    merge_xi();
+  }
+
+  // EO = G (moments of the mode coefficients c), timed like a neighbour sum
+  void expansion_sums(const double2 *c) {
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (time_nsum) {
+      HIP_CHECK(hipEventCreate(&e0));
+      HIP_CHECK(hipEventCreate(&e1));
+      HIP_CHECK(hipEventRecord(e0, s));
+    }
+    ex->moments(W, c, Nc, EM.as<double2>(), s);
+    ex->apply(W, EW.as<ExpWave>(), EM.as<double2>(), EO.as<double2>(), ldo, EP.as<double2>(), s);
+    if (time_nsum) {
+      HIP_CHECK(hipEventRecord(e1, s));
+      nsum_ev.push_back(e0);
+      nsum_ev.push_back(e1);
+      nsum_bytes.push_back(W * ex->bytes_read);
+      nsum_alg_bytes.push_back(W * ex->bytes_read);
+    }
   }
 
   // phase weights of the neighbour sums from al, be (after a wave changes)
   void upload_weights() {
+    if (ex) return;
     std::vector<double2> w1, w2;
     image_weights(al, be, psurf, w1);
     walls_weights(al, be, pwalls, w2);
@@ -439,6 +561,12 @@ struct Solver {
 
   // XI = Q^+ (C c) for mode coefficients in C
   void c_then_qpinv(const double2 *cmodes) {
+    if (ex) {
+      expansion_sums(cmodes);
+      apply_qpinv(EO.as<double2>() + ex->x.row0, ldo);
+      merge_xi();
+      return;
+    }
     launch_point_strengths(W, P, P, N, cmodes, SIG.as<double2>(), s, Nc);
     nsum(pwalls, wwalls, WR.as<double2>());
     walls_to_xi();
@@ -447,6 +575,12 @@ struct Solver {
   // out = (I + A_else A_0^+ - B Q^+ C A_0^+) x
   void apply_op(const double2 *x, double2 *out) {
     pinv_A0(x, C.as<double2>());
+    if (ex) {
+      expansion_sums(C.as<double2>());
+      apply_qpinv(EO.as<double2>() + ex->x.row0, ldo);
+      ex->local(W, EO.as<double2>(), ldo, XIH.as<double2>(), NQh, x, out, s);
+      return;
+    }
     launch_point_strengths(W, P, P, N, C.as<double2>(), SIG.as<double2>(), s, Nc);
     // both stored fields in one launch when they can (the wall rows read the
     // same strengths), else the surface sums now and the wall sums below
