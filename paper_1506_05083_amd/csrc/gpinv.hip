@@ -65,9 +65,12 @@ __global__ __launch_bounds__(256) void colnorm_kernel(const MatDesc *__restrict_
   if (lane == 0) out[(size_t)blockIdx.y * ld + c] = sqrt(s);
 }
 
-// dst column i = src column perm[i], times scale[perm[i]] when scale is given
+// dst column i = src column perm[i], times scale[perm[i]] when scale is given;
+// only the matrices with only[w] != 0 when that is given
 __global__ void gather_kernel(const MatDesc *__restrict__ src, const MatDesc *__restrict__ dst,
-                              const int *__restrict__ perm, int ldp, const double *__restrict__ scale) {
+                              const int *__restrict__ perm, int ldp, const double *__restrict__ scale,
+                              const int *__restrict__ only) {
+  if (only && !only[blockIdx.y]) return;
   const MatDesc s = src[blockIdx.y], d = dst[blockIdx.y];
   const int i = blockIdx.x;
   if (i >= d.n) return;
@@ -693,6 +696,12 @@ static bool use_cod(bool equilibrate, bool pivot, int n2max) {
   return equilibrate && n2max >= kCodMinCols;
 }
 
+// Panels of the periodizer's QR: Cholesky QR, or MFS_QR_PANEL=steps.
+static bool chol_panels() {
+  const char *e = std::getenv("MFS_QR_PANEL");
+  return !(e && std::string(e) == "steps");
+}
+
 // The equilibrated columns of the periodizer's Q are usually independent well
 // within the cutoff; the truncated SVD then keeps every singular value and
 // the pseudoinverse is D P R^{-1} Q_1^H, with Q_1 R the QR of the ordered,
@@ -883,7 +892,9 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
   std::vector<size_t> oa(W), of(W);
   // panel width of the blocked QR of the ordered columns, measured for this
   // size class (qr_tuned_nb)
-  g.qr_nb = qr_tuned_nb(in, s);
+  // Cholesky panels where the columns are expected to be independent
+  const bool chol = equilibrate && chol_panels();
+  g.qr_nb = qr_tuned_nb(in, s, chol);
   const int nbq = g.qr_nb;
   {
     size_t ta = 0, tf = 0;
@@ -912,10 +923,32 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
   }
   upload_descs(g.d_qc, g.h_qc, s);
   hipLaunchKernelGGL(gather_kernel, dim3(n2max, W), dim3(256), 0, s, g.d_in.as<MatDesc>(), g.d_qc.as<MatDesc>(),
-                     g.perm.as<int>(), nmax, cscl);
+                     g.perm.as<int>(), nmax, cscl, nullptr);
   HIP_CHECK(hipGetLastError());
   EvPair qre(s);
-  qr_factor(g.d_qc.as<MatDesc>(), g.h_qc, s, nbq);
+  if (chol) {
+    DevBuf bad((size_t)cdiv(W, 4) * sizeof(double2));
+    launch_zero(bad.as<double2>(), cdiv(W, 4), s);
+    qr_factor(g.d_qc.as<MatDesc>(), g.h_qc, s, nbq, bad.as<int>());
+    std::vector<int> hb(W);
+    HIP_CHECK(hipMemcpyAsync(hb.data(), bad.p, W * sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_CHECK(hipStreamSynchronize(s));
+    // the matrices with nearly dependent columns again by column steps (each
+    // on its own verdict, so that a wave's factors do not depend on the others)
+    std::vector<MatDesc> redo;
+    for (int w = 0; w < W; ++w)
+      if (hb[w]) redo.push_back(g.h_qc[w]);
+    if (!redo.empty()) {
+      hipLaunchKernelGGL(gather_kernel, dim3(n2max, W), dim3(256), 0, s, g.d_in.as<MatDesc>(), g.d_qc.as<MatDesc>(),
+                         g.perm.as<int>(), nmax, cscl, bad.as<int>());
+      DevBuf dr;
+      upload_descs(dr, redo, s);
+      qr_factor(dr.as<MatDesc>(), redo, s, nbq);
+      HIP_CHECK(hipStreamSynchronize(s));
+    }
+  } else {
+    qr_factor(g.d_qc.as<MatDesc>(), g.h_qc, s, nbq);
+  }
   qre.stop(s);
   if (g.ev_qr_done) HIP_CHECK(hipEventRecord(g.ev_qr_done, s));
   g.qr_flops = 0.0;

@@ -128,8 +128,11 @@ JacStats jac_run(const MatDesc *descs, const std::vector<MatDesc> &h, int init_m
 
 // batched QR of nmat matrices described by descs (device) / h (host copy),
 // panels of nb = 16, 32 or 64 columns (each matrix's T holds cdiv(n, nb)
-// nb x nb factors)
-void qr_factor(const MatDesc *descs, const std::vector<MatDesc> &h, hipStream_t s, int nb = kQRNB);
+// nb x nb factors).  bad (device, one int per matrix, zeroed by the caller):
+// panels by Cholesky QR, for matrices of independent columns; a matrix they
+// cannot factor gets its flag set and void factors.
+void qr_factor(const MatDesc *descs, const std::vector<MatDesc> &h, hipStream_t s, int nb = kQRNB,
+               int *bad = nullptr);
 // Column-pivoted QR steps and forms (gpinv.hip, qrcp.hip, qrcp_sketch.hip):
 // the triangles of descs in place (R above the diagonal, reflectors below,
 // tau), piv[w][i] the original column at position i (identity on entry).
@@ -148,8 +151,8 @@ struct QRPanels32 {
   void panel(int K0, hipStream_t s);
 };
 // the panel width for a batch like h: measured once per size class and GPU
-// model (see qr.hip), or MFS_QR_NB
-int qr_tuned_nb(const std::vector<MatDesc> &h, hipStream_t s);
+// model (see qr.hip), or MFS_QR_NB; chol: with Cholesky panels
+int qr_tuned_nb(const std::vector<MatDesc> &h, hipStream_t s, bool chol = false);
 
 // y = A^+ x with the kept factors: job layout
 //   mode 0 (one-body blocks): mat d = distinct mode, columns = bins d and P-d

@@ -35,7 +35,8 @@ namespace mfs {
 namespace {
 
 constexpr int CH = 256;     // rows per workgroup in the panel column step
-constexpr int KRMIN = 256;  // fewest rows of a V^H Y split-K slice (sizes the partials' buffer)
+constexpr int KRMIN = 64;   // fewest rows of a V^H Y split-K slice
+constexpr int VHYWG = 256;  // workgroups a V^H Y launch aims at by cutting its slices shorter
 constexpr int KS = 16;      // rows per LDS stage in V^H Y
 // V^H Y tiles: YT columns of Y a workgroup, a wave IB x CB blocks of 16 x 16
 // of the NB x YT tile, OCC waves a SIMD, DB: LDS stages double-buffered (one
@@ -321,6 +322,278 @@ __global__ __launch_bounds__(PTMAX) void bqr_panel_kernel(const MatDesc *__restr
   }
 }
 
+// Panels of 16 columns by Cholesky QR with the reflectors reconstructed, for
+// matrices whose columns are independent (the periodizer's equilibrated Q):
+// the column steps above are a chain of 17 launches a panel, each a
+// reduction over all rows (16 matrices of 2304 rows: 8.3 us a launch, most of it
+// latency, 143 us a panel); this is three launches of two reductions (6, 17 and
+// 30 us), and the panel's T comes with them.
+//   cq_gram_kernel   G = P^H P over 256-row chunks (matrix cores);
+//   cq_solve_kernel  R1 = chol(G), P <- P R1^{-1} by row-wise substitution, and
+//                    the chunk sums of its Gram matrix;
+//   cq_reflect_kernel R2 = chol of that (Q = P R2^{-1} is orthonormal to
+//                    rounding, R = R2 R1), then LU of the top block less a
+//                    unitary diagonal S, Q_top - S = L U with s_j minus the
+//                    phase of the j-th pivot (Ballard, Demmel, Grigori,
+//                    Jacquelin, Nguyen and Solomonik 2014):
+//                    V = [L; Q_rest U^{-1}], tau_j = -u_jj conj(s_j), and the
+//                    panel's triangle S R.  The product of the reflectors is
+//                    the one whose first columns are Q S^{-1}, so T and the
+//                    updates proceed as after the column steps.
+// Every workgroup repeats the 16 x 16 factorisations (an entry a thread, the
+// step's row and column through LDS, one barrier a step) instead of waiting for
+// another launch.  The substitutions are row-wise
+// backward stable whatever the panel's conditioning; the orthogonality after
+// the second pass needs the first Cholesky's pivots above 1e-12 of the columns'
+// norms (condition below 1e6 after column scaling).  A pivot below sets the
+// matrix's flag and its factors are void: the caller factors it again by
+// column steps.
+constexpr int CQ = 16;
+constexpr double kCholPivotMin = 1e-12;
+
+// 16 x 16 Gram matrix over the 64 rows of each wave given by ld(row of the
+// wave, column), the waves' sums added through red; out[i * 16 + j]
+template <class F>
+__device__ inline void cq_gram(F ld, double2 (*red)[CQ * CQ], double2 *out) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c = lane & 15, k = lane >> 4;
+  dx4 re = {0, 0, 0, 0}, im = re;
+#pragma unroll
+  for (int s0 = 0; s0 < 16; s0 += 8) {
+    double2 x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = ld(64 * wv + 4 * (s0 + u) + k, c);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      re = mfma_f64(x[u].x, x[u].x, re);
+      re = mfma_f64(x[u].y, x[u].y, re);
+      im = mfma_f64(x[u].x, x[u].y, im);
+      im = mfma_f64(-x[u].y, x[u].x, im);
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[wv][(k + 4 * v) * CQ + c] = cz(re[v], im[v]);
+  __syncthreads();
+  double2 t = red[0][threadIdx.x];
+#pragma unroll
+  for (int w = 1; w < CH / 64; ++w) t = cadd(t, red[w][threadIdx.x]);
+  out[threadIdx.x] = t;
+}
+
+__global__ __launch_bounds__(CH) void cq_gram_kernel(const MatDesc *__restrict__ descs, int k0,
+                                                     double2 *__restrict__ part, int nchmax) {
+  const MatDesc d = descs[blockIdx.y];
+  const int r0 = k0 + blockIdx.x * CH;
+  if (k0 >= d.n || r0 >= d.m) return;
+  const int nbp = min(CQ, d.n - k0);
+  __shared__ double2 red[CH / 64][CQ * CQ];
+  cq_gram([&](int row, int c) {
+    return ld_or0(d.a, (size_t)(k0 + min(c, nbp - 1)) * d.lda + min(r0 + row, d.m - 1), c < nbp && r0 + row < d.m);
+  }, red, part + ((size_t)blockIdx.y * nchmax + blockIdx.x) * CQ * CQ);
+}
+
+// Sum of the chunks' Gram matrices (identity outside the nbp columns), the
+// entry (i, j) = (tid / 16, tid % 16) of each thread
+__device__ inline double2 cq_sum(const double2 *part, int nch, int nbp) {
+  const int i = threadIdx.x / CQ, j = threadIdx.x % CQ;
+  double2 t = cz(0.0, 0.0);
+#pragma unroll 4
+  for (int c = 0; c < nch; ++c) t = cadd(t, part[(size_t)c * CQ * CQ + threadIdx.x]);
+  return i >= nbp || j >= nbp ? cz(i == j ? 1.0 : 0.0, 0.0) : t;
+}
+
+// G = R^H R, entry g of each thread: R into Rs (upper), the reciprocals of its
+// diagonal into rinv; false (to every thread) if a pivot is at most pivot_min
+// of its column's norm.  Ls, g0: work.
+__device__ inline bool cq_chol(double2 g, double2 (*Ls)[CQ + 1], double *g0, double2 (*Rs)[CQ + 1], double *rinv,
+                               double pivot_min) {
+  const int i = threadIdx.x / CQ, k = threadIdx.x % CQ;
+  if (i == k) g0[i] = g.x;
+  bool ok = true;
+#pragma unroll 1
+  for (int j = 0; j < CQ; ++j) {
+    if (k == j && i >= j) Ls[i][j] = g;
+    __syncthreads();
+    double dj = Ls[j][j].x;
+    if (!(dj > pivot_min * g0[j])) {   // a NaN as well
+      ok = false;
+      dj = 1.0;
+    }
+    if (i > j && k > j) {
+      const double2 w = cscale(cmul(Ls[i][j], cconj(Ls[k][j])), 1.0 / dj);
+      g = csub(g, w);
+    }
+    if (i == j && k >= j) {   // row j of R from column j of L
+      const double rs = 1.0 / sqrt(dj);
+      Rs[j][k] = k == j ? cz(dj * rs, 0.0) : cscale(cconj(Ls[k][j]), rs);
+      if (k == j) rinv[j] = rs;
+    }
+  }
+  __syncthreads();
+  return ok;
+}
+
+// X <- X R^{-1}, X 16 x 16 with entry x of each thread (R upper, ri its
+// reciprocal diagonal, real or complex); the result also in Xs
+template <class D, class F>
+__device__ inline double2 cq_solve16(double2 x, double2 (*Xs)[CQ + 1], F R, const D *ri) {
+  const int i = threadIdx.x / CQ, k = threadIdx.x % CQ;
+#pragma unroll 1
+  for (int j = 0; j < CQ; ++j) {
+    if (k == j) {
+      if constexpr (sizeof(D) == sizeof(double)) x = cscale(x, ri[j]);
+      else x = cmul(x, ri[j]);
+      Xs[i][j] = x;
+    }
+    __syncthreads();
+    if (k > j) x = csub(x, cmul(Xs[i][j], R(j, k)));
+  }
+  return x;
+}
+
+// x <- x R^{-1} for one row x (R upper in Rs, reciprocal diagonal ri).  The
+// loads of column j are tied to x[j - 2] (an offset of zero that the compiler
+// cannot see through): issued all at once they would not fit the registers.
+template <class D>
+__device__ inline void cq_subst(double2 (&x)[CQ], const double2 (*Rs)[CQ + 1], const D *ri) {
+  int z = 0;
+#pragma unroll
+  for (int j = 0; j < CQ; ++j) {
+    if (j >= 2) asm volatile("" : "+v"(z) : "v"(x[j - 2].x));
+    const double2 *col = &Rs[0][0] + z + j;
+    double2 t = x[j];
+#pragma unroll
+    for (int i = 0; i < j; ++i) t = csub(t, cmul(x[i], col[i * (CQ + 1)]));
+    if constexpr (sizeof(D) == sizeof(double)) x[j] = cscale(t, ri[j]);
+    else x[j] = cmul(t, ri[j]);
+  }
+}
+
+// side: [mat][2][16 * 16]: the top block of P R1^{-1}, then R1
+__global__ __launch_bounds__(CH) void cq_solve_kernel(const MatDesc *__restrict__ descs, int k0,
+                                                      const double2 *__restrict__ part, double2 *__restrict__ part2,
+                                                      double2 *__restrict__ side, int nchmax, int *__restrict__ bad) {
+  const MatDesc d = descs[blockIdx.y];
+  const int r0 = k0 + blockIdx.x * CH, tid = threadIdx.x, r = r0 + tid;
+  if (k0 >= d.n || r0 >= d.m) return;
+  const int nbp = min(CQ, d.n - k0), nch = (d.m - k0 + CH - 1) / CH;
+  const bool live = r < d.m;
+  __shared__ double2 Ls[CQ][CQ + 1], Rs[CQ][CQ + 1];
+  __shared__ double rinv[CQ], g0[CQ];
+  __shared__ double2 red[CH / 64][CQ * CQ];
+  __shared__ double2 Qs[CH][CQ + 1];
+  double2 x[CQ];
+#pragma unroll
+  for (int c = 0; c < CQ; ++c)
+    x[c] = ld_or0(d.a, (size_t)(k0 + min(c, nbp - 1)) * d.lda + min(r, d.m - 1), live && c < nbp);
+  const double2 g = cq_sum(part + (size_t)blockIdx.y * nchmax * CQ * CQ, nch, nbp);
+  const bool ok = cq_chol(g, Ls, g0, Rs, rinv, kCholPivotMin);
+  if (!ok && tid == 0) bad[blockIdx.y] = 1;
+  cq_subst(x, Rs, rinv);
+  double2 *sd = side + (size_t)blockIdx.y * 2 * CQ * CQ;
+#pragma unroll
+  for (int c = 0; c < CQ; ++c) {
+    Qs[tid][c] = x[c];
+    if (live && c < nbp) d.a[(size_t)(k0 + c) * d.lda + r] = x[c];
+    if (blockIdx.x == 0 && tid < CQ) sd[tid * CQ + c] = x[c];
+  }
+  if (blockIdx.x == 0) {
+    const int i = tid / CQ, j = tid % CQ;
+    sd[CQ * CQ + tid] = i <= j ? Rs[i][j] : cz(0.0, 0.0);
+  }
+  __syncthreads();
+  cq_gram([&](int row, int c) { return Qs[row][c]; }, red,
+          part2 + ((size_t)blockIdx.y * nchmax + blockIdx.x) * CQ * CQ);
+}
+
+// T16: the panel's T, into its block of the matrix's T (panels of nbo columns)
+// and, if tx is set, tx[mat] as well.
+__global__ __launch_bounds__(CH) void cq_reflect_kernel(const MatDesc *__restrict__ descs, int k0,
+                                                        const double2 *__restrict__ part2,
+                                                        const double2 *__restrict__ side, int nchmax,
+                                                        int *__restrict__ bad, int nbo, double2 *__restrict__ tx) {
+  const MatDesc d = descs[blockIdx.y];
+  const int r0 = k0 + blockIdx.x * CH, tid = threadIdx.x, r = r0 + tid;
+  if (k0 >= d.n || r0 >= d.m) return;
+  const int nbp = min(CQ, d.n - k0), nch = (d.m - k0 + CH - 1) / CH;
+  const bool below = r < d.m && r >= k0 + CQ;
+  __shared__ double2 Ls[CQ][CQ + 1], Rs[CQ][CQ + 1], LU[CQ][CQ + 1], Ws[CQ][CQ + 1];
+  __shared__ double rinv[CQ], g0[CQ];
+  __shared__ double2 winv[CQ], sgn[CQ];
+  const int i = tid / CQ, j = tid % CQ;
+  double2 x[CQ];
+#pragma unroll
+  for (int c = 0; c < CQ; ++c)
+    x[c] = ld_or0(d.a, (size_t)(k0 + min(c, nbp - 1)) * d.lda + min(r, d.m - 1), below && c < nbp);
+  const double2 *sd = side + (size_t)blockIdx.y * 2 * CQ * CQ;
+  double2 t = csel(j < nbp, sd[tid], cz(0.0, 0.0));   // past the last column: u = 1
+  const double2 g = cq_sum(part2 + (size_t)blockIdx.y * nchmax * CQ * CQ, nch, nbp);
+  // near the identity unless the first pass failed
+  const bool ok = cq_chol(g, Ls, g0, Rs, rinv, 0.1);
+  if (!ok && tid == 0) bad[blockIdx.y] = 1;
+  t = cq_solve16(t, Ws, [&](int p, int q) { return Rs[p][q]; }, rinv);
+  // LU of the top block less S
+#pragma unroll 1
+  for (int p = 0; p < CQ; ++p) {
+    if ((i == p && j >= p) || (j == p && i > p)) LU[i][j] = t;
+    __syncthreads();
+    const double2 pv = LU[p][p];
+    const double ab = sqrt(cabs2(pv));
+    const double2 sp = ab > 0.0 ? cz(-pv.x / ab, -pv.y / ab) : cz(-1.0, 0.0);
+    const double2 u = csub(pv, sp);
+    const double ui = 1.0 / cabs2(u);
+    const double2 l = cmul(LU[i][p], cz(u.x * ui, -u.y * ui));   // row i of column p of L
+    const double2 up = LU[p][j];
+    if (i > p && j > p) t = csub(t, cmul(l, up));
+    __syncthreads();   // the pivot column and diagonal are rewritten as L and U
+    if (j == p && i > p) LU[i][p] = l;
+    if (i == p && j == p) {
+      LU[p][p] = u;
+      sgn[p] = sp;
+    }
+  }
+  __syncthreads();
+  {
+    // W = U R2: the rows below are P R2^{-1} U^{-1} = P W'^{-1} with W' = U R2
+    t = cz(0.0, 0.0);
+    for (int k = i; k <= j; ++k) cfma(t, LU[i][k], Rs[k][j]);
+    Ws[i][j] = t;
+    if (i == j) {
+      const double w = 1.0 / cabs2(t);
+      winv[i] = cz(t.x * w, -t.y * w);
+    }
+    if (blockIdx.x == 0) {
+      if (j < nbp && i <= j) {   // S R2 R1
+        double2 v = cz(0.0, 0.0);
+        for (int k = i; k <= j; ++k) cfma(v, Rs[i][k], sd[CQ * CQ + k * CQ + j]);
+        d.a[(size_t)(k0 + j) * d.lda + k0 + i] = cmul(sgn[i], v);
+      } else if (j < nbp && k0 + i < d.m) {
+        d.a[(size_t)(k0 + j) * d.lda + k0 + i] = LU[i][j];
+      }
+    }
+  }
+  __syncthreads();
+  if (below) {
+    cq_subst(x, Ws, winv);
+#pragma unroll
+    for (int c = 0; c < CQ; ++c)
+      if (c < nbp) d.a[(size_t)(k0 + c) * d.lda + r] = x[c];
+  }
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    // T = -U S^{-1} L^{-H}
+    double2 v = i <= j ? cmul(LU[i][j], cconj(sgn[j])) : cz(0.0, 0.0);
+    v = cz(-v.x, -v.y);
+    if (i == j && i < nbp) d.tau[k0 + i] = v;
+    if (i == j) winv[i] = cz(1.0, 0.0);
+    __syncthreads();   // winv is free: the rows above are done in this workgroup
+    v = cq_solve16(v, Ls, [&](int p, int q) { return cconj(LU[q][p]); }, winv);
+    v = csel(i <= j && j < nbp, v, cz(0.0, 0.0));
+    const int o = k0 % nbo;
+    d.T[(size_t)(k0 / nbo) * nbo * nbo + (size_t)(o + j) * nbo + o + i] = v;
+    if (tx) tx[(size_t)blockIdx.y * CQ * CQ + j * CQ + i] = v;
+  }
+}
+
 // Y columns: which = 0 -> trailing columns of the matrix after the panel,
 // which = 1 -> columns [0, rank) of d.u, which = 2 -> columns [k0, rank) of
 // d.u (forming Q from the identity: the reflectors of the panel at k0 and
@@ -376,10 +649,9 @@ template <int NB>
 __global__ __launch_bounds__(256, VhyShape<NB>::OCC) void bqr_vhy_kernel(const MatDesc *__restrict__ descs, int k0,
                                                                         int which, int withV, int cend,
                                                                         double2 *__restrict__ P, int ldp,
-                                                                        int nkcmax) {
+                                                                        int nkcmax, int KR) {
   using S = VhyShape<NB>;
-  constexpr int YT = S::YT, IB = S::IB, CB = S::CB, DB = S::DB, KR = S::KR;
-  static_assert(KR >= KRMIN && KR % KS == 0, "a slice is whole LDS stages");
+  constexpr int YT = S::YT, IB = S::IB, CB = S::CB, DB = S::DB;
   constexpr int NWI = NB / 16 / IB;   // waves along the rows of P
   static_assert(NWI * (YT / 16 / CB) == 4, "four waves cover the tile");
   const MatDesc d = descs[blockIdx.z];
@@ -501,15 +773,18 @@ __global__ __launch_bounds__(256, VhyShape<NB>::OCC) void bqr_vhy_kernel(const M
 // V^H V from the slices of P.  Written to the matrix's T of panel k0 / NB,
 // or to Tx[mat] if Tx is set (an inner panel's T, needed only until its
 // update is done).
+// threads of the T kernel: the sum over the slices is spread over all of them
+// (64-column panels over 25 slices: 94 us with 256)
+template <int NB> struct TThreads { static constexpr int N = NB * NB / 4 < 256 ? 256 : NB * NB / 4; };
 template <int NB>
-__global__ __launch_bounds__(256) void bqr_t_kernel(const MatDesc *__restrict__ descs, int k0,
+__global__ __launch_bounds__(TThreads<NB>::N) void bqr_t_kernel(const MatDesc *__restrict__ descs, int k0,
                                                     const double2 *__restrict__ P, int ldp, int nkcmax,
-                                                    double2 *__restrict__ Tx) {
+                                                    double2 *__restrict__ Tx, int KR, int diag) {
+  constexpr int TT = TThreads<NB>::N;
   static_assert(NB % 16 == 0 && NB <= 64, "diagonal blocks of 16, one wave each");
   const MatDesc d = descs[blockIdx.x];
   if (k0 >= d.n) return;
   const int nbp = min(NB, d.n - k0);
-  constexpr int KR = VhyShape<NB>::KR;
   const int nkc = (d.m - k0 + KR - 1) / KR;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   __shared__ double2 gram[NB][NB + 1];
@@ -518,30 +793,38 @@ __global__ __launch_bounds__(256) void bqr_t_kernel(const MatDesc *__restrict__ 
   const double2 *base = P + (size_t)blockIdx.x * nkcmax * NB * ldp;
   {
     // strict upper part, summed over the slices (consecutive threads along a row of P)
-    double2 t[NB * NB / 256];
+    double2 t[NB * NB / TT];
 #pragma unroll
-    for (int u = 0; u < NB * NB / 256; ++u) t[u] = cz(0.0, 0.0);
+    for (int u = 0; u < NB * NB / TT; ++u) t[u] = cz(0.0, 0.0);
 #pragma unroll 4
     for (int kc = 0; kc < nkc; ++kc) {
 #pragma unroll
-      for (int u = 0; u < NB * NB / 256; ++u) {
-        const int idx = tid + 256 * u, i = idx % NB, g = idx / NB;
-        t[u] = cadd(t[u], ld_or0(base, ((size_t)kc * NB + g) * ldp + i, g < i && i < nbp));
+      for (int u = 0; u < NB * NB / TT; ++u) {
+        const int idx = tid + TT * u, i = idx % NB, g = idx / NB;
+        t[u] = cadd(t[u], ld_or0(base, ((size_t)kc * NB + g) * ldp + i, diag ? g / 16 < i / 16 && i < nbp : g < i && i < nbp));
       }
     }
 #pragma unroll
-    for (int u = 0; u < NB * NB / 256; ++u) {
-      const int idx = tid + 256 * u;
+    for (int u = 0; u < NB * NB / TT; ++u) {
+      const int idx = tid + TT * u;
       gram[idx / NB][idx % NB] = t[u];
     }
-    for (int idx = tid; idx < NB * (NB + 1); idx += 256) Tsh[idx / (NB + 1)][idx % (NB + 1)] = cz(0.0, 0.0);
+    for (int idx = tid; idx < NB * (NB + 1); idx += TT) Tsh[idx / (NB + 1)][idx % (NB + 1)] = cz(0.0, 0.0);
   }
   __syncthreads();
   // diagonal blocks, all at once: wave w < NB / 16 takes block w (lane l: row 16 w + l)
   __shared__ double2 tmp[NB];
   const bool blk = wv < NB / 16 && lane < 16;
   const int o = 16 * wv;
-  for (int i = 0; i < 16; ++i) {
+  if (diag) {   // given (cq_reflect_kernel)
+    const double2 *T = d.T + (size_t)(k0 / NB) * NB * NB;
+    for (int idx = tid; idx < NB * NB; idx += TT) {
+      const int r = idx % NB, c = idx / NB;
+      if (r / 16 == c / 16 && r <= c && c < nbp) Tsh[r][c] = T[idx];
+    }
+    __syncthreads();
+  }
+  for (int i = 0; i < 16 && !diag; ++i) {
     const int ci = o + i;
     const double2 ti = blk && ci < nbp ? d.tau[k0 + ci] : cz(0.0, 0.0);
     if (blk && lane < i) tmp[o + lane] = cmul(cz(-ti.x, -ti.y), gram[o + lane][ci]);
@@ -557,14 +840,14 @@ __global__ __launch_bounds__(256) void bqr_t_kernel(const MatDesc *__restrict__ 
   for (int h = 16; h < NB; h *= 2) {
     // pairs (o, o + h), o = 2 h p: X = G12 T2, then T12 = -T1 X
     const int npair = NB / (2 * h), nout = npair * h * h;
-    for (int idx = tid; idx < nout; idx += 256) {
+    for (int idx = tid; idx < nout; idx += TT) {
       const int p = idx / (h * h), r = (idx / h) % h, c = idx % h, o = 2 * h * p;
       double2 acc = cz(0.0, 0.0);
       for (int g = 0; g <= c; ++g) cfma(acc, gram[o + r][o + h + g], Tsh[o + h + g][o + h + c]);
       X[p * h + r][c] = acc;
     }
     __syncthreads();
-    for (int idx = tid; idx < nout; idx += 256) {
+    for (int idx = tid; idx < nout; idx += TT) {
       const int p = idx / (h * h), r = (idx / h) % h, c = idx % h, o = 2 * h * p;
       double2 acc = cz(0.0, 0.0);
       for (int g = r; g < h; ++g) cfma(acc, Tsh[o + r][o + g], X[p * h + g][c]);
@@ -573,7 +856,7 @@ __global__ __launch_bounds__(256) void bqr_t_kernel(const MatDesc *__restrict__ 
     __syncthreads();
   }
   double2 *T = Tx ? Tx + (size_t)blockIdx.x * NB * NB : d.T + (size_t)(k0 / NB) * NB * NB;
-  for (int idx = tid; idx < NB * NB; idx += 256) {
+  for (int idx = tid; idx < NB * NB; idx += TT) {
     const int r = idx % NB, c = idx / NB;
     T[idx] = (r <= c && c < nbp) ? Tsh[r][c] : cz(0.0, 0.0);
   }
@@ -594,7 +877,7 @@ __global__ __launch_bounds__(256, 3) void bqr_w2_kernel(const MatDesc *__restric
                                                      int withV, int trans, int cend,
                                                      const double2 *__restrict__ P, int ldp, int nkcmax,
                                                      double2 *__restrict__ W2, int ldw,
-                                                     const double2 *__restrict__ Tx) {
+                                                     const double2 *__restrict__ Tx, int KR) {
   static_assert(W2T == 16 && NB % 16 == 0, "a thread: one column of the tile, rows 16 apart");
   constexpr int R = NB / 16;
   const MatDesc d = descs[blockIdx.y];
@@ -606,7 +889,6 @@ __global__ __launch_bounds__(256, 3) void bqr_w2_kernel(const MatDesc *__restric
   if (which == 0) nb_cols = min(nb_cols, cend - (k0 + nbp));
   if ((int)blockIdx.x * W2T >= nb_cols) return;
   const int nv = withV ? NB : 0;
-  constexpr int KR = VhyShape<NB>::KR;
   const int nkc = (d.m - k0 + KR - 1) / KR;
   __shared__ double2 Tp[NB * (NB + 1) / 2];
   __shared__ double2 Ws[NB][W2T + 1];
@@ -763,13 +1045,25 @@ __global__ __launch_bounds__(256, 3) void bqr_update_kernel(const MatDesc *__res
     }
 }
 
+// Rows of a V^H Y slice: VhyShape's, halved down to 64 while the workgroups of
+// an average panel of the factorisation would leave compute units idle (4
+// matrices of 1600 x 400: the 64-wide launch 89 -> 23 us, a solve of two waves
+// 8.5 -> 7.7 ms; aims of 512 and 1024 workgroups 7.9 ms; 16 of 2304 x 650 the same
+// from 1 to 1024).
+int vhy_slice_rows(int nb, int nmat, int mmax, int ncols) {
+  int kr = nb == 64 ? VhyShape<64>::KR : (nb == 32 ? VhyShape<32>::KR : VhyShape<16>::KR);
+  while (kr > KRMIN && (long)cdiv(nb + ncols / 2, 64) * cdiv(std::max(mmax, 1), kr) * nmat < VHYWG) kr /= 2;
+  return kr;
+}
+
 struct ApplyWork {
   DevBuf P, W2;
-  int ldp = 0, ldw = 0, nkcmax = 0;
+  int ldp = 0, ldw = 0, nkcmax = 0, kr = 0;
   void size(int nmat, int mmax, int ncols, int nb) {
     ldp = nb + ncols;
     ldw = std::max(ncols, 1);
-    nkcmax = cdiv(std::max(mmax, 1), KRMIN);
+    kr = vhy_slice_rows(nb, nmat, mmax, ncols);
+    nkcmax = cdiv(std::max(mmax, 1), kr);
     P.alloc((size_t)nmat * nkcmax * nb * ldp * sizeof(double2));
     W2.alloc((size_t)nmat * nb * ldw * sizeof(double2));
   }
@@ -782,19 +1076,19 @@ constexpr int kNoEnd = 0x7fffffff;
 template <int NB>
 void apply_panel(const MatDesc *descs, int nmat, int mmax, int ncols_max, int k0, int which, int withV,
                  int trans, ApplyWork &w, bool build_t, hipStream_t s, int cend = kNoEnd,
-                 double2 *Tx = nullptr) {
+                 double2 *Tx = nullptr, int diag = 0) {
   const int ny = (withV ? NB : 0) + ncols_max;
-  const int nkc = cdiv(std::max(mmax - k0, 1), VhyShape<NB>::KR);
+  const int nkc = cdiv(std::max(mmax - k0, 1), w.kr);
   if (ny > 0)
     hipLaunchKernelGGL(bqr_vhy_kernel<NB>, dim3(cdiv(ny, VhyShape<NB>::YT), nkc, nmat), dim3(256), 0, s, descs, k0, which, withV,
-                       cend, w.P.as<double2>(), w.ldp, w.nkcmax);
+                       cend, w.P.as<double2>(), w.ldp, w.nkcmax, w.kr);
   if (build_t)
-    hipLaunchKernelGGL(bqr_t_kernel<NB>, dim3(nmat), dim3(256), 0, s, descs, k0, w.P.as<double2>(), w.ldp,
-                       w.nkcmax, Tx);
+    hipLaunchKernelGGL(bqr_t_kernel<NB>, dim3(nmat), dim3(TThreads<NB>::N), 0, s, descs, k0, w.P.as<double2>(), w.ldp,
+                       w.nkcmax, Tx, w.kr, diag);
   if (ncols_max > 0) {
     const int w2x = std::min(cdiv(ncols_max, W2T), std::max(1, cdiv(W2WG, nmat)));
     hipLaunchKernelGGL(bqr_w2_kernel<NB>, dim3(w2x, nmat), dim3(256), 0, s, descs, k0, which,
-                       withV, trans, cend, w.P.as<double2>(), w.ldp, w.nkcmax, w.W2.as<double2>(), w.ldw, Tx);
+                       withV, trans, cend, w.P.as<double2>(), w.ldp, w.nkcmax, w.W2.as<double2>(), w.ldw, Tx, w.kr);
     hipLaunchKernelGGL(bqr_update_kernel<NB>,
                        dim3(cdiv(ncols_max, UpdShape::UC), cdiv(std::max(mmax - k0, 1), UpdShape::UR), nmat),
                        dim3(256), 0, s, descs, k0, which, cend, w.W2.as<double2>(), w.ldw);
@@ -808,14 +1102,25 @@ struct PanelWork {
   static constexpr int NI = 16;
   DevBuf part, side;
   int nchmax = 0;
-  void size(int nmat, int mmax) {
+  int *bad = nullptr;   // given: Cholesky panels, [nmat] flags of matrices they could not factor
+  void size(int nmat, int mmax, int *flags) {
     nchmax = cdiv(mmax, CH);
-    part.alloc((size_t)nmat * 2 * nchmax * (NI + 1) * sizeof(double2));
-    side.alloc((size_t)nmat * 2 * NI * sizeof(double2));
+    bad = flags;
+    const int np = bad ? CQ * CQ : NI + 1, ns = bad ? CQ * CQ : NI;
+    part.alloc((size_t)nmat * 2 * nchmax * np * sizeof(double2));
+    side.alloc((size_t)nmat * 2 * ns * sizeof(double2));
   }
-  void factor(const MatDesc *descs, int nmat, int mmax, int nmax, int k0, hipStream_t s) {
+  void factor(const MatDesc *descs, int nmat, int mmax, int nmax, int k0, hipStream_t s, int nbo, double2 *tx) {
     const int nbp = std::min(NI, nmax - k0);
-    if (mmax - k0 <= PTMAX) {
+    if (bad) {
+      const dim3 g(cdiv(std::max(mmax - k0, 1), CH), nmat);
+      double2 *p2 = part.as<double2>() + (size_t)nmat * nchmax * CQ * CQ;
+      hipLaunchKernelGGL(cq_gram_kernel, g, dim3(CH), 0, s, descs, k0, part.as<double2>(), nchmax);
+      hipLaunchKernelGGL(cq_solve_kernel, g, dim3(CH), 0, s, descs, k0, part.as<double2>(), p2, side.as<double2>(),
+                         nchmax, bad);
+      hipLaunchKernelGGL(cq_reflect_kernel, g, dim3(CH), 0, s, descs, k0, p2, side.as<double2>(), nchmax, bad,
+                         nbo, tx);
+    } else if (mmax - k0 <= PTMAX) {
       // every matrix's remaining rows fit one workgroup: the panel in one launch
       const int threads = round_up(std::max(mmax - k0, 1), 64);
       hipLaunchKernelGGL(bqr_panel_kernel<NI>, dim3(nmat), dim3(threads), 0, s, descs, k0);
@@ -844,13 +1149,13 @@ struct BlockedQR {
   PanelWork pw;
   ApplyWork w, wi;
   DevBuf tx;
-  BlockedQR(const MatDesc *d, const std::vector<MatDesc> &h) : descs(d), nmat((int)h.size()) {
+  BlockedQR(const MatDesc *d, const std::vector<MatDesc> &h, int *bad = nullptr) : descs(d), nmat((int)h.size()) {
     for (const auto &m : h) {
       nmax = std::max(nmax, m.n);
       mmax = std::max(mmax, m.m);
     }
     if (nmax == 0 || nmat == 0) return;
-    pw.size(nmat, mmax);
+    pw.size(nmat, mmax, bad);
     w.size(nmat, mmax, nmax, NB);
     if (NB > NI) {
       wi.size(nmat, mmax, NB - NI, NI);
@@ -859,19 +1164,23 @@ struct BlockedQR {
   }
   // the panel of columns [K0, K0 + NB) and its update of the columns after it
   void panel(int K0, hipStream_t s) {
+    // Cholesky panels bring their T: the inner applies need no V^H V
+    const bool given = pw.bad != nullptr;
     for (int k0 = K0; k0 < std::min(K0 + NB, nmax); k0 += NI) {
-      pw.factor(descs, nmat, mmax, nmax, k0, s);
+      pw.factor(descs, nmat, mmax, nmax, k0, s, NB, NB > NI ? tx.as<double2>() : nullptr);
       const int rest = std::min(K0 + NB, nmax) - (k0 + NI);   // inner columns still to update
       if (NB > NI && rest > 0)
-        apply_panel<NI>(descs, nmat, mmax, rest, k0, 0, 1, 1, wi, true, s, K0 + NB, tx.as<double2>());
+        apply_panel<NI>(descs, nmat, mmax, rest, k0, 0, !given, 1, wi, !given, s, K0 + NB, tx.as<double2>());
     }
-    apply_panel<NB>(descs, nmat, mmax, std::max(0, nmax - K0 - NB), K0, 0, 1, 1, w, true, s);
+    const bool whole = NB == NI && given;   // T complete
+    apply_panel<NB>(descs, nmat, mmax, std::max(0, nmax - K0 - NB), K0, 0, !whole, 1, w, !whole, s, kNoEnd, nullptr,
+                    given);
   }
 };
 
 template <int NB>
-void qr_factor_t(const MatDesc *descs, const std::vector<MatDesc> &h, hipStream_t s) {
-  BlockedQR<NB> q(descs, h);
+void qr_factor_t(const MatDesc *descs, const std::vector<MatDesc> &h, hipStream_t s, int *bad) {
+  BlockedQR<NB> q(descs, h, bad);
   for (int K0 = 0; K0 < q.nmax; K0 += NB) q.panel(K0, s);
 }
 
@@ -965,7 +1274,7 @@ void tune_store(const std::string &key, int nb) {   // g_tune_mu held
 void qr_form_u(const MatDesc *descs, const std::vector<MatDesc> &h, int maxrank, hipStream_t s,
                bool from_identity, int nb);
 
-int qr_tuned_nb(const std::vector<MatDesc> &h, hipStream_t s) {
+int qr_tuned_nb(const std::vector<MatDesc> &h, hipStream_t s, bool chol) {
   if (const char *e = std::getenv("MFS_QR_NB")) {
     const int nb = std::atoi(e);
     MFS_REQUIRE(nb == 16 || nb == 32 || nb == 64, "MFS_QR_NB must be 16, 32 or 64");
@@ -977,7 +1286,7 @@ int qr_tuned_nb(const std::vector<MatDesc> &h, hipStream_t s) {
     mmax = std::max(mmax, d.m);
   }
   if (h.empty() || nmax == 0) return kQRNB;
-  const std::string key = tune_key(mmax, nmax);
+  const std::string key = tune_key(mmax, nmax) + (chol ? "/c" : "");
   std::lock_guard<std::mutex> lk(g_tune_mu);
   tune_load();
   auto it = g_tune.find(key);
@@ -1030,7 +1339,7 @@ int qr_tuned_nb(const std::vector<MatDesc> &h, hipStream_t s) {
     c.ldu = c.lda;
     hc.push_back(c);
   }
-  DevBuf ranks(hc.size() * sizeof(int));
+  DevBuf ranks(hc.size() * sizeof(int)), bad(hc.size() * sizeof(int));
   {
     std::vector<int> rk(hc.size());
     for (size_t k = 0; k < hc.size(); ++k) {
@@ -1059,7 +1368,7 @@ int qr_tuned_nb(const std::vector<MatDesc> &h, hipStream_t s) {
                                    hc[k].n, hipMemcpyDeviceToDevice, s));
       hipLaunchKernelGGL(tune_identity_kernel, dim3(snmax, (int)hc.size()), dim3(256), 0, s, dd.as<MatDesc>());
       HIP_CHECK(hipEventRecord(e0, s));
-      qr_factor(dd.as<MatDesc>(), hc, s, nb);
+      qr_factor(dd.as<MatDesc>(), hc, s, nb, chol ? bad.as<int>() : nullptr);
       qr_form_u(dd.as<MatDesc>(), hc, snmax, s, true, nb);
       HIP_CHECK(hipEventRecord(e1, s));
       HIP_CHECK(hipEventSynchronize(e1));
@@ -1085,11 +1394,11 @@ QRPanels32::QRPanels32(const MatDesc *descs, const std::vector<MatDesc> &h) : im
 QRPanels32::~QRPanels32() { delete impl; }
 void QRPanels32::panel(int K0, hipStream_t s) { impl->q.panel(K0, s); }
 
-void qr_factor(const MatDesc *descs, const std::vector<MatDesc> &h, hipStream_t s, int nb) {
+void qr_factor(const MatDesc *descs, const std::vector<MatDesc> &h, hipStream_t s, int nb, int *bad) {
   switch (nb) {
-    case 16: qr_factor_t<16>(descs, h, s); break;
-    case 32: qr_factor_t<32>(descs, h, s); break;
-    case 64: qr_factor_t<64>(descs, h, s); break;
+    case 16: qr_factor_t<16>(descs, h, s, bad); break;
+    case 32: qr_factor_t<32>(descs, h, s, bad); break;
+    case 64: qr_factor_t<64>(descs, h, s, bad); break;
     default: MFS_THROW(MFS_EINVAL, "QR panel width must be 16, 32 or 64");
   }
 }
