@@ -516,7 +516,7 @@ mfs_status mfs_factor_modes(mfs_op *op, double rel_cutoff, int32_t *ranks) {
     auto g = std::make_unique<GradedPinv>();
     g->ev_qr_done = op->ev[1];
     HIP_CHECK(hipEventRecord(op->ev[0], s));
-    graded_pinv(*g, in, rel_cutoff, 0, s);
+    graded_pinv(*g, in, rel_cutoff, s);
     HIP_CHECK(hipEventRecord(op->ev[2], s));
     HIP_CHECK(hipStreamSynchronize(s));
     float ms_qr = 0, ms_svd = 0;

@@ -8,30 +8,20 @@
 //     rounding level eps*sqrt(n)*s_max), and the rest are ordered by
 //     decreasing norm;
 //  2. blocked Householder QR without pivoting of the ordered columns,
-//     Q P = Q_1 R_1, which takes the tall matrix (7200 rows for the k = 10
-//     periodizer) down to its n2 x n2 triangle with matrix-product work;
-//     optionally (`pivot`) a column-pivoted Householder QR of that
-//     triangle, R_1 P_2 = Q_2 R (the largest remaining column moves to the
-//     front at every step: one pivot/reflector launch and one trailing
-//     update launch per column, compact-WY T factors per 32-column panel);
-//     trailing rows of the triangle (R_1, or R) whose joint Frobenius norm
-//     is below 1e-15 of the largest column norm are dropped: ~ R_top (r x n2);
+//     Q P = Q_1 R_1, which takes the tall matrix (2304 rows for a half of the
+//     k = 10 periodizer) down to its n2 x n2 triangle with matrix-product
+//     work; a column-pivoted Householder QR of that triangle, R_1 P_2 = Q_2 R;
+//     trailing rows of R whose joint Frobenius norm is below 1e-15 of the
+//     largest column norm are dropped: ~ R_top (r x n2);
 //  3. LQ of R_top via QR of R_top^H = Z L^H;
 //  4. one-sided Jacobi SVD of the r x r factor L = U_L S V_L^H, truncated at
 //     rel_cutoff * s_max as in the paper;
-//  5. Q^+ = P (Z V_L S^{-1}) (Q_1 [U_L; 0])^H, with Q_2 and P_2 in between
-//     when pivoting: U and W = P Z V_L S^{-1} are formed explicitly for the
-//     two-stage apply.
-// Ordering and LQ are the preconditioning that makes one-sided Jacobi
-// converge in a handful of sweeps.  On the strongly graded k = 10 periodizer
-// (n2 = 1257) the norm ordering alone does it (10 sweeps, as with the
-// pivoted triangle, against no convergence in 40 without the ordering), so
-// the pivoted QR's 2 n2 launches are saved; on the k = 2 pi 13 periodizer
-// (n2 = 9701) the pivoted triangle takes Jacobi from ~25 sweeps to ~14 for
-// about 3.6 s of matrix-vector work.  The per-mode MFS blocks are
-// rank-deficient without being graded by column, and there the pivoted
-// triangle cuts the Jacobi work by about 3x.  Either way the result is the
-// same truncated pseudoinverse the paper prescribes, to rounding.
+//  5. Q^+ = P P_2 (Z V_L S^{-1}) (Q_1 Q_2 [U_L; 0])^H, V_L S^{-1} = L^{-1} U_L:
+//     U and W = P P_2 Z V_L S^{-1} are formed explicitly for the two-stage apply.
+// Ordering, pivoting and LQ are the preconditioning that makes one-sided
+// Jacobi converge in a handful of sweeps, and the pivoted triangle's graded rows
+// are what L^{-1} U_L rests on (svd.hip).  The result is the truncated
+// pseudoinverse the paper prescribes, to rounding.
 #include <algorithm>
 #include <cmath>
 
@@ -155,10 +145,11 @@ __global__ void copy_r_kernel(const MatDesc *__restrict__ src, const MatDesc *__
   }
 }
 
-// After Jacobi on L (desc l: g = U_L S, v = V_L, perm/sv/rank sorted):
+// After Jacobi on L (desc l: g = U_L S, perm/sv/rank sorted):
 //   ql.u[:, k] = [g_{perm k} / s_k ; 0]  (m rows)   -- left factor, before Q_h
-//   l.u[:, k]  = [v_{perm k} / s_k ; 0]  (n2 rows)  -- right factor, before Z
-__global__ void prep_uv_kernel(const MatDesc *__restrict__ qd, const MatDesc *__restrict__ ld) {
+// and zeros where right_factor_kernel writes nothing of
+//   l.u[:, k]  = [V_L e_k / s_k ; 0]  (n2 rows)  -- right factor, before Z
+__global__ void prep_u_kernel(const MatDesc *__restrict__ qd, const MatDesc *__restrict__ ld) {
   const MatDesc q = qd[blockIdx.y], l = ld[blockIdx.y];
   const int k = blockIdx.x;
   const int r = l.n;
@@ -174,9 +165,79 @@ __global__ void prep_uv_kernel(const MatDesc *__restrict__ qd, const MatDesc *__
   const int c = l.perm[k];
   const double inv = 1.0 / l.sv[k];
   const double2 *g = l.g + (size_t)c * l.ldg;
-  const double2 *v = l.v + (size_t)c * l.ldg;
   for (int i = threadIdx.x; i < q.m; i += blockDim.x) uq[i] = (i < r) ? cscale(g[i], inv) : cz(0.0, 0.0);
-  for (int i = threadIdx.x; i < l.m; i += blockDim.x) ul[i] = (i < r) ? cscale(v[i], inv) : cz(0.0, 0.0);
+  for (int i = r + threadIdx.x; i < l.m; i += blockDim.x) ul[i] = cz(0.0, 0.0);
+}
+
+// l.u[0:r, 0:kept] = V_L S^+ = L^{-1} U_L = X^H U_L with X = R_L^{-1} (upper, x)
+// and U_L's columns g_{perm k} / s_k: one 64 x 64 tile a workgroup on the FP64
+// matrix cores, 16 rows of X and U_L staged through LDS at a time, the sum
+// ending with the tile's last row of L^{-1}.  Bound by the matrix cores: 4 r^2
+// kept flops against 16 r^3 a Jacobi sweep for rotating V along.  770 blocks of
+// 16 bodies (r about 250): 3.8 ms, X 5 ms, and the rotation apply 194 -> 99 ms;
+// the build 485 -> 402 ms.
+__global__ __launch_bounds__(256) void right_factor_kernel(const MatDesc *__restrict__ ld,
+                                                           const MatDesc *__restrict__ xd) {
+  constexpr int KS = 16, TS = 64;
+  const MatDesc l = ld[blockIdx.z], x = xd[blockIdx.z];
+  const int r = l.n, kept = l.rank[0];
+  const int c0 = blockIdx.x * TS, i0 = blockIdx.y * TS;
+  if (c0 >= kept || i0 >= r) return;
+  __shared__ double2 Xs[KS][TS + 1], Gs[KS][TS + 1];
+  __shared__ double inv[TS];
+  __shared__ int col[TS];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int l16 = lane & 15, k4 = lane >> 4, wi = wv & 1, wc = wv >> 1;
+  if (tid < TS) {
+    const bool in = c0 + tid < kept;
+    col[tid] = in ? l.perm[c0 + tid] : 0;
+    inv[tid] = in ? 1.0 / l.sv[c0 + tid] : 0.0;
+  }
+  dx4 re[2][2], im[2][2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v) re[u][v] = im[u][v] = dx4{0, 0, 0, 0};
+  const int jend = min(r, i0 + TS);
+  __syncthreads();
+  for (int j0 = 0; j0 < jend; j0 += KS) {
+#pragma unroll
+    for (int u = 0; u < KS * TS / 256; ++u) {
+      const int idx = tid + 256 * u, jj = idx % KS, c = idx / KS, j = j0 + jj;
+      Xs[jj][c] = ld_or0(x.a, (size_t)min(i0 + c, r - 1) * x.lda + min(j, r - 1), j <= i0 + c && i0 + c < r);
+      Gs[jj][c] = cscale(ld_or0(l.g, (size_t)col[c] * l.ldg + min(j, r - 1), j < r), inv[c]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kk = 0; kk < KS; kk += 4) {
+      double2 a[2], y[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) a[u] = Xs[kk + k4][32 * wi + 16 * u + l16];
+#pragma unroll
+      for (int v = 0; v < 2; ++v) y[v] = Gs[kk + k4][32 * wc + 16 * v + l16];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {   // conj(X)^T U
+          re[u][v] = mfma_f64(a[u].x, y[v].x, re[u][v]);
+          re[u][v] = mfma_f64(a[u].y, y[v].y, re[u][v]);
+          im[u][v] = mfma_f64(a[u].x, y[v].y, im[u][v]);
+          im[u][v] = mfma_f64(-a[u].y, y[v].x, im[u][v]);
+        }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      const int c = c0 + 32 * wc + 16 * v + l16;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = i0 + 32 * wi + 16 * u + k4 + 4 * e;
+        if (c < kept && i < r) l.u[(size_t)c * l.lda + i] = cz(re[u][v][e], im[u][v][e]);
+      }
+    }
 }
 
 // W[perm[i], k] = l.u[i, k] (rows of dropped columns stay zero)
@@ -688,8 +749,7 @@ static std::vector<double> tri_sigma1(const MatDesc *tri, const std::vector<int>
 // for every equilibrated batch (the periodizer), MFS_OPINV=cod takes it for
 // the one-body operators' blocks too (no singular values are then formed).
 constexpr int kCodMinCols = 4096;
-static bool use_cod(bool equilibrate, bool pivot, int n2max) {
-  if (!pivot) return false;
+static bool use_cod(bool equilibrate, int n2max) {
   const char *e = std::getenv(equilibrate ? "MFS_QPINV" : "MFS_OPINV");
   if (e && std::string(e) == "cod") return true;
   if (e && std::string(e) == "svd") return false;
@@ -799,8 +859,8 @@ static bool direct_pinv(GradedPinv &g, const std::vector<int> &n2, int nmax, dou
   return true;
 }
 
-void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutoff, int pivot_min_cols,
-                 hipStream_t s, bool equilibrate, bool keep_reflectors, bool halves) {
+void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutoff, hipStream_t s,
+                 bool equilibrate, bool keep_reflectors, bool halves) {
   const int W = (int)in.size();
   MFS_REQUIRE(!halves || W % 2 == 0, "graded pseudoinverse: halves come in pairs");
   int nmax = 0, mmax = 0;
@@ -881,8 +941,7 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
   const int n2max = *std::max_element(n2.begin(), n2.end());
   int nwhole = n2max;   // columns of the widest whole matrix
   for (int w = 0; halves && w < W; w += 2) nwhole = std::max(nwhole, n2[w] + n2[w + 1]);
-  const bool pivot = nwhole >= pivot_min_cols;
-  g.pivoted = pivot;
+  g.pivoted = true;
   // 2. QR without pivoting of the selected, ordered columns
   g.h_qc.resize(W);
   g.small.alloc((size_t)4 * W * sizeof(int));
@@ -964,9 +1023,9 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
       if (hipStreamSynchronize(s) == hipSuccess) { g.qr_ms = a.ms(); g.post_ms = b.ms(); }
     }
   } fin{g, qre, poste, s};
-  // the triangle that the row selection and the LQ read: R_1, or with
-  // pivoting R from the column-pivoted QR R_1 P_2 = Q_2 R
-  const MatDesc *tri = g.d_qc.as<MatDesc>();
+  // the triangle that the row selection and the LQ read: R from the
+  // column-pivoted QR R_1 P_2 = Q_2 R (its rows carry the grading, which the
+  // right factor from L^{-1} rests on)
   {
     std::vector<int> ident((size_t)W * nmax);
     for (int w = 0; w < W; ++w)
@@ -976,7 +1035,7 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     HIP_CHECK(hipStreamSynchronize(s));
   }
   if (equilibrate && direct_pinv(g, n2, nmax, rel_cutoff, cscl, in, s, keep_reflectors, halves)) return;
-  if (pivot) {
+  {
     g.h_rq.resize(W);
     {
       size_t ta = 0, tf = 0;
@@ -1037,8 +1096,8 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     hipLaunchKernelGGL(build_t_kernel, dim3(W, cdiv(n2max, kQRNB)), dim3(256), 0, s, g.d_rq.as<MatDesc>());
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(s));   // qn is released here
-    tri = g.d_rq.as<MatDesc>();
   }
+  const MatDesc *tri = g.d_rq.as<MatDesc>();
   // rows of the triangle to keep
   DevBuf rn((size_t)W * n2max * sizeof(double));
   hipLaunchKernelGGL(rownorm_kernel, dim3(cdiv(n2max, 256), W), dim3(256), 0, s, tri, rn.as<double>(), n2max);
@@ -1060,7 +1119,7 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
   // complete orthogonal decomposition: keep the rows of the pivoted triangle
   // until the trailing block's Frobenius norm is at most rel_cutoff times the
   // largest singular value (the rank-revealing counterpart of the SVD cut)
-  const bool cod = use_cod(equilibrate, pivot, nwhole);
+  const bool cod = use_cod(equilibrate, nwhole);
   g.cod = cod;
   if (cod) {
     std::vector<double> s1 = tri_sigma1(tri, n2, n2max, s);
@@ -1089,8 +1148,8 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
       oa[w] = ta;
       ta += arena_bytes((size_t)ld2 * n);
       of[w] = tf;
-      // tau, T, g, v, u, then sv and perm (2 n doubles' worth)
-      tf += arena_bytes((size_t)n + (size_t)npan * kQRNB * kQRNB + 2 * (size_t)n * ldg + (size_t)ld2 * n + n);
+      // tau, T, g, u, then sv and perm (2 n doubles' worth)
+      tf += arena_bytes((size_t)n + (size_t)npan * kQRNB * kQRNB + (size_t)n * ldg + (size_t)ld2 * n + n);
     }
     g.lq_a.alloc(ta);
     g.lq_fac.alloc(tf);
@@ -1105,7 +1164,6 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     d.tau = p; p += n;
     d.T = p; p += (size_t)npan * kQRNB * kQRNB;
     d.g = p; p += (size_t)n * ldg;
-    d.v = p; p += (size_t)n * ldg;
     d.u = p; p += (size_t)ld2 * n;
     d.ldg = ldg;
     double *rp = reinterpret_cast<double *>(p);
@@ -1120,7 +1178,6 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
   HIP_CHECK(hipGetLastError());
   qr_factor(g.d_lq.as<MatDesc>(), g.h_lq, s);
   const int rmax = *std::max_element(rr.begin(), rr.end());
-  DevBuf xa, dx;   // COD: X = R_L^{-1}
   if (cod) {
     // every kept row stays: L^{-1} = (R_L^{-1})^H in place of V_L S^+, U_L = I
     g.kept = rr;
@@ -1128,6 +1185,18 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     g.jacobi_launches = 0;
     g.jacobi_unconverged = 0;
     HIP_CHECK(hipMemcpyAsync(flags + W, rr.data(), W * sizeof(int), hipMemcpyHostToDevice, s));
+  } else {
+    const JacStats js = jac_run(g.d_lq.as<MatDesc>(), g.h_lq, 1, rel_cutoff, s);
+    g.jacobi_ms = js.ms;
+    g.jacobi_launches = js.launches;
+    g.jacobi_bytes = js.bytes;
+    g.jacobi_flops = js.flops;
+    g.jacobi_unconverged = js.unconverged;
+    jac_sort(g.d_lq.as<MatDesc>(), g.h_lq, rel_cutoff, s, g.kept, halves);
+  }
+  // X = R_L^{-1}, for L^{-1} (decomposition) or V_L S^+ = L^{-1} U_L
+  DevBuf xa, dx;
+  {
     std::vector<size_t> ox(W);
     size_t tx = 0;
     for (int w = 0; w < W; ++w) {
@@ -1150,14 +1219,6 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     trinv_offdiag(g.d_lq.as<MatDesc>(), dx.as<MatDesc>(), W, nblk, s);
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(s));   // hx goes out of scope
-  } else {
-    const JacStats js = jac_run(g.d_lq.as<MatDesc>(), g.h_lq, 1, rel_cutoff, s);
-    g.jacobi_ms = js.ms;
-    g.jacobi_launches = js.launches;
-    g.jacobi_bytes = js.bytes;
-    g.jacobi_flops = js.flops;
-    g.jacobi_unconverged = js.unconverged;
-    jac_sort(g.d_lq.as<MatDesc>(), g.h_lq, rel_cutoff, s, g.kept, halves);
   }
   // 5. explicit factors
   int kmax = 0;
@@ -1165,14 +1226,16 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
   if (cod)
     hipLaunchKernelGGL(cod_prep_kernel, dim3(rmax, W), dim3(256), 0, s, g.d_qc.as<MatDesc>(),
                        g.d_lq.as<MatDesc>(), dx.as<MatDesc>());
-  else
-    hipLaunchKernelGGL(prep_uv_kernel, dim3(rmax, W), dim3(256), 0, s, g.d_qc.as<MatDesc>(),
-                       g.d_lq.as<MatDesc>());
+  else {
+    hipLaunchKernelGGL(prep_u_kernel, dim3(rmax, W), dim3(256), 0, s, g.d_qc.as<MatDesc>(), g.d_lq.as<MatDesc>());
+    if (kmax > 0)
+      hipLaunchKernelGGL(right_factor_kernel, dim3(cdiv(kmax, 64), cdiv(rmax, 64), W), dim3(256), 0, s,
+                         g.d_lq.as<MatDesc>(), dx.as<MatDesc>());
+  }
   HIP_CHECK(hipGetLastError());
-  // U = Q_1 [U_L; 0], or Q_1 [Q_2 [U_L; 0]; 0] with pivoting (the
-  // reflectors of the pivoted triangle act on the first n2 rows first);
-  // V = Z V_L, before the column orders are undone in W
-  if (pivot) {
+  // U = Q_1 [Q_2 [U_L; 0]; 0] (the reflectors of the pivoted triangle act on
+  // the first n2 rows first); V = Z V_L, before the column orders are undone in W
+  {
     g.h_rqu = g.h_rq;
     for (int w = 0; w < W; ++w) {
       g.h_rqu[w].u = g.h_qc[w].u;

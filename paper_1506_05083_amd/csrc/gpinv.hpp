@@ -54,10 +54,7 @@ struct GradedPinv {
   void singular_values(int ldo, std::vector<double> &out, hipStream_t s) const;
 };
 
-// in[w]: matrix w (a, m, n, lda) only.  Fills g; blocking.  The
-// column-pivoted QR of the triangle is taken before the LQ when the widest
-// kept triangle has at least pivot_min_cols columns (0: always); below that
-// the norm ordering alone preconditions Jacobi.
+// in[w]: matrix w (a, m, n, lda) only.  Fills g; blocking.
 // equilibrate: factor A D instead of A, D scaling every kept column to unit
 // norm, so that the relative cutoff judges linear dependence rather than
 // column size; W then holds D V S^+ and the pseudoinverse is D (A D)^+.
@@ -65,12 +62,7 @@ struct GradedPinv {
 // Q_1 is not formed; the QR's reflectors stay for launch_qh_apply (g.reflect).
 // halves: matrices 2 i and 2 i + 1 are the diagonal blocks of one matrix; its
 // largest singular value, condition bound and column count decide for both.
-void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutoff, int pivot_min_cols,
-                 hipStream_t s, bool equilibrate = false, bool keep_reflectors = false, bool halves = false);
-
-// Widest periodizer triangle (columns of both halves together) factored
-// without the pivoted QR (measured unsplit: 1257 columns at k = 10 gain
-// nothing from it, 9701 at k = 2 pi 13 gain 30%).
-constexpr int kQPivotMinCols = 2048;
+void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutoff, hipStream_t s,
+                 bool equilibrate = false, bool keep_reflectors = false, bool halves = false);
 
 }  // namespace mfs

@@ -57,7 +57,6 @@ struct MatDesc {
   double2 *T;     // [npanels][nb*nb] compact-WY triangular factors
   double2 *g;     // n x n, ldg: Jacobi work matrix (R, rotated to U S)
   int ldg;
-  double2 *v;     // n x n, ldg: Jacobi right vectors
   double2 *u;     // m x n, lda: left singular vectors (kept columns)
   double2 *w;     // n x n, ldg: V S^+ (kept columns)
   double *sv;     // [n] singular values, descending

@@ -160,7 +160,7 @@ struct Solver {
     // Q's columns equilibrated: the harmonics of high degree are smaller than
     // the low ones by far more than the cutoff on the walls, and would
     // otherwise be dropped whatever their use
-    graded_pinv(gp, h_qdescs, rel_cutoff, kQPivotMinCols, s, true, qreflect, true);
+    graded_pinv(gp, h_qdescs, rel_cutoff, s, true, qreflect, true);
     
     qrank = gp.kept;
     progress("periodizer: factored (%s; Jacobi %.0f ms, %d launches)",

@@ -7,8 +7,13 @@
 // orthogonal by [g_p, g_q] <- [g_p, g_q] [[c, s e^{i th}], [-s e^{-i th}, c]],
 // zeta = (b - a) / (2 |gamma|), t = sign(zeta) / (|zeta| + sqrt(1 + zeta^2)),
 // c = 1 / sqrt(1 + t^2), s = c t; the squared norms become a - t|gamma| and
-// b + t|gamma|.  The same rotations accumulate V.  At convergence
-// G = U S with orthogonal columns, s_i = |g_i|.
+// b + t|gamma|.  At convergence G = L V = U S with orthogonal columns,
+// s_i = |g_i|.  V is not accumulated: the rotations act on the rows of G one by
+// one, so every row of U S is accurate relative to that row of L, and
+// V S^+ = L^{-1} U follows from the triangular L (a pivoted QR's, so its rows
+// carry the grading and the row-scaled rest is well conditioned) with the
+// accuracy of the accumulated V (Drmac and Veselic 2008); that halves the
+// rotation apply (gpinv.hip, right_factor_kernel).
 //
 // Blocked form for the GPU: the columns are cut into blocks of JB (16, or 32
 // once a batch's widest matrix has kJacWideMinCols columns) and the
@@ -24,9 +29,9 @@
 //      diagonal formulas above and the annihilated entry set to zero), the
 //      product J of the rotations accumulated alongside;
 //   3. jac_apply_mfma_kernel / jac_apply_mfma32_kernel: if any pair of the
-//      task rotated, G_IJ <- G_IJ J and V_IJ <- V_IJ J over row tiles.
+//      task rotated, G_IJ <- G_IJ J over row tiles.
 // The row tiles spread every round over the whole chip whatever the number
-// of tasks, and the apply streams G and V once per round.
+// of tasks, and the apply streams G once per round.
 // Every pair of columns meets in some workgroup every sweep, pairs inside a
 // block in every task of that block; sweeps repeat until no pair of a matrix
 // needed a rotation (|gamma| <= tol sqrt(a b)), a matrix that converged
@@ -55,7 +60,6 @@ __global__ void jac_init_kernel(const MatDesc *__restrict__ descs, int mode) {
     if (mode == 0) v = (r <= c) ? d.a[(size_t)c * d.lda + r] : cz(0.0, 0.0);
     else v = (c <= r) ? cconj(d.a[(size_t)r * d.lda + c]) : cz(0.0, 0.0);
     d.g[(size_t)c * d.ldg + r] = v;
-    d.v[(size_t)c * d.ldg + r] = cz(r == c ? 1.0 : 0.0, 0.0);
   }
 }
 
@@ -349,10 +353,9 @@ __global__ __launch_bounds__(64) void jac_gram_mfma_kernel(const MatDesc *__rest
   }
 }
 
-// 3'. G_IJ <- G_IJ J and V_IJ <- V_IJ J: one wave per 64-row tile (tiles
-//     [0, nt) of G, [nt, 2 nt) of V), four 16-row blocks and all 32 task
-//     columns, so that each fragment of J serves four row blocks; step s sums
-//     over task columns 4 s .. 4 s + 3.  The wave reads its rows of every
+// 3'. G_IJ <- G_IJ J: one wave per 64-row tile, four 16-row blocks and all 32
+//     task columns, so that each fragment of J serves four row blocks; step s
+//     sums over task columns 4 s .. 4 s + 3.  The wave reads its rows of every
 //     column before it writes any, and tiles share no rows, so the update is
 //     in place.
 __global__ __launch_bounds__(64) void jac_apply_mfma_kernel(const MatDesc *__restrict__ descs,
@@ -366,13 +369,13 @@ __global__ __launch_bounds__(64) void jac_apply_mfma_kernel(const MatDesc *__res
   const int n = d.n;
   const int pair = blockIdx.y;
   const int nt = (n + AT - 1) / AT;
-  if ((int)blockIdx.x >= 2 * nt) return;
+  if ((int)blockIdx.x >= nt) return;
   int bi, bj, nb;
   if (!task_blocks<JB>(d, round, pair, bi, bj, nb)) return;
   if (!rot[(size_t)mat * npair_max + pair]) return;
   const int l = threadIdx.x;
-  const int r0 = ((int)blockIdx.x % nt) * AT;
-  double2 *M = (int)blockIdx.x < nt ? d.g : d.v;
+  const int r0 = (int)blockIdx.x * AT;
+  double2 *M = d.g;
   const double2 *ji = jbuf + ((size_t)mat * npair_max + pair) * JC * JC;
   const int i = l & 15, k = l >> 4;
   double2 b0[KS], b1[KS];
@@ -506,9 +509,8 @@ __global__ __launch_bounds__(128) void jac_gram_mfma32_kernel(const MatDesc *__r
   }
 }
 
-// 3''. G_IJ <- G_IJ J and V_IJ <- V_IJ J for 32-column blocks: one wave per
-//      16-row tile (tiles [0, nt) of G, [nt, 2 nt) of V) against all 64 task
-//      columns, step s summing over task columns
+// 3''. G_IJ <- G_IJ J for 32-column blocks: one wave per 16-row tile against all
+//      64 task columns, step s summing over task columns
 //      4 s .. 4 s + 3 with the fragments of J read as they are needed.  The
 //      wave reads its rows of every column before it writes any, and tiles
 //      share no rows, so the update is in place.
@@ -523,13 +525,13 @@ __global__ __launch_bounds__(64) void jac_apply_mfma32_kernel(const MatDesc *__r
   const int n = d.n;
   const int pair = blockIdx.y;
   const int nt = (n + TR - 1) / TR;
-  if ((int)blockIdx.x >= 2 * nt) return;
+  if ((int)blockIdx.x >= nt) return;
   int bi, bj, nb;
   if (!task_blocks<JB>(d, round, pair, bi, bj, nb)) return;
   if (!rot[(size_t)mat * npair_max + pair]) return;
   const int l = threadIdx.x;
-  const int r0 = ((int)blockIdx.x % nt) * TR;
-  double2 *M = (int)blockIdx.x < nt ? d.g : d.v;
+  const int r0 = (int)blockIdx.x * TR;
+  double2 *M = d.g;
   const double2 *ji = jbuf + ((size_t)mat * npair_max + pair) * JC * JC;
   const int i = l & 15, k = l >> 4;
   dx4 re[RB][NF], im[RB][NF];
@@ -711,10 +713,10 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
                          tol, hpart.as<double2>(), jbuf.as<double2>(), rotf.as<int>(), npair_max, ntile_max, cs,
                          sweep * rounds + rnd);
       if (JB == 16)
-        hipLaunchKernelGGL(jac_apply_mfma_kernel, dim3(2 * atile_max, npair_max, nmat), dim3(64), 0, s, descs,
+        hipLaunchKernelGGL(jac_apply_mfma_kernel, dim3(atile_max, npair_max, nmat), dim3(64), 0, s, descs,
                            act.as<int>(), rnd, jbuf.as<double2>(), rotf.as<int>(), npair_max);
       else
-        hipLaunchKernelGGL(jac_apply_mfma32_kernel, dim3(2 * cdiv(nmax, 16), npair_max, nmat), dim3(64), 0, s,
+        hipLaunchKernelGGL(jac_apply_mfma32_kernel, dim3(cdiv(nmax, 16), npair_max, nmat), dim3(64), 0, s,
                            descs, act.as<int>(), rnd, jbuf.as<double2>(), rotf.as<int>(), npair_max);
     }
     HIP_CHECK(hipGetLastError());
@@ -728,8 +730,7 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
     st.launches += 3 * rounds;
     // algorithmic work: every checked task (a pair not known converged) reads
     // its columns of G and forms the Hermitian Gram matrix; a task that
-    // rotated writes them back and reads and writes its columns of V, applying
-    // the c x c rotation product to both
+    // rotated writes them back, times the c x c rotation product
     bool any = false;
     int nact = 0;
     long nrot = 0, nchecked = 0;
@@ -737,8 +738,8 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
       if (!active[i]) continue;
       nchecked += checked[i];
       const double n = h[i].n, c = width[i], col = n * sizeof(double2);
-      st.bytes += (double)checked[i] * c * col + (double)flags[i] * 3.0 * c * col;
-      st.flops += (double)checked[i] * 4.0 * c * (c + 1.0) * n + (double)flags[i] * 16.0 * c * c * n;
+      st.bytes += (double)checked[i] * c * col + (double)flags[i] * c * col;
+      st.flops += (double)checked[i] * 4.0 * c * (c + 1.0) * n + (double)flags[i] * 8.0 * c * c * n;
       if (flags[i] != 0) { any = true; ++nact; nrot += flags[i]; }
       else active[i] = 0;
     }
