@@ -378,6 +378,140 @@ __global__ __launch_bounds__(256) void qrcp_update_kernel(const MatDesc *__restr
   if (lane == 0) norms[(size_t)blockIdx.y * ld + c] = sqrt(s);
 }
 
+// The whole column-pivoted QR of a triangle of at most QN columns in one
+// launch, one workgroup a matrix: norms, the pivot column and the pivot record
+// in LDS, the triangle in place (from L2), a wave a column with the column's
+// rows in registers between its product with the reflector and its update, two
+// columns a wave in flight.  The steps of the two kernels above without their
+// 2 n launches: bound by the step's chain (argmax, swap, reflector, the
+// columns' round trip to L2).  17 triangles of 60 columns: 0.23 ms, the
+// scattering pass around it 3.17 -> 2.87 ms.
+constexpr int QN = 256, QT = 1024;
+__global__ __launch_bounds__(QT) void qrcp_one_kernel(const MatDesc *__restrict__ descs, int *__restrict__ piv,
+                                                      int ld) {
+  constexpr int NW = QT / 64, RL = QN / 64;
+  const MatDesc d = descs[blockIdx.x];
+  const int n = d.n, m = d.m, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  int *pv = piv + (size_t)blockIdx.x * ld;
+  __shared__ double nr[QN];
+  __shared__ double2 v[QN];
+  __shared__ double rv[NW];
+  __shared__ int ri[NW];
+  __shared__ double red[NW];
+  for (int c = wv; c < n; c += NW) {
+    double s = 0.0;
+    for (int r = lane; r < m; r += 64) s += cabs2(d.a[(size_t)c * d.lda + r]);
+    s = wave_sum(s);
+    if (lane == 0) nr[c] = s;
+  }
+  __syncthreads();
+  for (int k = 0; k < n; ++k) {
+    double best = -1.0;
+    int bi = k;
+    for (int c = k + tid; c < n; c += QT) {
+      const double x = nr[c];
+      if (x > best) { best = x; bi = c; }
+    }
+    if (wv * 64 + k < n) {   // waves without a column have nothing to compare
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const double ov = __shfl_xor(best, o, 64);
+        const int oi = __shfl_xor(bi, o, 64);
+        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+      }
+    }
+    if (lane == 0) { rv[wv] = best; ri[wv] = bi; }
+    __syncthreads();
+    best = rv[0];
+    int p = ri[0];
+    for (int w = 1; w < NW; ++w)
+      if (rv[w] > best || (rv[w] == best && ri[w] < p)) { best = rv[w]; p = ri[w]; }
+    double2 *ck = d.a + (size_t)k * d.lda, *cp = d.a + (size_t)p * d.lda;
+    if (tid < m) {
+      const double2 t = cp[tid];
+      if (p != k) cp[tid] = ck[tid];
+      v[tid] = t;
+    }
+    const double q = wave_sum(tid > k && tid < m ? cabs2(v[tid]) : 0.0);   // a thread reads its own entry
+    if (lane == 0) red[wv] = q;
+    __syncthreads();
+    if (tid == 0 && p != k) {
+      nr[p] = nr[k];
+      const int ti = pv[k];
+      pv[k] = pv[p];
+      pv[p] = ti;
+    }
+    double ssum = 0.0;
+#pragma unroll
+    for (int w = 0; w < QN / 64; ++w) ssum += red[w];   // rows past QN do not exist
+    const double2 alpha = v[k];
+    double2 tau = cz(0.0, 0.0), scal = cz(1.0, 0.0);
+    double2 diag = alpha;
+    if (!(ssum == 0.0 && alpha.y == 0.0)) {
+      const double beta = -copysign(sqrt(alpha.x * alpha.x + alpha.y * alpha.y + ssum), alpha.x);
+      tau = cz((beta - alpha.x) / beta, -alpha.y / beta);
+      const double2 den = cz(alpha.x - beta, alpha.y);
+      const double dd = cabs2(den);
+      scal = cz(den.x / dd, -den.y / dd);
+      diag = cz(beta, 0.0);
+    }
+    __syncthreads();   // every thread has read v[k]
+    if (tid < m) {
+      double2 t = v[tid];
+      if (tid > k) t = cmul(t, scal);
+      ck[tid] = tid == k ? diag : t;
+      v[tid] = tid < k ? cz(0.0, 0.0) : (tid == k ? cz(1.0, 0.0) : t);
+    }
+    if (tid == 0) d.tau[k] = tau;
+    __syncthreads();
+    const double2 ctau = cconj(tau);
+    const int rb = k / 64;   // first 64-row block the reflector touches
+    for (int c = k + 1 + 2 * wv; c < n; c += 2 * NW) {
+      const bool two = c + 1 < n;
+      double2 *a0 = d.a + (size_t)c * d.lda, *a1 = d.a + (size_t)(two ? c + 1 : c) * d.lda;
+      double2 x0[RL], x1[RL], d0 = cz(0.0, 0.0), d1 = d0;
+#pragma unroll
+      for (int u = 0; u < RL; ++u) {
+        const int r = 64 * u + lane;
+        const bool in = u >= rb && r < m;
+        x0[u] = ld_or0(a0, r, in);
+        x1[u] = ld_or0(a1, r, in);
+      }
+#pragma unroll
+      for (int u = 0; u < RL; ++u)
+        if (u >= rb && 64 * u < m) {
+          const double2 vr = 64 * u + lane < m ? v[64 * u + lane] : cz(0.0, 0.0);
+          cfmac(d0, vr, x0[u]);
+          cfmac(d1, vr, x1[u]);
+        }
+      const double2 f0 = cmul(ctau, wave_sum(d0)), f1 = cmul(ctau, wave_sum(d1));
+      double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+      for (int u = 0; u < RL; ++u)
+        if (u >= rb && 64 * u < m) {
+          const int r = 64 * u + lane;
+          if (r < m && r >= k) {
+            const double2 vr = v[r];
+            const double2 y0 = csub(x0[u], cmul(vr, f0)), y1 = csub(x1[u], cmul(vr, f1));
+            a0[r] = y0;
+            if (two) a1[r] = y1;
+            if (r > k) {
+              s0 += cabs2(y0);
+              s1 += cabs2(y1);
+            }
+          }
+        }
+      s0 = wave_sum(s0);
+      s1 = wave_sum(s1);
+      if (lane == 0) {
+        nr[c] = s0;
+        if (two) nr[c + 1] = s1;
+      }
+    }
+    __syncthreads();   // norms and columns settled before the next step
+  }
+}
+
 }  // namespace
 
 // One step of the column-pivoted QR above on a batch (the pivot and its
@@ -1070,16 +1204,17 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     // (qrcp_sketch.hip): A is read once per block, not per column (the
     // large periodizer's 8 triangles of 10805 columns: 7.3 -> 3.0 s per
     // incidence; the 256-obstacle batch's triangles: truncation 10.3 ->
-    // 8.8 s).  Small batches of narrow triangles (the k = 10 body's 33 of
-    // 200 columns: 2.3 ms slower sketched) take the column-at-a-time form,
-    // whose steps are short launches there.  MFS_QRCP=sketched, blocked
-    // (the deterministic panel form: panels of 32, updates deferred, norms
-    // downdated, qrcp.hip) or unblocked (every step updating the whole
-    // trailing block) decides.
+    // 8.8 s).  Small batches of triangles narrower than 256 columns (the k = 10
+    // body's 33 of 200) take one launch with a workgroup a matrix
+    // (qrcp_one_kernel).  MFS_QRCP=sketched, blocked (the deterministic panel
+    // form: panels of 32, updates deferred, norms downdated, qrcp.hip) or
+    // unblocked (two launches a column over the whole chip) decides.
     const char *qe = std::getenv("MFS_QRCP");
     const bool big = n2max >= 256 || (size_t)W * n2max * n2max >= ((size_t)1 << 24);
-    const std::string form = qe ? std::string(qe) : (big ? "sketched" : "unblocked");
-    if (form == "sketched") {
+    const std::string form = qe ? std::string(qe) : (big ? "sketched" : "one");
+    if (form == "one" && n2max <= QN) {
+      hipLaunchKernelGGL(qrcp_one_kernel, dim3(W), dim3(QT), 0, s, g.d_rq.as<MatDesc>(), g.piv.as<int>(), nmax);
+    } else if (form == "sketched") {
       qrcp_sketched(g.d_rq.as<MatDesc>(), g.h_rq, g.piv.as<int>(), nmax, s);
     } else if (form != "blocked") {
       for (int k = 0; k < n2max; ++k) {
@@ -1093,7 +1228,10 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
       qrcp_blocked(g.d_rq.as<MatDesc>(), g.h_rq, qn.as<double>(), g.piv.as<int>(), nmax, s);
     }
     HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(build_t_kernel, dim3(W, cdiv(n2max, kQRNB)), dim3(256), 0, s, g.d_rq.as<MatDesc>());
+    // T of 32-column panels: read where U is formed with panels that narrow
+    // only (qr_form_u regroups wider matrices into 64 columns)
+    if (n2max <= kQRNB)
+      hipLaunchKernelGGL(build_t_kernel, dim3(W, cdiv(n2max, kQRNB)), dim3(256), 0, s, g.d_rq.as<MatDesc>());
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(s));   // qn is released here
   }

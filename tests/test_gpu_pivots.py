@@ -1,0 +1,45 @@
+"""GPU tests of the pivoted QR of the triangles at the edges of its forms: one
+workgroup a matrix up to 256 columns, sketched above, with the sketch's pivots
+in one launch up to 1536 remaining columns; and of the QR's one-launch panels
+at row counts around whole waves."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mfs():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_1506_05083_amd as m
+    m.lib()
+    return m
+
+
+@pytest.mark.parametrize("M,N", [
+    (2, 1), (4, 3), (33, 32), (34, 33), (65, 64), (66, 65), (127, 100), (128, 128), (129, 127), (193, 192),
+    (257, 255), (256, 256), (300, 257), (512, 500), (513, 513), (1040, 1030), (1560, 1540),
+])
+def test_singular_values_at_edges(mfs, M, N):
+    """Singular values of the GPU's own blocks against LAPACK, 1e-13 of the
+    largest or N eps where that is larger (each side is backward stable), and the
+    kept ranks within one of LAPACK's count."""
+    b = W.small_periodic().body
+    ctx = mfs.create(0)
+    op = mfs.build_operator(ctx, [mfs.BodySpec(M, N, 2, 64, b.k, mfs.polar_geometry(
+        b.shape.a, b.shape.eps, b.shape.j, M, N, b.tau, b.colloc))])
+    blocks = op.blocks().cpu().numpy().transpose(0, 2, 1)
+    ranks = op.factor_modes(1e-10)
+    sv = op.singular_values(0)
+    tol = max(1e-13, N * np.finfo(float).eps)
+    for n in range(blocks.shape[0]):
+        s = np.linalg.svd(blocks[n], compute_uv=False)
+        e = float(np.max(np.abs(sv[n][: s.size] - s)) / s[0])
+        print(f"[pivots {M} x {N}] mode {n}: rank {ranks[n]}, singular values {e:.1e}", flush=True)
+        assert abs(int(ranks[n]) - int(np.sum(s > 1e-10 * s[0]))) <= 1
+        assert e < tol
