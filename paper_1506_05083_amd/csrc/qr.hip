@@ -212,113 +212,167 @@ __global__ __launch_bounds__(CH) void bqr_col_kernel(const MatDesc *__restrict__
 }
 
 // The whole panel at k0 of a matrix whose rows from k0 on fit one workgroup
-// (m - k0 <= blockDim.x <= 512): one row per thread with the row's panel
-// entries in registers, the NB column steps of bqr_col_kernel carried out
-// in turn with block-wide sums (wave sums, then across the waves in LDS)
-// instead of one launch each, so the panel is read and written once.  The
-// arithmetic of a step is that of bqr_col_kernel: x^H a_c over the rows
-// r >= j, |x(2:)|^2 over r > j, LAPACK's zlarfg reflector.
-constexpr int PTMAX = 512;             // threads (rows) of the one-launch panel
-constexpr int PWMAX = PTMAX / 64;
-template <int NB>
-__global__ __launch_bounds__(PTMAX) void bqr_panel_kernel(const MatDesc *__restrict__ descs, int k0) {
-  constexpr int NPART = NB + 1;
-  const MatDesc d = descs[blockIdx.x];
-  if (k0 >= d.n) return;
-  const int nbp = min(NB, d.n - k0);
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int nw = blockDim.x >> 6;
-  const int r = k0 + tid;
-  const bool live = r < d.m;
-  __shared__ double2 red[PWMAX][NPART];
-  __shared__ double2 fin[NPART];
-  __shared__ double2 srow[NB];
-  __shared__ double2 s_scale, s_tau, s_alpha;
-  __shared__ double s_beta;
-  __shared__ int s_refl;
-  double2 vals[NB];
+// (m - k0 <= PTMAX) in one launch, with the panel's T.  A thread holds one
+// column c = lane % 16 of the rows 4 u + lane / 16 (u < RPT) of its wave's
+// 4 RPT rows, wave 0 the first.  Step S:
+//   * column S goes from lane S to its row of 16 lanes by DPP, and every thread
+//     adds up t_c = sum conj(x_r) a_c(r) over its rows r below j = k0 + S;
+//     the four threads of a column in a wave are added by lane swaps, the
+//     waves through LDS (one barrier a step, two buffers);
+//   * t_S = |x(2:)|^2 gives LAPACK's zlarfg reflector v = scale x (1 on row j),
+//     w_c = v^H a_c = a_c(j) + conj(scale) t_c, and the columns c > S are
+//     updated: a_c(r) -= x_r (scale tau^* w_c), row j by tau^* w_c;
+//   * the finished columns c < S hold x unscaled, so their t_c is what
+//     v_c^H v_S of T needs.
+// The columns are scaled to v at the end, and wave 0 runs T's recurrence.
+// A step is a serial chain (sums, square root, division, update).  With a row a
+// thread, every column's sum a DPP scan of its own and five barriers, a step
+// took 4 us whatever the rows: 17 panels of 60 rows 50 -> 19 us, 65 of 250 rows
+// 67 -> 31, and 65 of 700 rows, a launch a column, 144 -> 55.  Past PTMAX rows the
+// entries no longer fit a workgroup's registers.
+constexpr int PTMAX = 1024;   // rows of the one-launch panel
+constexpr int PNB = 16;       // its columns
+
+// lane C of every row of 16 lanes to the whole row (all lanes active)
+template <int C>
+__device__ inline double row_lane(double v) {
+  return __longlong_as_double(
+      __builtin_amdgcn_update_dpp(0L, (long)__double_as_longlong(v), 0x150 + C, 0xf, 0xf, true));
+}
+template <int C>
+__device__ inline double2 row_lane(double2 v) {
+  return cz(row_lane<C>(v.x), row_lane<C>(v.y));
+}
+// sum over the wave's four rows of 16 lanes, the same bits in all of them
+__device__ inline double sum_rows16(double v) {
+  auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  v = __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+  l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+}
+
+struct PanelShared {
+  double2 red[2][PTMAX / 64][PNB], row[2][PNB];
+  double2 g[PNB][PNB + 1], tau[PNB];
+};
+
+template <int S, int RPT, int NWMAX>
+__device__ inline void panel_steps(double2 (&a)[RPT], double2 &myscale, PanelShared &sh, int nbp,
+                                   int wv, int c, int k) {
+  if constexpr (S < PNB) {
+    if (S < nbp) {   // uniform
+      constexpr int B = S & 1, U = S / 4;
+      const bool top = wv == 0;
+      double2 t = cz(0.0, 0.0), t1 = t;
 #pragma unroll
-  for (int c = 0; c < NB; ++c) vals[c] = ld_or0(d.a, (size_t)(k0 + c) * d.lda + r, live && c < nbp);
-  for (int s = 0; s < nbp; ++s) {
-    const int j = k0 + s;
-    double2 x = cz(0.0, 0.0);   // vals[s] without a run-time index into the array
-#pragma unroll
-    for (int c = 0; c < NB; ++c)
-      if (c == s) x = vals[c];
-    if (live && r == j) {
-#pragma unroll
-      for (int c = 0; c < NB; ++c)
-        if (c >= s && c < nbp) srow[c] = vals[c];
-    }
-    const double2 xr = (live && r >= j) ? x : cz(0.0, 0.0);
-    {
-      double q = (live && r > j) ? cabs2(x) : 0.0;
-      q = wave_sum(q);
-      if (lane == 0) red[wv][0] = cz(q, 0.0);
-    }
-#pragma unroll
-    for (int c = 0; c < NB; ++c) {
-      if (c > s && c < nbp) {
-        double2 p = cz(0.0, 0.0);
-        cfmac(p, xr, vals[c]);
-        p = wave_sum(p);
-        if (lane == 0) red[wv][1 + c] = p;
+      for (int u = 0; u < RPT; ++u) {
+        // the rows in order: fetched ahead, x takes 4 RPT registers
+        if (u >= 2) asm volatile("" : "+v"(a[u].x), "+v"(a[u].y) : "v"(t.x), "v"(t1.x));
+        double2 x = row_lane<S>(a[u]);
+        if (u <= U) x = csel(top && 4 * u + k <= S, cz(0.0, 0.0), x);
+        cfmac((u & 1) ? t1 : t, x, a[u]);
       }
-    }
-    __syncthreads();
-    if (tid < NPART && (tid == 0 || (tid - 1 > s && tid - 1 < nbp))) {
-      double2 t = red[0][tid];
-      for (int w = 1; w < nw; ++w) t = cadd(t, red[w][tid]);
-      fin[tid] = t;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      const double ssum = fin[0].x;
-      const double2 alpha = srow[s];
-      s_alpha = alpha;
-      if (ssum == 0.0 && alpha.y == 0.0) {
-        s_refl = 0;
-        s_tau = cz(0.0, 0.0);
-        s_beta = alpha.x;
-        s_scale = cz(0.0, 0.0);
-      } else {
+      t = cadd(t, t1);
+      t = cz(sum_rows16(t.x), sum_rows16(t.y));
+      if (k == 0) sh.red[B][wv][c] = t;
+      if (top && k == (S & 3)) sh.row[B][c] = a[U];
+      __syncthreads();
+      t = cz(0.0, 0.0);
+#pragma unroll
+      for (int w = 0; w < NWMAX; w += 4) t = cadd(t, sh.red[B][w + k][c]);   // 0 past the last wave
+      t = cz(sum_rows16(t.x), sum_rows16(t.y));
+      const double2 acj = sh.row[B][c], alpha = sh.row[B][S];
+      const double ssum = row_lane<S>(t.x);
+      double2 tau = cz(0.0, 0.0), scale = cz(0.0, 0.0), diag = alpha;
+      if (!(ssum == 0.0 && alpha.y == 0.0)) {
         const double beta = -copysign(sqrt(alpha.x * alpha.x + alpha.y * alpha.y + ssum), alpha.x);
         const double2 den = cz(alpha.x - beta, alpha.y);
         const double dd = cabs2(den);
-        s_refl = 1;
-        s_tau = cz((beta - alpha.x) / beta, -alpha.y / beta);
-        s_beta = beta;
-        s_scale = cz(den.x / dd, -den.y / dd);
+        tau = cz((beta - alpha.x) / beta, -alpha.y / beta);
+        scale = cz(den.x / dd, -den.y / dd);
+        diag = cz(beta, 0.0);
       }
-      d.tau[j] = s_tau;
-    }
-    __syncthreads();
-    const double2 scale = s_scale, tau = s_tau, alpha = s_alpha;
-    const int refl = s_refl;
-    if (live && r >= j) {
-      const double2 v = (r == j) ? cz(1.0, 0.0) : (refl ? cmul(x, scale) : x);
+      // tau^* (a_c(j) + conj(scale) t_c) of the columns still to come
+      double2 f = acj;
+      cfma(f, cconj(scale), t);
+      f = csel(c > S, cmul(cconj(tau), f), cz(0.0, 0.0));
+      const double2 g = cmul(scale, f), mg = cz(-g.x, -g.y);
+      if (top && k == 0 && c < S)   // v_c^H v_S
+        sh.g[c][S] = cmul(cconj(myscale), cadd(cconj(acj), cmul(scale, cconj(t))));
 #pragma unroll
-      for (int c = 0; c < NB; ++c) {
-        if (c > s && c < nbp) {
-          // w_c = v^H a_c = a_c(j) + conj(scale) (x^H a_c - conj(alpha) a_c(j))
-          const double2 acj = srow[c];
-          double2 w = csub(fin[1 + c], cmul(cconj(alpha), acj));
-          w = cadd(acj, cmul(cconj(scale), w));
-          const double2 f = refl ? cmul(cconj(tau), w) : cz(0.0, 0.0);
-          vals[c] = csub(vals[c], cmul(v, f));
-        }
+      for (int u = 0; u < RPT; ++u) {
+        // likewise, and column S fetched again rather than kept from above
+        if (u >= 2)
+          asm volatile("" : "+v"(a[u].x), "+v"(a[u].y) : "v"(a[u - 2].x), "v"(a[u - 2].y));
+        else
+          asm volatile("" : "+v"(a[u].x), "+v"(a[u].y) : "v"(mg.x));
+        double2 x = row_lane<S>(a[u]);
+        if (u <= U) x = csel(top && 4 * u + k <= S, cz(0.0, 0.0), x);
+        cfma(a[u], x, mg);
       }
-      const double2 nv = (r == j) ? (refl ? cz(s_beta, 0.0) : alpha) : v;
-#pragma unroll
-      for (int c = 0; c < NB; ++c)
-        if (c == s) vals[c] = nv;
+      if (top && k == (S & 3)) a[U] = c == S ? diag : csub(a[U], f);
+      myscale = csel(c == S, scale, myscale);
+      if (top && c == 0 && k == 0) sh.tau[S] = tau;
+      panel_steps<S + 1, RPT, NWMAX>(a, myscale, sh, nbp, wv, c, k);
     }
-    __syncthreads();   // srow, fin and the scalars are rewritten by the next step
   }
-  if (live) {
+}
+
+// row c of T = -T V^H V tau, upper triangular, a column at a time
+template <int S>
+__device__ inline void panel_t(double2 (&t)[PNB], double2 mytau, const PanelShared &sh, int nbp, int c) {
+  if constexpr (S < PNB) {
+    const double2 tau = row_lane<S>(mytau);
+    double2 acc = cz(0.0, 0.0);
+    if (S < nbp) {
 #pragma unroll
-    for (int c = 0; c < NB; ++c)
-      if (c < nbp) d.a[(size_t)(k0 + c) * d.lda + r] = vals[c];
+      for (int i = 0; i < S; ++i) cfma(acc, t[i], sh.g[i][S]);
+    }
+    acc = cmul(cz(-tau.x, -tau.y), acc);
+    t[S] = S >= nbp || c > S ? cz(0.0, 0.0) : csel(c == S, tau, acc);
+    panel_t<S + 1>(t, mytau, sh, nbp, c);
+  }
+}
+
+template <int RPT, int NWMAX>
+__global__ __launch_bounds__(64 * NWMAX) void bqr_panel_kernel(const MatDesc *__restrict__ descs, int k0, int nbo,
+                                                               double2 *__restrict__ tx) {
+  const MatDesc d = descs[blockIdx.x];
+  if (k0 >= d.n) return;
+  const int nbp = min(PNB, d.n - k0);
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int c = lane & 15, k = lane >> 4;
+  __shared__ PanelShared sh;
+  for (int i = tid; i < 2 * (PTMAX / 64) * PNB; i += blockDim.x) (&sh.red[0][0][0])[i] = cz(0.0, 0.0);
+  const int r0 = k0 + 4 * RPT * wv + k;
+  double2 *col = d.a + (size_t)(k0 + min(c, nbp - 1)) * d.lda;
+  double2 a[RPT];
+#pragma unroll
+  for (int u = 0; u < RPT; ++u) a[u] = ld_or0(col, r0 + 4 * u, c < nbp && r0 + 4 * u < d.m);
+  double2 myscale = cz(0.0, 0.0);
+  __syncthreads();
+  panel_steps<0, RPT, NWMAX>(a, myscale, sh, nbp, wv, c, k);
+#pragma unroll
+  for (int u = 0; u < RPT; ++u) {
+    const int r = r0 + 4 * u;
+    if (c < nbp && r < d.m) col[r] = r > k0 + c ? cmul(a[u], myscale) : a[u];
+  }
+  __syncthreads();
+  if (wv > 0) return;
+  const double2 mytau = csel(c < nbp, sh.tau[c], cz(0.0, 0.0));
+  double2 t[PNB];
+  panel_t<0>(t, mytau, sh, nbp, c);
+  if (k == 0) {
+    if (c < nbp) d.tau[k0 + c] = mytau;
+    const int o = k0 % nbo;
+    double2 *T = d.T + (size_t)(k0 / nbo) * nbo * nbo + (size_t)o * nbo + o;
+#pragma unroll
+    for (int j = 0; j < PNB; ++j) {
+      T[(size_t)j * nbo + c] = t[j];
+      if (tx) tx[(size_t)blockIdx.x * PNB * PNB + j * PNB + c] = t[j];
+    }
   }
 }
 
@@ -816,7 +870,7 @@ __global__ __launch_bounds__(TThreads<NB>::N) void bqr_t_kernel(const MatDesc *_
   __shared__ double2 tmp[NB];
   const bool blk = wv < NB / 16 && lane < 16;
   const int o = 16 * wv;
-  if (diag) {   // given (cq_reflect_kernel)
+  if (diag) {   // given (cq_reflect_kernel, bqr_panel_kernel)
     const double2 *T = d.T + (size_t)(k0 / NB) * NB * NB;
     for (int idx = tid; idx < NB * NB; idx += TT) {
       const int r = idx % NB, c = idx / NB;
@@ -1099,7 +1153,7 @@ void apply_panel(const MatDesc *descs, int nmat, int mmax, int ncols_max, int k0
 // Householder vectors and tau of the columns [k0, k0 + NI) (NI = 16), the
 // column steps of bqr_col_kernel or the one-launch bqr_panel_kernel
 struct PanelWork {
-  static constexpr int NI = 16;
+  static constexpr int NI = PNB;
   DevBuf part, side;
   int nchmax = 0;
   int *bad = nullptr;   // given: Cholesky panels, [nmat] flags of matrices they could not factor
@@ -1110,6 +1164,8 @@ struct PanelWork {
     part.alloc((size_t)nmat * 2 * nchmax * np * sizeof(double2));
     side.alloc((size_t)nmat * 2 * ns * sizeof(double2));
   }
+  // whether factor() brings T of the panel at k0
+  bool brings_t(int mmax, int k0) const { return bad || mmax - k0 <= PTMAX; }
   void factor(const MatDesc *descs, int nmat, int mmax, int nmax, int k0, hipStream_t s, int nbo, double2 *tx) {
     const int nbp = std::min(NI, nmax - k0);
     if (bad) {
@@ -1121,9 +1177,17 @@ struct PanelWork {
       hipLaunchKernelGGL(cq_reflect_kernel, g, dim3(CH), 0, s, descs, k0, p2, side.as<double2>(), nchmax, bad,
                          nbo, tx);
     } else if (mmax - k0 <= PTMAX) {
-      // every matrix's remaining rows fit one workgroup: the panel in one launch
-      const int threads = round_up(std::max(mmax - k0, 1), 64);
-      hipLaunchKernelGGL(bqr_panel_kernel<NI>, dim3(nmat), dim3(threads), 0, s, descs, k0);
+      // every matrix's remaining rows fit one workgroup: the panel in one launch,
+      // with the fewest rows a thread that eight waves can take (a step of four
+      // rows a thread 1.2 us, of eight 1.8, of sixteen 2.5 to 3.4)
+      const int rows = std::max(mmax - k0, 1);
+      if (rows <= 128)
+        hipLaunchKernelGGL((bqr_panel_kernel<4, 8>), dim3(nmat), dim3(64 * cdiv(rows, 16)), 0, s, descs, k0, nbo, tx);
+      else if (rows <= 256)
+        hipLaunchKernelGGL((bqr_panel_kernel<8, 8>), dim3(nmat), dim3(64 * cdiv(rows, 32)), 0, s, descs, k0, nbo, tx);
+      else
+        hipLaunchKernelGGL((bqr_panel_kernel<16, 16>), dim3(nmat), dim3(64 * cdiv(rows, 64)), 0, s, descs, k0, nbo,
+                           tx);
     } else {
       const int nch = cdiv(std::max(mmax - k0, 1), CH);
       for (int st = -1; st < nbp; ++st)
@@ -1164,14 +1228,15 @@ struct BlockedQR {
   }
   // the panel of columns [K0, K0 + NB) and its update of the columns after it
   void panel(int K0, hipStream_t s) {
-    // Cholesky panels bring their T: the inner applies need no V^H V
-    const bool given = pw.bad != nullptr;
+    // Cholesky and one-launch panels bring their T: the inner applies need no V^H V
     for (int k0 = K0; k0 < std::min(K0 + NB, nmax); k0 += NI) {
       pw.factor(descs, nmat, mmax, nmax, k0, s, NB, NB > NI ? tx.as<double2>() : nullptr);
       const int rest = std::min(K0 + NB, nmax) - (k0 + NI);   // inner columns still to update
+      const bool given = pw.brings_t(mmax, k0);
       if (NB > NI && rest > 0)
         apply_panel<NI>(descs, nmat, mmax, rest, k0, 0, !given, 1, wi, !given, s, K0 + NB, tx.as<double2>());
     }
+    const bool given = pw.brings_t(mmax, K0);   // then also of the panels after it
     const bool whole = NB == NI && given;   // T complete
     apply_panel<NB>(descs, nmat, mmax, std::max(0, nmax - K0 - NB), K0, 0, !whole, 1, w, !whole, s, kNoEnd, nullptr,
                     given);
