@@ -18,20 +18,24 @@
 // Blocked form for the GPU: the columns are cut into blocks of JB (16, or 32
 // once a batch's widest matrix has kJacWideMinCols columns) and the
 // round-robin (circle) schedule pairs the blocks, n_b - 1 rounds per sweep.
-// A task is a block pair (JC = 2 JB columns); a round is three launches over
-// all tasks of all matrices:
-//   1. jac_gram_mfma_kernel (JB = 16) / jac_gram_mfma32_kernel (JB = 32):
-//      partial H = G_IJ^H G_IJ (JC x JC) over 128-row tiles on the FP64
-//      matrix cores, every entry a dot product of two columns;
-//   2. jac_inner_kernel (one workgroup per task): H summed over the tiles,
-//      one Jacobi sweep over the JC columns carried out on H in LDS (the
+// A task is a block pair (JC = 2 JB columns), a workgroup's work in a round:
+//   1. H = G_IJ^H G_IJ (JC x JC) on the FP64 matrix cores, every entry a dot
+//      product of two columns;
+//   2. one Jacobi sweep over the JC columns carried out on H in LDS (the
 //      two-sided update H <- R^H H R of each rotation R, with the exact
 //      diagonal formulas above and the annihilated entry set to zero), the
 //      product J of the rotations accumulated alongside;
-//   3. jac_apply_mfma_kernel / jac_apply_mfma32_kernel: if any pair of the
-//      task rotated, G_IJ <- G_IJ J over row tiles.
-// The row tiles spread every round over the whole chip whatever the number
-// of tasks, and the apply streams G once per round.
+//   3. if any pair of the task rotated, G_IJ <- G_IJ J over row tiles.
+// JB = 16, many tasks: one launch a round (jac_round_kernel): workgroups in
+// different phases share a compute unit, so the matrix cores, the rotations'
+// FP64 and the memory traffic overlap, and step 3 finds step 1's columns in
+// the caches.  1105 tasks of 550 rows: 329 us a round while all rotate, where
+// three launches took 105 + 108 + 166; 34 tasks of 60 rows 30 us, 10 + 32 + 9
+// before.  (In groups of matrices that fit the last-level cache three launches
+// were too small: 16 bodies 387 -> 473 ms with 160 MB groups.)
+// Few tasks of many rows: three launches, which spread the rows over the chip:
+// the Gram matrix over 128-row tiles, the sweep a workgroup a task, the product
+// over 64-row tiles (JB = 32: 16-row tiles).
 // Every pair of columns meets in some workgroup every sweep, pairs inside a
 // block in every task of that block; sweeps repeat until no pair of a matrix
 // needed a rotation (|gamma| <= tol sqrt(a b)), a matrix that converged
@@ -131,8 +135,102 @@ __global__ void jac_clear_checks(JacClean cs, int nmat) {
   if (i < nmat) cs.nchk[i] = 0;
 }
 
-// 2. one workgroup per task: H = sum of the partials, one Jacobi sweep over
-//    its JC columns on H, J = product of the rotations -> jbuf, rot = any rotation
+// One Jacobi sweep over the JC columns of a task on H (Hs), the rotations'
+// product in Js (identity on entry); returns the number of rotations.  All
+// JB * JB threads, H and J settled (a barrier) on entry.  Rotation of pair
+// (p, q) from a = H_pp, b = H_qq, gamma = H_pq, d = b - a:
+//   q' = 2 sign(d) / (|d| + sqrt(d^2 + 4 |gamma|^2)),  t = q' |gamma|,
+//   c = 1 / sqrt(1 + t^2),  s e^{i th} = c q' gamma,  t |gamma| = q' |gamma|^2
+// (the formulas of the header with zeta = d / (2 |gamma|), |gamma| never formed).
+// H <- R^H H R acts on every 2 x 2 block (rows of pair i, columns of pair j)
+// on its own: JB x JB blocks over the threads, J <- J R alongside.  A round is
+// a serial chain (entries, root, quotient, root, update, two barriers), so the
+// blocks of H and J are fetched before the chain of the first JB threads, and
+// a pair that does not turn is the identity rotation, not a branch.
+template <int JB>
+struct InnerWork {
+  double r_c[JB], r_a[JB], r_b[JB];
+  double2 r_se[JB];
+  unsigned mask;   // pairs that turn
+};
+template <int JB>
+__device__ inline void inner_pair(int rnd, int pair, int &p, int &q) {   // circle_pair without quotients, rnd < 2 JB - 1
+  constexpr int mod = 2 * JB - 1;
+  p = rnd + pair;
+  q = rnd - pair;
+  p -= p >= mod ? mod : 0;
+  q += q < 0 ? mod : 0;
+  if (pair == 0) q = mod;
+}
+template <int JB>
+__device__ inline int jac_inner_sweep(double2 (*Hs)[2 * JB + 1], double2 (*Js)[2 * JB + 1], InnerWork<JB> &wk,
+                                      double tol2) {
+  constexpr int JC = 2 * JB;
+  const int tid = threadIdx.x, bi = tid / JB, bj = tid % JB, k = 2 * bi;
+  int nrot = 0;
+  for (int rnd = 0; rnd < JC - 1; ++rnd) {
+    int p, q, u, v;
+    inner_pair<JB>(rnd, bi, p, q);
+    inner_pair<JB>(rnd, bj, u, v);
+    double2 h_pu = Hs[p][u], h_pv = Hs[p][v], h_qu = Hs[q][u], h_qv = Hs[q][v];
+    const double2 x0 = Js[k][u], y0 = Js[k][v], x1 = Js[k + 1][u], y1 = Js[k + 1][v];
+    if (tid < JB) {
+      inner_pair<JB>(rnd, tid, p, q);
+      const double a = Hs[p][p].x, b = Hs[q][q].x;
+      const double2 gam = Hs[p][q];
+      const double g2 = cabs2(gam);
+      const bool on = g2 > tol2 * a * b;
+      const double dd = b - a;
+      const double qq = copysign(2.0, dd) / (fabs(dd) + sqrt(fma(dd, dd, 4.0 * g2)));
+      const double cs = rsqrt(fma(qq * qq, g2, 1.0));
+      const unsigned long long m = __ballot(on);
+      wk.r_c[tid] = on ? cs : 1.0;
+      wk.r_se[tid] = on ? cz(cs * qq * gam.x, cs * qq * gam.y) : cz(0.0, 0.0);
+      wk.r_a[tid] = a - qq * g2;
+      wk.r_b[tid] = b + qq * g2;
+      if (tid == 0) wk.mask = (unsigned)m;
+      inner_pair<JB>(rnd, bi, p, q);
+    }
+    __syncthreads();
+    const unsigned m = wk.mask;
+    if (m) {   // uniform
+      nrot += __popc(m);
+      const bool ai = (m >> bi) & 1, aj = (m >> bj) & 1;
+      const double ci = wk.r_c[bi], cj = wk.r_c[bj];
+      const double2 si = wk.r_se[bi], sj = wk.r_se[bj], sic = cconj(si), sjc = cconj(sj);
+      // columns: [x_u, x_v] <- [c x_u - conj(se) x_v, se x_u + c x_v]
+      if (ai || aj) {
+        double2 pu = csub(cscale(h_pu, cj), cmul(sjc, h_pv));
+        double2 pv = cadd(cmul(sj, h_pu), cscale(h_pv, cj));
+        double2 qu = csub(cscale(h_qu, cj), cmul(sjc, h_qv));
+        double2 qv = cadd(cmul(sj, h_qu), cscale(h_qv, cj));
+        // rows: [y_p; y_q] <- [c y_p - se y_q; conj(se) y_p + c y_q]
+        h_pu = csub(cscale(pu, ci), cmul(si, qu));
+        h_qu = cadd(cmul(sic, pu), cscale(qu, ci));
+        h_pv = csub(cscale(pv, ci), cmul(si, qv));
+        h_qv = cadd(cmul(sic, pv), cscale(qv, ci));
+        if (bi == bj) {   // pivot block: exact values
+          h_pu = cz(wk.r_a[bi], 0.0);
+          h_qv = cz(wk.r_b[bi], 0.0);
+          h_pv = cz(0.0, 0.0);
+          h_qu = cz(0.0, 0.0);
+        }
+        Hs[p][u] = h_pu; Hs[p][v] = h_pv; Hs[q][u] = h_qu; Hs[q][v] = h_qv;
+      }
+      if (aj) {
+        Js[k][u] = csub(cscale(x0, cj), cmul(sjc, y0));
+        Js[k][v] = cadd(cmul(sj, x0), cscale(y0, cj));
+        Js[k + 1][u] = csub(cscale(x1, cj), cmul(sjc, y1));
+        Js[k + 1][v] = cadd(cmul(sj, x1), cscale(y1, cj));
+      }
+    }
+    __syncthreads();   // H, J and the rotations of this round settled before the next
+  }
+  return nrot;
+}
+
+// 2. as a launch: H summed over the row tiles' partials, the sweep, J -> jbuf,
+// rot = any rotation
 template <int JB>
 __global__ __launch_bounds__(JB * JB) void jac_inner_kernel(const MatDesc *__restrict__ descs,
                                                         const int *__restrict__ act, int round, double tol_eps,
@@ -155,10 +253,7 @@ __global__ __launch_bounds__(JB * JB) void jac_inner_kernel(const MatDesc *__res
   }
   __shared__ double2 Hs[JC][JC + 1];
   __shared__ double2 Js[JC][JC + 1];
-  __shared__ double r_c[JB], r_tg[JB], r_a[JB], r_b[JB];
-  __shared__ double2 r_se[JB];
-  __shared__ int r_act[JB];
-  __shared__ int s_nrot;
+  __shared__ InnerWork<JB> wk;
   const int tid = threadIdx.x;
   const int ntile = (d.n + GT - 1) / GT;
   // relative orthogonality reachable in floating point, ~ sqrt(n) eps of this
@@ -180,98 +275,8 @@ __global__ __launch_bounds__(JB * JB) void jac_inner_kernel(const MatDesc *__res
       Js[idx / JC][idx % JC] = cz(idx / JC == idx % JC ? 1.0 : 0.0, 0.0);
     }
   }
-  if (tid == 0) s_nrot = 0;
   __syncthreads();
-  // one sweep over the JC columns on H.  Rotation of pair (p, q) from
-  // a = H_pp, b = H_qq, gamma = H_pq, d = b - a:
-  //   q' = 2 sign(d) / (|d| + sqrt(d^2 + 4 |gamma|^2)),  t = q' |gamma|,
-  //   c = 1 / sqrt(1 + t^2),  s e^{i th} = c q' gamma,  t |gamma| = q' |gamma|^2
-  // (the formulas of the header with zeta = d / (2 |gamma|), |gamma| never formed).
-  // H <- R^H H R acts on every 2 x 2 block (rows of pair i, columns of pair j)
-  // on its own: JB x JB blocks over the threads, J <- J R alongside.
-  for (int rnd = 0; rnd < JC - 1; ++rnd) {
-    if (tid < JB) {
-      int p, q;
-      circle_pair(JC, rnd, tid, p, q);
-      const double a = Hs[p][p].x, b = Hs[q][q].x;
-      const double2 gam = Hs[p][q];
-      const double g2 = cabs2(gam);
-      const int on = g2 > tol2 * a * b;
-      if (on) {
-        const double dd = b - a;
-        const double qq = copysign(2.0, dd) / (fabs(dd) + sqrt(fma(dd, dd, 4.0 * g2)));
-        const double cs = rsqrt(fma(qq * qq, g2, 1.0));
-        r_c[tid] = cs;
-        r_se[tid] = cz(cs * qq * gam.x, cs * qq * gam.y);
-        r_tg[tid] = qq * g2;
-        r_a[tid] = a;
-        r_b[tid] = b;
-      }
-      r_act[tid] = on;
-    }
-    __syncthreads();
-    int any = 0;
-#pragma unroll
-    for (int i = 0; i < JB; ++i) any |= r_act[i];
-    if (any) {   // uniform: every thread read the same flags
-      if (tid == 0) {
-        int cnt = 0;
-        for (int i = 0; i < JB; ++i) cnt += r_act[i];
-        s_nrot += cnt;
-      }
-      {
-        // H block (pair i rows, pair j columns)
-        const int bi = tid / JB, bj = tid % JB;
-        int p, q, u, v;
-        circle_pair(JC, rnd, bi, p, q);
-        circle_pair(JC, rnd, bj, u, v);
-        const int ai = r_act[bi], aj = r_act[bj];
-        if (ai || aj) {
-          double2 h_pu = Hs[p][u], h_pv = Hs[p][v], h_qu = Hs[q][u], h_qv = Hs[q][v];
-          if (bi == bj) {
-            // pivot block: exact values
-            h_pu = cz(r_a[bi] - r_tg[bi], 0.0);
-            h_qv = cz(r_b[bi] + r_tg[bi], 0.0);
-            h_pv = cz(0.0, 0.0);
-            h_qu = cz(0.0, 0.0);
-          } else {
-            if (aj) {   // columns: [x_u, x_v] <- [c x_u - conj(se) x_v, se x_u + c x_v]
-              const double cs = r_c[bj];
-              const double2 se = r_se[bj], sec = cconj(r_se[bj]);
-              const double2 pu = csub(cscale(h_pu, cs), cmul(sec, h_pv));
-              const double2 pv = cadd(cmul(se, h_pu), cscale(h_pv, cs));
-              const double2 qu = csub(cscale(h_qu, cs), cmul(sec, h_qv));
-              const double2 qv = cadd(cmul(se, h_qu), cscale(h_qv, cs));
-              h_pu = pu; h_pv = pv; h_qu = qu; h_qv = qv;
-            }
-            if (ai) {   // rows: [y_p; y_q] <- [c y_p - se y_q; conj(se) y_p + c y_q]
-              const double cs = r_c[bi];
-              const double2 se = r_se[bi], sec = cconj(r_se[bi]);
-              const double2 pu = csub(cscale(h_pu, cs), cmul(se, h_qu));
-              const double2 qu = cadd(cmul(sec, h_pu), cscale(h_qu, cs));
-              const double2 pv = csub(cscale(h_pv, cs), cmul(se, h_qv));
-              const double2 qv = cadd(cmul(sec, h_pv), cscale(h_qv, cs));
-              h_pu = pu; h_pv = pv; h_qu = qu; h_qv = qv;
-            }
-          }
-          Hs[p][u] = h_pu; Hs[p][v] = h_pv; Hs[q][u] = h_qu; Hs[q][v] = h_qv;
-        }
-        // J columns of pair bj, rows 2 bi and 2 bi + 1
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int k = 2 * bi + e;
-          if (aj) {
-            const double cs = r_c[bj];
-            const double2 se = r_se[bj], sec = cconj(r_se[bj]);
-            const double2 x = Js[k][u], y = Js[k][v];
-            Js[k][u] = csub(cscale(x, cs), cmul(sec, y));
-            Js[k][v] = cadd(cmul(se, x), cscale(y, cs));
-          }
-        }
-      }
-    }
-    __syncthreads();   // H, J and the flags of this round settled before the next
-  }
+  const int s_nrot = jac_inner_sweep<JB>(Hs, Js, wk, tol2);
   double2 *jo = jbuf + ((size_t)mat * npair_max + pair) * JC * JC;
   for (int idx = tid; idx < JC * JC; idx += IT) jo[idx] = Js[idx / JC][idx % JC];
   if (tid == 0) {
@@ -426,6 +431,133 @@ __global__ __launch_bounds__(64) void jac_apply_mfma_kernel(const MatDesc *__res
         if (cB >= 0) M[(size_t)cB * d.ldg + row] = cz(re1[rb][v], im1[rb][v]);
       }
     }
+}
+
+// A round of JB = 16: one workgroup a task.
+//   Gram: the rows are the summation index; step s of a wave's 32-row run takes
+//   rows 4 s + k, and the fragment a lane loads (row 4 s + k of task column c)
+//   is at once its A operand (conj(G)^T) and its B operand (G), for the column
+//   blocks (0, 0), (0, 1) and (1, 1); block (1, 0) is the conjugate transpose
+//   of (0, 1).  The waves take alternate runs and add up through LDS.
+//   Apply: a wave takes 16-row blocks of all 32 task columns; step s sums over
+//   task columns 4 s .. 4 s + 3 with the fragments of J read from LDS.  It reads its rows of every column before it writes any,
+//   and tiles share no rows, so the update is in place.
+__global__ __launch_bounds__(256, 4) void jac_round_kernel(const MatDesc *__restrict__ descs,
+                                                           const int *__restrict__ act, int round, double tol_eps,
+                                                           JacClean cs, int gr) {
+  constexpr int JB = 16, JC = 32, KB = 4;
+  const int mat = blockIdx.y;
+  if (!act[mat]) return;
+  const MatDesc d = descs[mat];
+  const int n = d.n;
+  int bi, bj, nb;
+  if (!task_blocks<JB>(d, round, blockIdx.x, bi, bj, nb)) return;
+  if (jac_clean(cs, mat, bi, bj)) return;   // uniform; converged and unchanged since
+  __shared__ double2 Hs[JC][JC + 1], Js[JC][JC + 1];
+  __shared__ InnerWork<JB> wk;
+  const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6;
+  const int c = l & 15, k = l >> 4;
+  {
+    const int c0 = task_col<JB>(c, bi, bj, nb, n), c1 = task_col<JB>(JB + c, bi, bj, nb, n);
+    const double2 *g0 = d.g + (size_t)max(c0, 0) * d.ldg, *g1 = d.g + (size_t)max(c1, 0) * d.ldg;
+    dx4 r00 = {0, 0, 0, 0}, i00 = r00, r01 = r00, i01 = r00, r11 = r00, i11 = r00;
+    for (int rb = 4 * KB * wv; rb < n; rb += 16 * KB) {   // uniform over the wave
+      double2 x0[KB], x1[KB];
+#pragma unroll
+      for (int s = 0; s < KB; ++s) {
+        const int r = rb + 4 * s + k;
+        x0[s] = ld_or0(g0, r, r < n && c0 >= 0);
+        x1[s] = ld_or0(g1, r, r < n && c1 >= 0);
+      }
+#pragma unroll
+      for (int s = 0; s < KB; ++s) {
+        // conj(x_I)^T x_J: real part xr^T xr + xi^T xi, imaginary xr^T xi - xi^T xr
+        r00 = mfma_f64(x0[s].x, x0[s].x, r00);
+        r00 = mfma_f64(x0[s].y, x0[s].y, r00);
+        i00 = mfma_f64(x0[s].x, x0[s].y, i00);
+        i00 = mfma_f64(-x0[s].y, x0[s].x, i00);
+        r01 = mfma_f64(x0[s].x, x1[s].x, r01);
+        r01 = mfma_f64(x0[s].y, x1[s].y, r01);
+        i01 = mfma_f64(x0[s].x, x1[s].y, i01);
+        i01 = mfma_f64(-x0[s].y, x1[s].x, i01);
+        r11 = mfma_f64(x1[s].x, x1[s].x, r11);
+        r11 = mfma_f64(x1[s].y, x1[s].y, r11);
+        i11 = mfma_f64(x1[s].x, x1[s].y, i11);
+        i11 = mfma_f64(-x1[s].y, x1[s].x, i11);
+      }
+    }
+    // the waves in turn (every lane owns its entries)
+    for (int w = 0; w < 4; ++w) {
+      if (wv == w) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int i = k + 4 * v;
+          const double2 a = cz(r00[v], i00[v]), b = cz(r01[v], i01[v]), e = cz(r11[v], i11[v]);
+          Hs[i][c] = w ? cadd(Hs[i][c], a) : a;
+          Hs[i][JB + c] = w ? cadd(Hs[i][JB + c], b) : b;
+          Hs[JB + i][JB + c] = w ? cadd(Hs[JB + i][JB + c], e) : e;
+        }
+      }
+      __syncthreads();
+    }
+  }
+  {
+    const int i = tid / JB, j = tid % JB;
+    Hs[JB + j][i] = cconj(Hs[i][JB + j]);
+  }
+  for (int idx = tid; idx < JC * JC; idx += 256) Js[idx / JC][idx % JC] = cz(idx / JC == idx % JC ? 1.0 : 0.0, 0.0);
+  __syncthreads();
+  // relative orthogonality reachable in floating point, ~ sqrt(n) eps of this
+  // matrix (the stopping rule of LAPACK's one-sided Jacobi)
+  const double tol = tol_eps * sqrt((double)n);
+  const int nrot = jac_inner_sweep<JB>(Hs, Js, wk, tol * tol);
+  if (tid == 0) {
+    atomicAdd(cs.nchk + mat, 1);
+    if (nrot > 0) {
+      atomicAdd(d.flag, 1);
+      cs.bmod[mat * cs.nbp + bi] = gr;
+      cs.bmod[mat * cs.nbp + bj] = gr;
+    } else {
+      cs.pchk[((size_t)mat * cs.nbp + min(bi, bj)) * cs.nbp + max(bi, bj)] = gr;
+    }
+  }
+  if (nrot == 0) return;
+  constexpr int KS = JC / 4;
+  const int cA = task_col<JB>(c, bi, bj, nb, n), cB = task_col<JB>(JB + c, bi, bj, nb, n);
+  double2 a[KS];
+  auto rows = [&](int r) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int col = task_col<JB>(4 * s + k, bi, bj, nb, n);
+      a[s] = ld_or0(d.g + (size_t)max(col, 0) * d.ldg, r, r < n && col >= 0);
+    }
+  };
+  rows(16 * wv + c);
+  for (int r0 = 16 * wv; r0 < n; r0 += 64) {
+    dx4 re0 = {0, 0, 0, 0}, im0 = re0, re1 = re0, im1 = re0;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const double2 b0 = Js[4 * s + k][c], b1 = Js[4 * s + k][JB + c];
+      re0 = mfma_f64(a[s].x, b0.x, re0);
+      re0 = mfma_f64(-a[s].y, b0.y, re0);
+      im0 = mfma_f64(a[s].x, b0.y, im0);
+      im0 = mfma_f64(a[s].y, b0.x, im0);
+      re1 = mfma_f64(a[s].x, b1.x, re1);
+      re1 = mfma_f64(-a[s].y, b1.y, re1);
+      im1 = mfma_f64(a[s].x, b1.y, im1);
+      im1 = mfma_f64(a[s].y, b1.x, im1);
+      if (s % 2) __builtin_amdgcn_sched_barrier(0);   // all of J's fragments fetched ahead spill
+    }
+    rows(r0 + 64 + c);   // the next rows are on their way while these are stored
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = r0 + k + 4 * v;
+      if (row < n) {
+        if (cA >= 0) d.g[(size_t)cA * d.ldg + row] = cz(re0[v], im0[v]);
+        if (cB >= 0) d.g[(size_t)cB * d.ldg + row] = cz(re1[v], im1[v]);
+      }
+    }
+  }
 }
 
 // 1''. partial Gram matrix for 32-column blocks (64 task columns, four
@@ -680,9 +812,21 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
   DevBuf act((size_t)nmat * sizeof(int));
   const int npair_max = std::max(1, nbpmax / 2);
   const int ntile_max = cdiv(nmax, GT), atile_max = cdiv(nmax, AT);
-  DevBuf hpart((size_t)nmat * npair_max * ntile_max * JC * JC * sizeof(double2));
-  DevBuf jbuf((size_t)nmat * npair_max * JC * JC * sizeof(double2));
-  DevBuf rotf((size_t)nmat * npair_max * sizeof(int));
+  // A workgroup a task and one launch a round, unless a round's few workgroups
+  // would take long runs of rows each: passes of 2 matrices of 1000 columns (63
+  // tasks) 101 ms in one launch and 83 in three, 9 of 1000 143 and 137, 5 of 2000
+  // 564 and 512; 9 of 200 9.5 and 10.4, 65 of 550 (1105 tasks) 106 and 116.
+  // MFS_JAC_ROUND=1 or 0 decides.
+  long ntask = 0;
+  for (const auto &d : h) ntask += cdiv(d.n, 2 * JB);
+  const char *jr = getenv("MFS_JAC_ROUND");
+  const bool one = JB == 16 && (jr ? atoi(jr) != 0 : nmax <= 512 || ntask >= 1024);
+  DevBuf hpart, jbuf, rotf;
+  if (!one) {
+    hpart.alloc((size_t)nmat * npair_max * ntile_max * JC * JC * sizeof(double2));
+    jbuf.alloc((size_t)nmat * npair_max * JC * JC * sizeof(double2));
+    rotf.alloc((size_t)nmat * npair_max * sizeof(int));
+  }
   const size_t ncl = (size_t)nmat * nbpmax * (nbpmax + 1);
   DevBuf cleanbuf((ncl + nmat) * sizeof(int));
   JacClean cs{cleanbuf.as<int>(), cleanbuf.as<int>() + (size_t)nmat * nbpmax, cleanbuf.as<int>() + ncl, nbpmax};
@@ -703,6 +847,11 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
     hipLaunchKernelGGL(jac_clear_checks, dim3(cdiv(nmat, 256)), dim3(256), 0, s, cs, nmat);
     HIP_CHECK(hipEventRecord(e0, s));
     for (int rnd = 0; rnd < rounds; ++rnd) {
+      if (one) {
+        hipLaunchKernelGGL(jac_round_kernel, dim3(npair_max, nmat), dim3(256), 0, s, descs, act.as<int>(), rnd, tol, cs,
+                           sweep * rounds + rnd);
+        continue;
+      }
       if (JB == 16)
         hipLaunchKernelGGL(jac_gram_mfma_kernel, dim3(ntile_max, npair_max, nmat), dim3(64), 0, s, descs,
                            act.as<int>(), rnd, hpart.as<double2>(), npair_max, ntile_max, cs);
@@ -727,7 +876,7 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
     float ms = 0.f;
     HIP_CHECK(hipEventElapsedTime(&ms, e0, e1));
     st.ms += ms;
-    st.launches += 3 * rounds;
+    st.launches += (one ? 1 : 3) * rounds;
     // algorithmic work: every checked task (a pair not known converged) reads
     // its columns of G and forms the Hermitian Gram matrix; a task that
     // rotated writes them back, times the c x c rotation product

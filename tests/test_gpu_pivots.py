@@ -43,3 +43,22 @@ def test_singular_values_at_edges(mfs, M, N):
         print(f"[pivots {M} x {N}] mode {n}: rank {ranks[n]}, singular values {e:.1e}", flush=True)
         assert abs(int(ranks[n]) - int(np.sum(s > 1e-10 * s[0]))) <= 1
         assert e < tol
+
+
+@pytest.mark.parametrize("M,N,P", [(48, 40, 4), (36, 17, 4), (210, 200, 16), (620, 600, 4)])
+def test_jacobi_rounds_in_one_launch_match_three(mfs, monkeypatch, M, N, P):
+    """A round of the blocked Jacobi in one launch and in three: the same kept
+    ranks, singular values within 1e-13 of the largest or N eps (both converge
+    to the same relative orthogonality)."""
+    b = W.small_periodic().body
+    ctx = mfs.create(0)
+    got = []
+    for form in ("1", "0"):
+        monkeypatch.setenv("MFS_JAC_ROUND", form)
+        op = mfs.build_operator(ctx, [mfs.BodySpec(M, N, P, 64, b.k, mfs.polar_geometry(
+            b.shape.a, b.shape.eps, b.shape.j, M, N, b.tau, b.colloc))])
+        got.append((np.array(op.factor_modes(1e-10)), op.singular_values(0)))
+    (r1, s1), (r3, s3) = got
+    e = max(float(np.max(np.abs(a - c)) / c[0]) for a, c in zip(s1, s3))
+    print(f"[jacobi rounds {M} x {N}] {e:.1e}", flush=True)
+    assert (r1 == r3).all() and e < max(1e-13, N * np.finfo(float).eps)
