@@ -62,3 +62,22 @@ def test_jacobi_rounds_in_one_launch_match_three(mfs, monkeypatch, M, N, P):
     e = max(float(np.max(np.abs(a - c)) / c[0]) for a, c in zip(s1, s3))
     print(f"[jacobi rounds {M} x {N}] {e:.1e}", flush=True)
     assert (r1 == r3).all() and e < max(1e-13, N * np.finfo(float).eps)
+
+
+def test_jacobi_streams_give_the_same_bits(mfs, monkeypatch):
+    """Matrices of three bodies' modes in one group or in four, each group's
+    rounds on its own stream: every matrix runs its own rounds, so the singular
+    values and ranks are the same bits."""
+    b = W.small_periodic().body
+    ctx = mfs.create(0)
+    specs = [mfs.BodySpec(M, N, P, 64, b.k, mfs.polar_geometry(b.shape.a, b.shape.eps, b.shape.j, M, N, b.tau, b.colloc))
+             for M, N, P in ((48, 40, 16), (120, 100, 8), (36, 17, 4))]
+    got = []
+    for ns in ("1", "4"):
+        monkeypatch.setenv("MFS_JAC_STREAMS", ns)
+        op = mfs.build_operator(ctx, specs)
+        got.append((np.array(op.factor_modes(1e-10)), [op.singular_values(i) for i in range(3)]))
+    (r1, s1), (r4, s4) = got
+    assert (r1 == r4).all()
+    for x, y in zip(s1, s4):
+        assert all((np.asarray(u) == np.asarray(v)).all() for u, v in zip(x, y))
