@@ -168,6 +168,13 @@ __device__ inline int jac_inner_sweep(double2 (*Hs)[2 * JB + 1], double2 (*Js)[2
   constexpr int JC = 2 * JB;
   const int tid = threadIdx.x, bi = tid / JB, bj = tid % JB, k = 2 * bi;
   int nrot = 0;
+  {
+    // no pair of the task to turn (two tasks in five of a whole run): H stays as
+    // it is, and the rounds would find the same
+    auto turns = [&](int p, int q) { return cabs2(Hs[p][q]) > tol2 * Hs[p][p].x * Hs[q][q].x; };
+    const bool any = turns(bi, JB + bj) || (bi < bj && (turns(bi, bj) || turns(JB + bi, JB + bj)));
+    if (!__syncthreads_or(any)) return 0;
+  }
   for (int rnd = 0; rnd < JC - 1; ++rnd) {
     int p, q, u, v;
     inner_pair<JB>(rnd, bi, p, q);
@@ -471,11 +478,11 @@ __global__ __launch_bounds__(256, 4) void jac_round_kernel(const MatDesc *__rest
       }
 #pragma unroll
       for (int s = 0; s < KB; ++s) {
-        // conj(x_I)^T x_J: real part xr^T xr + xi^T xi, imaginary xr^T xi - xi^T xr
+        // conj(x_I)^T x_J: real part xr^T xr + xi^T xi, imaginary xr^T xi - xi^T xr;
+        // for I = J the second is the transpose of the first, taken off below
         r00 = mfma_f64(x0[s].x, x0[s].x, r00);
         r00 = mfma_f64(x0[s].y, x0[s].y, r00);
         i00 = mfma_f64(x0[s].x, x0[s].y, i00);
-        i00 = mfma_f64(-x0[s].y, x0[s].x, i00);
         r01 = mfma_f64(x0[s].x, x1[s].x, r01);
         r01 = mfma_f64(x0[s].y, x1[s].y, r01);
         i01 = mfma_f64(x0[s].x, x1[s].y, i01);
@@ -483,7 +490,6 @@ __global__ __launch_bounds__(256, 4) void jac_round_kernel(const MatDesc *__rest
         r11 = mfma_f64(x1[s].x, x1[s].x, r11);
         r11 = mfma_f64(x1[s].y, x1[s].y, r11);
         i11 = mfma_f64(x1[s].x, x1[s].y, i11);
-        i11 = mfma_f64(-x1[s].y, x1[s].x, i11);
       }
     }
     // the waves in turn (every lane owns its entries)
@@ -504,6 +510,15 @@ __global__ __launch_bounds__(256, 4) void jac_round_kernel(const MatDesc *__rest
   {
     const int i = tid / JB, j = tid % JB;
     Hs[JB + j][i] = cconj(Hs[i][JB + j]);
+    if (i <= j) {
+#pragma unroll
+      for (int o = 0; o < JC; o += JB) {
+        const double2 u = Hs[o + i][o + j], l = Hs[o + j][o + i];
+        const double im = u.y - l.y;
+        Hs[o + i][o + j] = cz(u.x, im);
+        Hs[o + j][o + i] = cz(u.x, -im);
+      }
+    }
   }
   for (int idx = tid; idx < JC * JC; idx += 256) Js[idx / JC][idx % JC] = cz(idx / JC == idx % JC ? 1.0 : 0.0, 0.0);
   __syncthreads();
