@@ -159,6 +159,39 @@ __device__ inline void lane_column_sums(double2 (&v)[NB], int lane) {
   butterfly_stages<NB / 2, NB>(v, lane);
 }
 
+// v_permlane32_swap / v_permlane16_swap and an add: the sums of a's two halves
+// (rows 2 i, 2 i + 1 of 16 lanes) in the lower lanes, of b's in the upper
+__device__ inline double swap32_add(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+}
+__device__ inline double swap16_add(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+}
+// lane l's value (l uniform) to all lanes
+__device__ inline double lane_value(double v, int l) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), l), hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+  return __hiloint2double(hi, lo);
+}
+// the largest value of the wave, in every lane
+__device__ inline double wave_max_dpp(double v) {
+  v = fmax(v, dpp_move<0xb1, 0xf>(v));
+  v = fmax(v, dpp_move<0x4e, 0xf>(v));
+  v = fmax(v, dpp_move<0x141, 0xf>(v));
+  v = fmax(v, dpp_move<0x140, 0xf>(v));
+  {
+    const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = fmax(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
+  }
+  const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return fmax(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
+}
+
 constexpr int QHR = 128;   // rows a workgroup in the reflector apply
 
 __device__ inline double wave_sum(double v) {

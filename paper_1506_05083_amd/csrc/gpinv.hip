@@ -378,137 +378,169 @@ __global__ __launch_bounds__(256) void qrcp_update_kernel(const MatDesc *__restr
   if (lane == 0) norms[(size_t)blockIdx.y * ld + c] = sqrt(s);
 }
 
-// The whole column-pivoted QR of a triangle of at most QN columns in one
-// launch, one workgroup a matrix: norms, the pivot column and the pivot record
-// in LDS, the triangle in place (from L2), a wave a column with the column's
-// rows in registers between its product with the reflector and its update, two
-// columns a wave in flight.  The steps of the two kernels above without their
-// 2 n launches: bound by the step's chain (argmax, swap, reflector, the
-// columns' round trip to L2).  17 triangles of 60 columns: 0.23 ms, the
-// scattering pass around it 3.17 -> 2.87 ms.
-constexpr int QN = 256, QT = 1024;
-__global__ __launch_bounds__(QT) void qrcp_one_kernel(const MatDesc *__restrict__ descs, int *__restrict__ piv,
-                                                      int ld) {
-  constexpr int NW = QT / 64, RL = QN / 64;
-  const MatDesc d = descs[blockIdx.x];
-  const int n = d.n, m = d.m, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  int *pv = piv + (size_t)blockIdx.x * ld;
-  __shared__ double nr[QN];
-  __shared__ double2 v[QN];
-  __shared__ double rv[NW];
-  __shared__ int ri[NW];
-  __shared__ double red[NW];
-  for (int c = wv; c < n; c += NW) {
-    double s = 0.0;
-    for (int r = lane; r < m; r += 64) s += cabs2(d.a[(size_t)c * d.lda + r]);
-    s = wave_sum(s);
-    if (lane == 0) nr[c] = s;
+// The whole column-pivoted QR of a triangle of at most 64 RL rows and 16 CW
+// columns in one launch, one workgroup a matrix, the triangle in registers:
+// wave w holds the columns w, w + 16, ..., a lane a row of each 64.  Nothing is
+// swapped: the chosen column's wave forms its reflector, writes the finished
+// column where it belongs and drops it; the others read the reflector from LDS.
+// A step is two barriers: every wave finds the largest norm by itself (the
+// column's index in the last bits, so equal norms to 2^-45 go to the lowest
+// index), the chosen column's wave forms the reflector; all apply it and
+// recompute their norms, the sums of all a wave's columns in one butterfly.
+// Bound by that chain: 17 triangles of 60 columns 102 us, of 120 309 us; with the
+// triangle in L2 and the columns swapped 234 and 588 us.
+constexpr int QN = 128, QW = 16;
+
+// Sums over the wave of N values (N = 4, 8 or 16): on return lane 4 i holds the
+// sum of v[i] in v[0] (so do lanes 4 i + 1 .. 4 i + 3, to rounding).
+template <int N>
+__device__ inline void wave_sums(double (&v)[N], int lane) {
+  if constexpr (N == 16) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = swap32_add(v[i], v[i + 8]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = swap32_add(v[i], v[i]);
   }
+  if constexpr (N >= 8) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = swap16_add(v[i], v[i + 4]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = swap16_add(v[i], v[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const bool hi = lane & 8;
+    const double send = hi ? v[i] : v[i + 2], keep = hi ? v[i + 2] : v[i];
+    v[i] = keep + dpp_move<0x128, 0xf>(send);   // row_ror 8
+  }
+  const bool hi = lane & 4;
+  const double send = hi ? v[0] : v[1], keep = hi ? v[1] : v[0];
+  double t = keep + dpp_move<0x141, 0xf>(send);   // row_half_mirror
+  t += dpp_move<0x4e, 0xf>(t);                    // quad_perm 2 3 0 1
+  v[0] = t + dpp_move<0xb1, 0xf>(t);              // quad_perm 1 0 3 2
+}
+
+template <int RL, int CW>
+__global__ __launch_bounds__(64 * QW) void qrcp_one_kernel(const MatDesc *__restrict__ descs, int *__restrict__ piv,
+                                                           int ld) {
+  const MatDesc d = descs[blockIdx.x];
+  const int n = d.n, m = d.m, tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int *pv = piv + (size_t)blockIdx.x * ld;
+  __shared__ double nr[QW * CW];
+  __shared__ int lab[QW * CW];
+  __shared__ double2 v[64 * RL];
+  __shared__ double2 s_tau;
+  double2 a[CW][RL];
+  unsigned live = 0;
+#pragma unroll
+  for (int j = 0; j < CW; ++j) {
+    const int c = QW * j + wv;
+    live |= c < n ? 1u << j : 0u;
+#pragma unroll
+    for (int u = 0; u < RL; ++u)
+      a[j][u] = ld_or0(d.a + (size_t)min(c, n - 1) * d.lda, 64 * u + lane, c < n && 64 * u + lane < m);
+  }
+  if (tid < QW * CW) lab[tid] = tid < n ? pv[tid] : 0;
+  // norms of the rows from k0 on
+  auto norms = [&](int k0) {
+    double q[CW < 4 ? 4 : CW];
+#pragma unroll
+    for (int j = 0; j < (CW < 4 ? 4 : CW); ++j) {
+      q[j] = 0.0;
+      if (j < CW)
+#pragma unroll
+        for (int u = 0; u < RL; ++u) q[j] += 64 * u + lane >= k0 ? cabs2(a[j < CW ? j : 0][u]) : 0.0;
+    }
+    wave_sums(q, lane);
+    const int j = lane >> 2;
+    // a NaN stays in the race, an infinity stays a number with an index in it
+    if ((lane & 3) == 0 && j < CW) nr[QW * j + wv] = (live >> j) & 1 ? (q[0] >= 0.0 ? fmin(q[0], 1.7e308) : 0.0) : -1.0;
+  };
+  norms(0);
   __syncthreads();
   for (int k = 0; k < n; ++k) {
+    // the largest norm's column
     double best = -1.0;
-    int bi = k;
-    for (int c = k + tid; c < n; c += QT) {
+#pragma unroll
+    for (int c = lane; c < QW * CW; c += 64) {
       const double x = nr[c];
-      if (x > best) { best = x; bi = c; }
+      const long long b = (__double_as_longlong(x) & ~127LL) | (127 - c);
+      best = x >= 0.0 ? fmax(best, __longlong_as_double(b)) : best;
     }
-    if (wv * 64 + k < n) {   // waves without a column have nothing to compare
+    best = wave_max_dpp(best);
+    const int p = __builtin_amdgcn_readfirstlane(127 - ((int)__double_as_longlong(best) & 127));
+    if (wv == p % QW) {   // uniform
+      double2 x[RL];
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const double ov = __shfl_xor(best, o, 64);
-        const int oi = __shfl_xor(bi, o, 64);
-        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+      for (int j = 0; j < CW; ++j)
+        if (j == p / QW)
+#pragma unroll
+          for (int u = 0; u < RL; ++u) x[u] = a[j][u];
+      live &= ~(1u << (p / QW));
+      double q = 0.0;
+      double2 alpha = cz(0.0, 0.0);
+#pragma unroll
+      for (int u = 0; u < RL; ++u) {
+        q += 64 * u + lane > k ? cabs2(x[u]) : 0.0;
+        if (u == k / 64) alpha = x[u];
       }
-    }
-    if (lane == 0) { rv[wv] = best; ri[wv] = bi; }
-    __syncthreads();
-    best = rv[0];
-    int p = ri[0];
-    for (int w = 1; w < NW; ++w)
-      if (rv[w] > best || (rv[w] == best && ri[w] < p)) { best = rv[w]; p = ri[w]; }
-    double2 *ck = d.a + (size_t)k * d.lda, *cp = d.a + (size_t)p * d.lda;
-    if (tid < m) {
-      const double2 t = cp[tid];
-      if (p != k) cp[tid] = ck[tid];
-      v[tid] = t;
-    }
-    const double q = wave_sum(tid > k && tid < m ? cabs2(v[tid]) : 0.0);   // a thread reads its own entry
-    if (lane == 0) red[wv] = q;
-    __syncthreads();
-    if (tid == 0 && p != k) {
-      nr[p] = nr[k];
-      const int ti = pv[k];
-      pv[k] = pv[p];
-      pv[p] = ti;
-    }
-    double ssum = 0.0;
-#pragma unroll
-    for (int w = 0; w < QN / 64; ++w) ssum += red[w];   // rows past QN do not exist
-    const double2 alpha = v[k];
-    double2 tau = cz(0.0, 0.0), scal = cz(1.0, 0.0);
-    double2 diag = alpha;
-    if (!(ssum == 0.0 && alpha.y == 0.0)) {
-      const double beta = -copysign(sqrt(alpha.x * alpha.x + alpha.y * alpha.y + ssum), alpha.x);
-      tau = cz((beta - alpha.x) / beta, -alpha.y / beta);
-      const double2 den = cz(alpha.x - beta, alpha.y);
-      const double dd = cabs2(den);
-      scal = cz(den.x / dd, -den.y / dd);
-      diag = cz(beta, 0.0);
-    }
-    __syncthreads();   // every thread has read v[k]
-    if (tid < m) {
-      double2 t = v[tid];
-      if (tid > k) t = cmul(t, scal);
-      ck[tid] = tid == k ? diag : t;
-      v[tid] = tid < k ? cz(0.0, 0.0) : (tid == k ? cz(1.0, 0.0) : t);
-    }
-    if (tid == 0) d.tau[k] = tau;
-    __syncthreads();
-    const double2 ctau = cconj(tau);
-    const int rb = k / 64;   // first 64-row block the reflector touches
-    for (int c = k + 1 + 2 * wv; c < n; c += 2 * NW) {
-      const bool two = c + 1 < n;
-      double2 *a0 = d.a + (size_t)c * d.lda, *a1 = d.a + (size_t)(two ? c + 1 : c) * d.lda;
-      double2 x0[RL], x1[RL], d0 = cz(0.0, 0.0), d1 = d0;
+      q = wave_sum(q);
+      alpha = cz(lane_value(alpha.x, k & 63), lane_value(alpha.y, k & 63));
+      double2 tau = cz(0.0, 0.0), scal = cz(1.0, 0.0), diag = alpha;
+      if (!(q == 0.0 && alpha.y == 0.0)) {
+        const double beta = -copysign(sqrt(alpha.x * alpha.x + alpha.y * alpha.y + q), alpha.x);
+        tau = cz((beta - alpha.x) / beta, -alpha.y / beta);
+        const double2 den = cz(alpha.x - beta, alpha.y);
+        const double dd = cabs2(den);
+        scal = cz(den.x / dd, -den.y / dd);
+        diag = cz(beta, 0.0);
+      }
+      double2 *ck = d.a + (size_t)k * d.lda;
 #pragma unroll
       for (int u = 0; u < RL; ++u) {
         const int r = 64 * u + lane;
-        const bool in = u >= rb && r < m;
-        x0[u] = ld_or0(a0, r, in);
-        x1[u] = ld_or0(a1, r, in);
+        const double2 t = cmul(x[u], scal);
+        v[r] = csel(r > k, t, cz(r == k ? 1.0 : 0.0, 0.0));
+        if (r < m) ck[r] = csel(r > k, t, csel(r == k, diag, x[u]));
       }
-#pragma unroll
-      for (int u = 0; u < RL; ++u)
-        if (u >= rb && 64 * u < m) {
-          const double2 vr = 64 * u + lane < m ? v[64 * u + lane] : cz(0.0, 0.0);
-          cfmac(d0, vr, x0[u]);
-          cfmac(d1, vr, x1[u]);
-        }
-      const double2 f0 = cmul(ctau, wave_sum(d0)), f1 = cmul(ctau, wave_sum(d1));
-      double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-      for (int u = 0; u < RL; ++u)
-        if (u >= rb && 64 * u < m) {
-          const int r = 64 * u + lane;
-          if (r < m && r >= k) {
-            const double2 vr = v[r];
-            const double2 y0 = csub(x0[u], cmul(vr, f0)), y1 = csub(x1[u], cmul(vr, f1));
-            a0[r] = y0;
-            if (two) a1[r] = y1;
-            if (r > k) {
-              s0 += cabs2(y0);
-              s1 += cabs2(y1);
-            }
-          }
-        }
-      s0 = wave_sum(s0);
-      s1 = wave_sum(s1);
       if (lane == 0) {
-        nr[c] = s0;
-        if (two) nr[c + 1] = s1;
+        s_tau = tau;
+        d.tau[k] = tau;
+        pv[k] = lab[p];
       }
     }
-    __syncthreads();   // norms and columns settled before the next step
+    __syncthreads();
+    if (live) {   // uniform
+      const double2 ctau = cconj(s_tau);
+      double2 vr[RL], vt[RL];
+#pragma unroll
+      for (int u = 0; u < RL; ++u) {
+        vr[u] = v[64 * u + lane];
+        vt[u] = cmul(ctau, vr[u]);
+        vt[u] = cz(-vt[u].x, -vt[u].y);
+      }
+      double s[2 * CW];
+#pragma unroll
+      for (int j = 0; j < CW; ++j) {
+        double2 t = cz(0.0, 0.0);
+#pragma unroll
+        for (int u = 0; u < RL; ++u) cfmac(t, vr[u], a[j][u]);
+        s[2 * j] = t.x;
+        s[2 * j + 1] = t.y;
+      }
+      wave_sums(s, lane);
+#pragma unroll
+      for (int j = 0; j < CW; ++j) {
+        const double2 f = cz(lane_value(s[0], 8 * j), lane_value(s[0], 8 * j + 4));
+#pragma unroll
+        for (int u = 0; u < RL; ++u) cfma(a[j][u], vt[u], f);
+      }
+    }
+    norms(k + 1);
+    __syncthreads();   // norms settled, the reflector's slots free
   }
 }
 
@@ -1204,16 +1236,22 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     // (qrcp_sketch.hip): A is read once per block, not per column (the
     // large periodizer's 8 triangles of 10805 columns: 7.3 -> 3.0 s per
     // incidence; the 256-obstacle batch's triangles: truncation 10.3 ->
-    // 8.8 s).  Small batches of triangles narrower than 256 columns (the k = 10
-    // body's 33 of 200) take one launch with a workgroup a matrix
-    // (qrcp_one_kernel).  MFS_QRCP=sketched, blocked (the deterministic panel
+    // 8.8 s).  Triangles that fit a workgroup's registers take one launch with
+    // a workgroup a matrix (qrcp_one_kernel: a penetrable body's 17 of 120
+    // columns 3.7 ms a pass and 4.3 sketched; the k = 10 body's 33 of 200 were
+    // 1.0 ms faster sketched than in one launch from L2).  MFS_QRCP=sketched, blocked (the deterministic panel
     // form: panels of 32, updates deferred, norms downdated, qrcp.hip) or
     // unblocked (two launches a column over the whole chip) decides.
     const char *qe = std::getenv("MFS_QRCP");
-    const bool big = n2max >= 256 || (size_t)W * n2max * n2max >= ((size_t)1 << 24);
+    const bool big = n2max > QN || (size_t)W * n2max * n2max >= ((size_t)1 << 24);
     const std::string form = qe ? std::string(qe) : (big ? "sketched" : "one");
     if (form == "one" && n2max <= QN) {
-      hipLaunchKernelGGL(qrcp_one_kernel, dim3(W), dim3(QT), 0, s, g.d_rq.as<MatDesc>(), g.piv.as<int>(), nmax);
+      if (n2max <= 64)
+        hipLaunchKernelGGL((qrcp_one_kernel<1, 4>), dim3(W), dim3(64 * QW), 0, s, g.d_rq.as<MatDesc>(),
+                           g.piv.as<int>(), nmax);
+      else
+        hipLaunchKernelGGL((qrcp_one_kernel<2, 8>), dim3(W), dim3(64 * QW), 0, s, g.d_rq.as<MatDesc>(),
+                           g.piv.as<int>(), nmax);
     } else if (form == "sketched") {
       qrcp_sketched(g.d_rq.as<MatDesc>(), g.h_rq, g.piv.as<int>(), nmax, s);
     } else if (form != "blocked") {

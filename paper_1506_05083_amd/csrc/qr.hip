@@ -245,12 +245,8 @@ __device__ inline double2 row_lane(double2 v) {
 }
 // sum over the wave's four rows of 16 lanes, the same bits in all of them
 __device__ inline double sum_rows16(double v) {
-  auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
-  auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
-  v = __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
-  l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
-  h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
-  return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+  v = swap16_add(v, v);
+  return swap32_add(v, v);
 }
 
 struct PanelShared {
