@@ -176,11 +176,11 @@ const char *mfs_version(void);
 mfs_status mfs_create(int device, mfs_ctx **out);
 void mfs_destroy(mfs_ctx *ctx);
 
-/* Device memory of the library.  Every device buffer of 1 MiB or more that
- * the library allocates comes from a per-device cache: a released buffer is
- * kept (after the device has finished the work queued before its release)
- * and handed to the next request of about its size, so repeated solves do
- * not return tens of GB to the driver and ask for them again.  At most half
+/* Device memory of the library.  Every device buffer that the library
+ * allocates comes from a per-device cache: a released buffer is kept and,
+ * once the device has finished the work queued before its release, handed to
+ * the next request of about its size, so repeated solves do not return tens
+ * of GB to the driver and ask for them again.  At most half
  * of the device's memory is kept idle; a failed allocation first frees the
  * idle blocks and retries.
  *   mfs_memory_stats: bytes held by live library buffers (in_use), their

@@ -603,6 +603,7 @@ mfs_status mfs_apply_solution_op(const mfs_op *op, int32_t body, int32_t nrhs, c
   apply_solution_layouts(op, b, nrhs, reinterpret_cast<const double2 *>(in), in_layout,
                          reinterpret_cast<double2 *>(out), out_layout, im.as<double2>(), om.as<double2>(), nullptr,
                          s);
+  if (im.p || om.p) HIP_CHECK(hipStreamSynchronize(s));   // released here: an error under graph capture
   MFS_API_END
 }
 

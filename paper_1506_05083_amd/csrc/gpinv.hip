@@ -1142,7 +1142,6 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     d.tau = p; p += n;
     d.T = p; p += (size_t)npan * nbq * nbq;
     d.u = p;
-    d.flag = flags + 2 * W + w;   // unused by QR; kept distinct
     d.rank = flags + W + w;       // shared with the Jacobi descriptor (kept rank)
     g.h_qc[w] = d;
   }
@@ -1222,7 +1221,6 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
       d.a = arena_at(g.rq_a, oa[w]); d.m = n; d.n = n; d.lda = ldr;
       d.tau = p; p += n;
       d.T = p;
-      d.flag = flags + 3 * W + w;
       d.rank = flags + W + w;
       g.h_rq[w] = d;
     }
@@ -1345,7 +1343,6 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     double *rp = reinterpret_cast<double *>(p);
     d.sv = rp;
     d.perm = reinterpret_cast<int *>(rp + n);
-    d.flag = flags + w;
     d.rank = flags + W + w;
     g.h_lq[w] = d;
   }

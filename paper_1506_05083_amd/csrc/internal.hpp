@@ -18,7 +18,7 @@ struct DevBuf {
   void *p = nullptr;
   size_t bytes = 0;
   int dev = 0;
-  size_t cached = 0;   // size of the cached block behind p (0: plain hipMalloc)
+  size_t cached = 0;   // size of the block behind p
   DevBuf() = default;
   explicit DevBuf(size_t n) { alloc(n); }
   ~DevBuf() { release(); }
@@ -38,6 +38,17 @@ struct DevBuf {
   void alloc(size_t n);
   void release();
   template <class T> T *as() const { return static_cast<T *>(p); }
+};
+// Pinned host memory (hipHostMalloc), from a small cache of 64 KiB blocks where
+// that holds it.  Nothing queued may still use it when it is destroyed, except
+// while an error unwinds (then it is not reused).
+struct PinnedBuf {
+  void *p = nullptr;
+  size_t bytes;
+  explicit PinnedBuf(size_t n);
+  ~PinnedBuf();
+  PinnedBuf(const PinnedBuf &) = delete;
+  PinnedBuf &operator=(const PinnedBuf &) = delete;
 };
 // Idle bytes held by the cache of device dev; free them all (pool_trim).
 size_t pool_idle_bytes(int dev);
@@ -62,7 +73,6 @@ struct MatDesc {
   double *sv;     // [n] singular values, descending
   int *perm;      // [n] work
   int *rank;      // [1] kept rank
-  int *flag;      // [1] Jacobi sweep activity flag
   int ldu;        // leading dimension of u (0: lda)
 };
 
@@ -86,7 +96,7 @@ struct BodyData {
   std::vector<double> h_rho, h_z, h_nrho, h_nz, h_srho, h_sz, h_srho2, h_sz2;
   bool trans() const { return km > 0.0; }
   DevBuf blocks;      // [nd][cols][ldA]
-  DevBuf fac;         // tau, T, g, v, u, w, sv, perm, rank, flag for all nd blocks
+  DevBuf fac;         // tau, T, g, v, u, w, sv, perm, rank for all nd blocks
   DevBuf descs;       // MatDesc[nd] on device
   std::vector<MatDesc> h_descs;
   std::vector<int> rank;

@@ -443,7 +443,7 @@ std::shared_ptr<NearLowRank> build_near_lowrank(const BodyData &b, const NsumPla
       MatDesc d{};
       d.a = Y.as<double2>(); d.m = T; d.n = ell; d.lda = ldy;
       d.tau = tau.as<double2>(); d.T = Tf.as<double2>();
-      d.rank = flags.as<int>(); d.flag = flags.as<int>() + 1;
+      d.rank = flags.as<int>();
       std::vector<MatDesc> hd{d};
       DevBuf dd(sizeof(MatDesc));
       HIP_CHECK(hipMemcpyAsync(dd.p, &hd[0], sizeof(MatDesc), hipMemcpyHostToDevice, s));

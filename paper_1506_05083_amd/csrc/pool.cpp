@@ -5,17 +5,24 @@
 // benchmark repeats that many times.  Returning such blocks to the driver
 // and asking for them again costs far more than the work itself on some
 // steps (the driver clears and maps freed device memory before it hands it
-// out again), so every buffer of at least kPoolMin bytes goes through a
-// per-device cache: a released block is kept and handed to the next request
-// of about its size.  Smaller buffers go straight to hipMalloc / hipFree.
+// out again), so every buffer goes through a per-device cache: a released block
+// is kept and handed to the next request of about its size (blocks under
+// kPoolMin by powers of two: hipMalloc and hipFree of the 65 of a free-space
+// scattering pass were 0.6 ms of its 2.3).
 //
 // Ordering.  hipFree waits for the device to finish the work queued before
 // it, which is what makes releasing a buffer that a queued kernel still
-// reads safe.  A cached block keeps that rule: its release synchronises the
-// device before the block becomes available again, so a later request on
-// any stream never sees it while earlier work still uses it.
+// reads safe.  A cached block keeps that rule: a released block becomes
+// available again only after a synchronisation of the device that began after
+// its release, so a later request on any stream never sees it while earlier
+// work still uses it.  The released blocks wait together for one such
+// synchronisation, made when a request finds none available but some waiting
+// (a synchronisation at every release kept the host from running ahead: 75
+// of them in the k = 10 step from the geometry on).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <exception>
 #include <map>
 #include <mutex>
 #include <string>
@@ -27,13 +34,39 @@ namespace mfs {
 
 namespace {
 
-constexpr size_t kPoolMin = (size_t)1 << 20;     // smaller blocks are not cached
-constexpr size_t kPoolGrain = (size_t)2 << 20;   // cached sizes are multiples of this
+constexpr size_t kPoolMin = (size_t)1 << 20;     // smaller blocks are cached by powers of two
+constexpr size_t kPoolGrain = (size_t)2 << 20;   // sizes of the others are multiples of this
+
+constexpr int kSmallClasses = 12;                // 512 bytes << class: up to kPoolMin
+constexpr size_t kSmallCap = (size_t)64 << 20;   // idle small blocks kept at most
+
+int small_class(size_t n) {
+  int c = 0;
+  while (((size_t)512 << c) < n) ++c;
+  return c;
+}
+// small blocks of a class that wait before a request synchronises for them
+// (below that it allocates another)
+size_t small_wait(int c) { return ((size_t)512 << c) <= ((size_t)64 << 10) ? 32 : 8; }
+
+struct Blocks {
+  std::multimap<size_t, void *> large;   // size -> block
+  std::vector<void *> small[kSmallClasses];
+  void take(Blocks &o) {   // o's blocks too
+    large.insert(o.large.begin(), o.large.end());
+    o.large.clear();
+    for (int c = 0; c < kSmallClasses; ++c) {
+      small[c].insert(small[c].end(), o.small[c].begin(), o.small[c].end());
+      o.small[c].clear();
+    }
+  }
+};
 
 struct Pool {
   std::mutex mu;
-  std::multimap<size_t, void *> idle;   // size -> block, not in use
-  size_t idle_bytes = 0;
+  Blocks ready, waiting;                // not in use: available, released since the last synchronisation
+  size_t idle_bytes = 0;                // of the large blocks of both
+  size_t small_bytes = 0;               // of the small ones
   size_t cap = 0;                       // largest idle total kept (0: not yet read)
   size_t in_use = 0, peak = 0;          // bytes of live DevBufs (cached blocks at their block size)
 };
@@ -60,15 +93,55 @@ int current_device() {
   return dev;
 }
 
-// Free idle blocks of p (largest first) until at most `keep` bytes stay idle.
-// Called with p.mu held.
+// Free idle large blocks of p (largest first) until at most `keep` bytes stay
+// idle; with keep = 0 the small ones too.  Called with p.mu held.
 void trim_locked(Pool &p, size_t keep) {
-  while (p.idle_bytes > keep && !p.idle.empty()) {
-    auto it = std::prev(p.idle.end());
-    (void)hipFree(it->second);
-    p.idle_bytes -= it->first;
-    p.idle.erase(it);
+  for (Blocks *b : {&p.ready, &p.waiting}) {
+    while (p.idle_bytes > keep && !b->large.empty()) {
+      auto it = std::prev(b->large.end());
+      (void)hipFree(it->second);
+      p.idle_bytes -= it->first;
+      b->large.erase(it);
+    }
+    if (keep == 0)
+      for (auto &v : b->small) {
+        for (void *q : v) (void)hipFree(q);
+        v.clear();
+      }
   }
+  if (keep == 0) p.small_bytes = 0;
+}
+
+// Make the waiting blocks available: the device (the current one) finishes what
+// was queued before their release.  lk holds p.mu, let go meanwhile.
+void recycle(Pool &p, std::unique_lock<std::mutex> &lk) {
+  Blocks b;
+  b.take(p.waiting);
+  lk.unlock();
+  const hipError_t e = hipDeviceSynchronize();
+  lk.lock();
+  (e == hipSuccess ? p.ready : p.waiting).take(b);
+  if (e != hipSuccess) (void)hipGetLastError();
+}
+
+// the smallest block that fits, if it wastes at most 1/8 of it
+std::multimap<size_t, void *>::iterator fit(std::multimap<size_t, void *> &m, size_t want) {
+  auto it = m.lower_bound(want);
+  return it != m.end() && it->first - want <= want / 8 ? it : m.end();
+}
+
+// hipMalloc; the idle blocks are given back and it is tried again if it fails
+void *device_malloc(Pool &pl, size_t n) {
+  void *q = nullptr;
+  if (hipMalloc(&q, n) == hipSuccess) return q;
+  (void)hipGetLastError();
+  {
+    std::lock_guard<std::mutex> lk(pl.mu);
+    trim_locked(pl, 0);
+  }
+  if (hipMalloc(&q, n) == hipSuccess) return q;
+  (void)hipGetLastError();
+  throw Error{MFS_ENOMEM, "hipMalloc of " + std::to_string(n) + " bytes failed"};
 }
 
 }  // namespace
@@ -78,90 +151,125 @@ void DevBuf::alloc(size_t n) {
   if (n == 0) return;
   dev = current_device();
   Pool &pl = pool_of(dev);
+  std::unique_lock<std::mutex> lk(pl.mu);
   if (n < kPoolMin) {
-    if (hipMalloc(&p, n) != hipSuccess) {
-      p = nullptr;
-      (void)hipGetLastError();
-      throw Error{MFS_ENOMEM, "hipMalloc of " + std::to_string(n) + " bytes failed"};
+    const int c = small_class(n);
+    auto &v = pl.ready.small[c];
+    if (v.empty() && pl.waiting.small[c].size() >= small_wait(c)) recycle(pl, lk);
+    const size_t size = (size_t)512 << c;
+    if (!v.empty()) {
+      p = v.back();
+      v.pop_back();
+      pl.small_bytes -= size;
+    } else {
+      lk.unlock();
+      p = device_malloc(pl, size);
+      lk.lock();
     }
+    cached = size;
     bytes = n;
-    cached = 0;
-    std::lock_guard<std::mutex> lk(pl.mu);
     note_alloc(pl, n);
     return;
   }
   const size_t want = (n + kPoolGrain - 1) / kPoolGrain * kPoolGrain;
-  {
-    std::lock_guard<std::mutex> lk(pl.mu);
-    // the smallest idle block that fits, if it wastes at most 1/8 of it
-    auto it = pl.idle.lower_bound(want);
-    if (it != pl.idle.end() && it->first - want <= want / 8) {
-      p = it->second;
-      cached = it->first;
-      pl.idle_bytes -= it->first;
-      pl.idle.erase(it);
-      bytes = n;
-      note_alloc(pl, cached);
-      return;
-    }
+  auto it = fit(pl.ready.large, want);
+  if (it == pl.ready.large.end() && fit(pl.waiting.large, want) != pl.waiting.large.end()) {
+    recycle(pl, lk);
+    it = fit(pl.ready.large, want);
   }
-  void *q = nullptr;
-  if (hipMalloc(&q, want) != hipSuccess) {
-    (void)hipGetLastError();
-    {
-      std::lock_guard<std::mutex> lk(pl.mu);
-      trim_locked(pl, 0);
-    }
-    if (hipMalloc(&q, want) != hipSuccess) {
-      (void)hipGetLastError();
-      throw Error{MFS_ENOMEM, "hipMalloc of " + std::to_string(want) + " bytes failed"};
-    }
+  if (it != pl.ready.large.end()) {
+    p = it->second;
+    cached = it->first;
+    pl.idle_bytes -= it->first;
+    pl.ready.large.erase(it);
+  } else {
+    lk.unlock();
+    p = device_malloc(pl, want);
+    lk.lock();
+    cached = want;
   }
-  p = q;
-  cached = want;
   bytes = n;
-  std::lock_guard<std::mutex> lk(pl.mu);
-  note_alloc(pl, want);
+  note_alloc(pl, cached);
 }
 
 void DevBuf::release() {
   if (!p) return;
-  if (!cached) {
-    (void)hipFree(p);
-    Pool &pl = pool_of(dev);
+  Pool &pl = pool_of(dev);
+  const bool small = cached < kPoolGrain;
+  int prev = 0;
+  (void)hipGetDevice(&prev);
+  if (prev != dev) (void)hipSetDevice(dev);
+  {
     std::lock_guard<std::mutex> lk(pl.mu);
-    pl.in_use -= bytes;
-  } else {
-    int prev = 0;
-    (void)hipGetDevice(&prev);
-    if (prev != dev) (void)hipSetDevice(dev);
-    // the rule hipFree keeps: nothing queued before this point may still
-    // be using the block when it is handed out again
-    (void)hipDeviceSynchronize();
-    Pool &pl = pool_of(dev);
-    {
-      std::lock_guard<std::mutex> lk(pl.mu);
+    pl.in_use -= small ? bytes : cached;
+    if (small) {
+      if (pl.small_bytes + cached > kSmallCap) {
+        (void)hipFree(p);
+      } else {
+        pl.waiting.small[small_class(cached)].push_back(p);
+        pl.small_bytes += cached;
+      }
+    } else {
       if (pl.cap == 0) {
         size_t fr = 0, tot = 0;
         (void)hipMemGetInfo(&fr, &tot);
         pl.cap = tot / 2;   // keep at most half of the device idle in the cache
       }
-      pl.idle.emplace(cached, p);
+      pl.waiting.large.emplace(cached, p);
       pl.idle_bytes += cached;
-      pl.in_use -= cached;
       trim_locked(pl, pl.cap);
     }
-    if (prev != dev) (void)hipSetDevice(prev);
   }
+  if (prev != dev) (void)hipSetDevice(prev);
   p = nullptr;
   bytes = 0;
   cached = 0;
 }
 
+namespace {
+constexpr size_t kPinned = (size_t)64 << 10;
+constexpr size_t kPinnedKept = 16;
+std::mutex g_pinned_mu;
+std::vector<void *> &pinned_idle() {
+  static auto *v = new std::vector<void *>;   // still valid while the process ends
+  return *v;
+}
+}  // namespace
+
+PinnedBuf::PinnedBuf(size_t n) : bytes(std::max(n, kPinned)) {
+  if (bytes == kPinned) {
+    std::lock_guard<std::mutex> lk(g_pinned_mu);
+    auto &v = pinned_idle();
+    if (!v.empty()) {
+      p = v.back();
+      v.pop_back();
+      return;
+    }
+  }
+  if (hipHostMalloc(&p, bytes, hipHostMallocPortable) != hipSuccess) {
+    p = nullptr;
+    (void)hipGetLastError();
+    throw Error{MFS_ENOMEM, "hipHostMalloc of " + std::to_string(bytes) + " bytes failed"};
+  }
+}
+
+PinnedBuf::~PinnedBuf() {
+  if (!p) return;
+  if (bytes == kPinned && std::uncaught_exceptions() == 0) {
+    std::lock_guard<std::mutex> lk(g_pinned_mu);
+    auto &v = pinned_idle();
+    if (v.size() < kPinnedKept) {
+      v.push_back(p);
+      return;
+    }
+  }
+  (void)hipHostFree(p);
+}
+
 size_t pool_idle_bytes(int dev) {
   Pool &pl = pool_of(dev);
   std::lock_guard<std::mutex> lk(pl.mu);
-  return pl.idle_bytes;
+  return pl.idle_bytes + pl.small_bytes;
 }
 
 void pool_trim(int dev) {
@@ -181,7 +289,7 @@ void pool_stats(int dev, size_t *in_use, size_t *peak, size_t *idle) {
   std::lock_guard<std::mutex> lk(pl.mu);
   if (in_use) *in_use = pl.in_use;
   if (peak) *peak = pl.peak;
-  if (idle) *idle = pl.idle_bytes;
+  if (idle) *idle = pl.idle_bytes + pl.small_bytes;
 }
 
 void pool_reset_peak(int dev) {

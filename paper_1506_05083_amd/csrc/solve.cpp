@@ -73,25 +73,6 @@ void apply_solution_layouts(const mfs_op *op, const BodyData &b, int nrhs, const
 
 using namespace mfs;
 
-namespace {
-// pinned host memory (hipHostMalloc), freed on every way out
-struct PinnedBuf {
-  void *p = nullptr;
-  explicit PinnedBuf(size_t n) {
-    if (hipHostMalloc(&p, n, hipHostMallocDefault) != hipSuccess) {
-      p = nullptr;
-      (void)hipGetLastError();
-      throw Error{MFS_ENOMEM, "hipHostMalloc of " + std::to_string(n) + " bytes failed"};
-    }
-  }
-  ~PinnedBuf() {
-    if (p) (void)hipHostFree(p);
-  }
-  PinnedBuf(const PinnedBuf &) = delete;
-  PinnedBuf &operator=(const PinnedBuf &) = delete;
-};
-}  // namespace
-
 extern "C" mfs_status mfs_solve_incident(mfs_ctx *ctx, const mfs_op *op, int32_t body, const mfs_lattice *lat,
                                          int32_t nwaves, const mfs_wave *waves, double tol, int32_t maxit,
                                          double rel_cutoff, const double *targets, int32_t ntargets,

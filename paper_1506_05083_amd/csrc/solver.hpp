@@ -126,7 +126,6 @@ struct Solver {
         MatDesc d{};
         d.a = Q[w].as<double2>() + (par ? (size_t)ldq * nc[0] : 0);
         d.m = rows_h; d.n = nc[par]; d.lda = ldq;
-        d.flag = flags + 2 * w + par;
         d.rank = flags + NM + 2 * w + par;
         h_qdescs[2 * w + par] = d;
         a.Q[par] = d.a;

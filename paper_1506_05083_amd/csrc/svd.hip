@@ -67,11 +67,6 @@ __global__ void jac_init_kernel(const MatDesc *__restrict__ descs, int mode) {
   }
 }
 
-__global__ void jac_clear_flags(const MatDesc *__restrict__ descs, int nmat) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nmat) descs[i].flag[0] = 0;
-}
-
 constexpr int kJacWideMinCols = 2048;  // 32-column blocks from this width on
 
 __device__ inline void circle_pair(int np, int round, int pair, int &p, int &q) {
@@ -117,22 +112,22 @@ __device__ inline int task_col(int a, int bi, int bj, int nb, int n) {
 // the same columns, so skipping them changes no result.
 struct JacClean {
   int *bmod, *pchk;
-  int *nchk;   // [mat] pairs checked (not skipped) in the current sweep
   int nbp;
+  // of the current sweep, [mat]: tasks that rotated, tasks checked (not skipped)
+  int *flag, *nchk;
 };
 __device__ inline bool jac_clean(const JacClean &cs, int mat, int bi, int bj) {
   const int a = min(bi, bj), b = max(bi, bj);
   const int c = cs.pchk[((size_t)mat * cs.nbp + a) * cs.nbp + b];
   return c >= 0 && c > cs.bmod[mat * cs.nbp + bi] && c > cs.bmod[mat * cs.nbp + bj];
 }
-__global__ void jac_clean_init(JacClean cs, int nmat) {
+// no block turned and no pair checked yet; of the control words ctl, nctl in
+// all, the first nmat (the matrices active in the first sweep) 1, the others 0
+__global__ void jac_clean_init(JacClean cs, int nmat, int *__restrict__ ctl, int nctl) {
   const long n = (long)nmat * cs.nbp * (cs.nbp + 1);
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
-    cs.bmod[i] = -1;   // bmod and pchk are one allocation
-}
-__global__ void jac_clear_checks(JacClean cs, int nmat) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nmat) cs.nchk[i] = 0;
+  const long i0 = (long)blockIdx.x * blockDim.x + threadIdx.x, step = (long)gridDim.x * blockDim.x;
+  for (long i = i0; i < n; i += step) cs.bmod[i] = -1;   // bmod and pchk are one allocation
+  for (long i = i0; i < nctl; i += step) ctl[i] = i < nmat;
 }
 
 // One Jacobi sweep over the JC columns of a task on H (Hs), the rotations'
@@ -290,7 +285,7 @@ __global__ __launch_bounds__(JB * JB) void jac_inner_kernel(const MatDesc *__res
     rot[(size_t)mat * npair_max + pair] = s_nrot > 0;
     atomicAdd(cs.nchk + mat, 1);
     if (s_nrot > 0) {
-      atomicAdd(d.flag, 1);
+      atomicAdd(cs.flag + mat, 1);
       cs.bmod[mat * cs.nbp + tbi] = gr;
       cs.bmod[mat * cs.nbp + tbj] = gr;
     } else {
@@ -529,7 +524,7 @@ __global__ __launch_bounds__(256, 4) void jac_round_kernel(const MatDesc *__rest
   if (tid == 0) {
     atomicAdd(cs.nchk + mat, 1);
     if (nrot > 0) {
-      atomicAdd(d.flag, 1);
+      atomicAdd(cs.flag + mat, 1);
       cs.bmod[mat * cs.nbp + bi] = gr;
       cs.bmod[mat * cs.nbp + bj] = gr;
     } else {
@@ -833,15 +828,11 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
     nbpmax = std::max(nbpmax, nb + (nb & 1));
   }
   if (nmax == 0) return st;
-  hipEvent_t e0, e1;
-  HIP_CHECK(hipEventCreate(&e0));
-  HIP_CHECK(hipEventCreate(&e1));
   hipLaunchKernelGGL(jac_init_kernel, dim3(std::min(1024, cdiv(nmax * nmax, 256)), nmat), dim3(256),
                      0, s, descs, init_mode);
   HIP_CHECK(hipGetLastError());
   for (int i = 0; i < nmat; ++i) {
-    MFS_REQUIRE(h[i].flag == h[0].flag + i && h[i].rank == h[0].rank + i,
-                "jacobi: flags and ranks must be contiguous");
+    MFS_REQUIRE(h[i].rank == h[0].rank + i, "jacobi: ranks must be contiguous");
   }
   // per matrix and sweep: tasks and their mean width (columns), for the
   // algorithmic byte and flop counts
@@ -861,8 +852,7 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
       }
     width[i] = tasks[i] > 0.0 ? cols / tasks[i] : 0.0;
   }
-  std::vector<int> flags(nmat), checked(nmat), active(nmat, 1);
-  DevBuf act((size_t)nmat * sizeof(int));
+  std::vector<int> active(nmat, 1);
   const int npair_max = std::max(1, nbpmax / 2);
   const int ntile_max = cdiv(nmax, GT), atile_max = cdiv(nmax, AT);
   // A workgroup a task and one launch a round, unless a round's few workgroups
@@ -899,12 +889,6 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
     g0[ngroup] = nmat;
   }
   SideStreams side(ngroup - 1);
-  const size_t ncl = (size_t)nmat * nbpmax * (nbpmax + 1);
-  DevBuf cleanbuf((ncl + nmat) * sizeof(int));
-  JacClean cs{cleanbuf.as<int>(), cleanbuf.as<int>() + (size_t)nmat * nbpmax, cleanbuf.as<int>() + ncl, nbpmax};
-  hipLaunchKernelGGL(jac_clean_init, dim3(std::min(1024, cdiv(nmat * nbpmax * (nbpmax + 1), 256))), dim3(256), 0,
-                     s, cs, nmat);
-  HIP_CHECK(hipGetLastError());
   // rotation threshold 4 sqrt(n) eps, n of each matrix (set in the kernel)
   const double tol = 4.0 * 2.220446049250313e-16;
   // sweep cap; MFS_JACOBI_MAX_SWEEPS lowers it (a test of the not-converged
@@ -912,12 +896,43 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
   int max_sweeps = 40;
   if (const char *e = getenv("MFS_JACOBI_MAX_SWEEPS")) max_sweeps = std::max(1, std::min(40, atoi(e)));
   const bool dbg = getenv("MFS_DEBUG") != nullptr;
-  int sweep = 0;
-  for (; sweep < max_sweeps; ++sweep) {
-    HIP_CHECK(hipMemcpyAsync(act.p, active.data(), nmat * sizeof(int), hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(jac_clear_flags, dim3(cdiv(nmat, 256)), dim3(256), 0, s, descs, nmat);
-    hipLaunchKernelGGL(jac_clear_checks, dim3(cdiv(nmat, 256)), dim3(256), 0, s, cs, nmat);
-    HIP_CHECK(hipEventRecord(e0, s));
+  // control words: [mat] 1, then of each sweep [mat] tasks that rotated and
+  // [mat] tasks checked; a matrix is active in a sweep if it rotated in the one before
+  const size_t ncl = (size_t)nmat * nbpmax * (nbpmax + 1);
+  const int nctl = nmat * (1 + 2 * max_sweeps);
+  DevBuf cleanbuf((ncl + nctl) * sizeof(int));
+  int *ctl = cleanbuf.as<int>() + ncl;
+  JacClean cs{cleanbuf.as<int>(), cleanbuf.as<int>() + (size_t)nmat * nbpmax, nbpmax, nullptr, nullptr};
+  hipLaunchKernelGGL(jac_clean_init, dim3(std::min(1024, cdiv(nmat * nbpmax * (nbpmax + 1), 256))), dim3(256), 0,
+                     s, cs, nmat, ctl, nctl);
+  HIP_CHECK(hipGetLastError());
+  // A sweep of few launches is queued before the one ahead of it is known to
+  // have turned anything (its workgroups return at once if nothing did): the
+  // read-back between the sweeps of 17 matrices of 60 columns, 50 us, is hidden.
+  const bool ahead = rounds * (one ? ngroup : 3) <= 16;
+  PinnedBuf back((size_t)2 * 2 * nmat * sizeof(int));
+  struct SweepEvents {
+    hipEvent_t e0[2], e1[2], done[2];
+    SweepEvents() {
+      for (int i = 0; i < 2; ++i) {
+        HIP_CHECK(hipEventCreate(&e0[i]));
+        HIP_CHECK(hipEventCreate(&e1[i]));
+        HIP_CHECK(hipEventCreateWithFlags(&done[i], hipEventDisableTiming));
+      }
+    }
+    ~SweepEvents() {
+      for (int i = 0; i < 2; ++i) {
+        (void)hipEventDestroy(e0[i]);
+        (void)hipEventDestroy(e1[i]);
+        (void)hipEventDestroy(done[i]);
+      }
+    }
+  } ev;
+  auto queue_sweep = [&](int sweep) {
+    int *act = sweep ? ctl + (size_t)nmat * (2 * sweep - 1) : ctl;
+    cs.flag = ctl + (size_t)nmat * (2 * sweep + 1);
+    cs.nchk = cs.flag + nmat;
+    HIP_CHECK(hipEventRecord(ev.e0[sweep & 1], s));
     side.fork(s);
     for (int rnd = 0; rnd < rounds; ++rnd) {
       if (one) {
@@ -927,36 +942,44 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
           for (int i = m0; i < m0 + nm; ++i)
             if (active[i]) np = std::max(np, cdiv(cdiv(h[i].n, JB), 2));
           if (np == 0 || rnd >= 2 * np - 1) continue;   // a matrix runs its own rounds
-          const JacClean cg{cs.bmod + (size_t)m0 * nbpmax, cs.pchk + (size_t)m0 * nbpmax * nbpmax, cs.nchk + m0, nbpmax};
+          const JacClean cg{cs.bmod + (size_t)m0 * nbpmax, cs.pchk + (size_t)m0 * nbpmax * nbpmax, nbpmax, cs.flag + m0,
+                            cs.nchk + m0};
           hipLaunchKernelGGL(jac_round_kernel, dim3(np, nm), dim3(256), 0, g ? side.st[g - 1] : s, descs + m0,
-                             act.as<int>() + m0, rnd, tol, cg, sweep * rounds + rnd);
+                             act + m0, rnd, tol, cg, sweep * rounds + rnd);
         }
         continue;
       }
       if (JB == 16)
         hipLaunchKernelGGL(jac_gram_mfma_kernel, dim3(ntile_max, npair_max, nmat), dim3(64), 0, s, descs,
-                           act.as<int>(), rnd, hpart.as<double2>(), npair_max, ntile_max, cs);
+                           act, rnd, hpart.as<double2>(), npair_max, ntile_max, cs);
       else
         hipLaunchKernelGGL(jac_gram_mfma32_kernel, dim3(ntile_max, npair_max, nmat), dim3(128), 0, s, descs,
-                           act.as<int>(), rnd, hpart.as<double2>(), npair_max, ntile_max, cs);
-      hipLaunchKernelGGL(jac_inner_kernel<JB>, dim3(npair_max, nmat), dim3(JB * JB), 0, s, descs, act.as<int>(), rnd,
+                           act, rnd, hpart.as<double2>(), npair_max, ntile_max, cs);
+      hipLaunchKernelGGL(jac_inner_kernel<JB>, dim3(npair_max, nmat), dim3(JB * JB), 0, s, descs, act, rnd,
                          tol, hpart.as<double2>(), jbuf.as<double2>(), rotf.as<int>(), npair_max, ntile_max, cs,
                          sweep * rounds + rnd);
       if (JB == 16)
         hipLaunchKernelGGL(jac_apply_mfma_kernel, dim3(atile_max, npair_max, nmat), dim3(64), 0, s, descs,
-                           act.as<int>(), rnd, jbuf.as<double2>(), rotf.as<int>(), npair_max);
+                           act, rnd, jbuf.as<double2>(), rotf.as<int>(), npair_max);
       else
         hipLaunchKernelGGL(jac_apply_mfma32_kernel, dim3(cdiv(nmax, 16), npair_max, nmat), dim3(64), 0, s,
-                           descs, act.as<int>(), rnd, jbuf.as<double2>(), rotf.as<int>(), npair_max);
+                           descs, act, rnd, jbuf.as<double2>(), rotf.as<int>(), npair_max);
     }
     HIP_CHECK(hipGetLastError());
     side.join(s);
-    HIP_CHECK(hipEventRecord(e1, s));
-    HIP_CHECK(hipMemcpyAsync(flags.data(), h[0].flag, nmat * sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_CHECK(hipMemcpyAsync(checked.data(), cs.nchk, nmat * sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_CHECK(hipStreamSynchronize(s));
+    HIP_CHECK(hipEventRecord(ev.e1[sweep & 1], s));
+    HIP_CHECK(hipMemcpyAsync(static_cast<int *>(back.p) + (size_t)(sweep & 1) * 2 * nmat, cs.flag,
+                             (size_t)2 * nmat * sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_CHECK(hipEventRecord(ev.done[sweep & 1], s));
+  };
+  int sweep = 0;
+  queue_sweep(0);
+  for (; sweep < max_sweeps; ++sweep) {
+    if (ahead ? sweep + 1 < max_sweeps : sweep > 0) queue_sweep(ahead ? sweep + 1 : sweep);
+    HIP_CHECK(hipEventSynchronize(ev.done[sweep & 1]));
+    const int *flags = static_cast<int *>(back.p) + (size_t)(sweep & 1) * 2 * nmat, *checked = flags + nmat;
     float ms = 0.f;
-    HIP_CHECK(hipEventElapsedTime(&ms, e0, e1));
+    HIP_CHECK(hipEventElapsedTime(&ms, ev.e0[sweep & 1], ev.e1[sweep & 1]));
     st.ms += ms;
     st.launches += (one ? 1 : 3) * rounds;
     // algorithmic work: every checked task (a pair not known converged) reads
@@ -984,8 +1007,7 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
   // matrices that still rotated in the last sweep allowed did not converge
   if (sweep == max_sweeps)
     for (int i = 0; i < nmat; ++i) st.unconverged += active[i] ? 1 : 0;
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
+  if (ahead) HIP_CHECK(hipStreamSynchronize(s));   // the sweep queued ahead writes to the pinned block too
   return st;
 }
 
