@@ -10,10 +10,10 @@
 namespace mfs {
 
 // ------------------------------------------------------------ device buffer
-// Device memory of the calling thread's current device.  Blocks of 1 MiB
-// and more come from a per-device cache (pool.cpp): release keeps them for
-// the next request of about their size, after the device has finished the
-// work queued before the release (the rule hipFree keeps).
+// Device memory of the calling thread's current device, from a per-device
+// cache (pool.cpp): release keeps the block for a later request of about its
+// size, which gets it once the device has finished the work queued before the
+// release (the rule hipFree keeps).
 struct DevBuf {
   void *p = nullptr;
   size_t bytes = 0;

@@ -376,8 +376,8 @@ __global__ __launch_bounds__(64 * NWMAX) void bqr_panel_kernel(const MatDesc *__
 // matrices whose columns are independent (the periodizer's equilibrated Q):
 // the column steps above are a chain of 17 launches a panel, each a
 // reduction over all rows (16 matrices of 2304 rows: 8.3 us a launch, most of it
-// latency, 143 us a panel); this is three launches of two reductions (6, 17 and
-// 30 us), and the panel's T comes with them.
+// latency, 143 us a panel); this is three launches of two reductions (6, 12 and
+// 16 us), and the panel's T comes with them.
 //   cq_gram_kernel   G = P^H P over 256-row chunks (matrix cores);
 //   cq_solve_kernel  R1 = chol(G), P <- P R1^{-1} by row-wise substitution, and
 //                    the chunk sums of its Gram matrix;
@@ -385,14 +385,15 @@ __global__ __launch_bounds__(64 * NWMAX) void bqr_panel_kernel(const MatDesc *__
 //                    rounding, R = R2 R1), then LU of the top block less a
 //                    unitary diagonal S, Q_top - S = L U with s_j minus the
 //                    phase of the j-th pivot (Ballard, Demmel, Grigori,
-//                    Jacquelin, Nguyen and Solomonik 2014):
-//                    V = [L; Q_rest U^{-1}], tau_j = -u_jj conj(s_j), and the
-//                    panel's triangle S R.  The product of the reflectors is
+//                    Jacquelin, Nguyen and Solomonik 2014), as P_top - S R2 = L W,
+//                    W = U R2: V = [L; P_rest W^{-1}], tau_j = -u_jj conj(s_j),
+//                    and the panel's triangle S R.  The product of the reflectors is
 //                    the one whose first columns are Q S^{-1}, so T and the
 //                    updates proceed as after the column steps.
-// Every workgroup repeats the 16 x 16 factorisations (an entry a thread, the
-// step's row and column through LDS, one barrier a step) instead of waiting for
-// another launch.  The substitutions are row-wise
+// Every workgroup repeats the 16 x 16 factorisations instead of waiting for
+// another launch, in a wave's registers (panel_fact; with an entry a thread, the
+// step's row and column through LDS and a barrier a step the launches took 15
+// and 29 us).  The substitutions are row-wise
 // backward stable whatever the panel's conditioning; the orthogonality after
 // the second pass needs the first Cholesky's pivots above 1e-12 of the columns'
 // norms (condition below 1e6 after column scaling).  A pivot below sets the
@@ -446,75 +447,129 @@ __global__ __launch_bounds__(CH) void cq_gram_kernel(const MatDesc *__restrict__
 __device__ inline double2 cq_sum(const double2 *part, int nch, int nbp) {
   const int i = threadIdx.x / CQ, j = threadIdx.x % CQ;
   double2 t = cz(0.0, 0.0);
-#pragma unroll 4
+#pragma unroll 8
   for (int c = 0; c < nch; ++c) t = cadd(t, part[(size_t)c * CQ * CQ + threadIdx.x]);
   return i >= nbp || j >= nbp ? cz(i == j ? 1.0 : 0.0, 0.0) : t;
 }
 
-// G = R^H R, entry g of each thread: R into Rs (upper), the reciprocals of its
-// diagonal into rinv; false (to every thread) if a pivot is at most pivot_min
-// of its column's norm.  Ls, g0: work.
-__device__ inline bool cq_chol(double2 g, double2 (*Ls)[CQ + 1], double *g0, double2 (*Rs)[CQ + 1], double *rinv,
-                               double pivot_min) {
-  const int i = threadIdx.x / CQ, k = threadIdx.x % CQ;
-  if (i == k) g0[i] = g.x;
-  bool ok = true;
-#pragma unroll 1
-  for (int j = 0; j < CQ; ++j) {
-    if (k == j && i >= j) Ls[i][j] = g;
-    __syncthreads();
-    double dj = Ls[j][j].x;
-    if (!(dj > pivot_min * g0[j])) {   // a NaN as well
-      ok = false;
-      dj = 1.0;
-    }
-    if (i > j && k > j) {
-      const double2 w = cscale(cmul(Ls[i][j], cconj(Ls[k][j])), 1.0 / dj);
-      g = csub(g, w);
-    }
-    if (i == j && k >= j) {   // row j of R from column j of L
-      const double rs = 1.0 / sqrt(dj);
-      Rs[j][k] = k == j ? cz(dj * rs, 0.0) : cscale(cconj(Ls[k][j]), rs);
-      if (k == j) rinv[j] = rs;
-    }
-  }
-  __syncthreads();
-  return ok;
+// The 16 x 16 matrices of a panel's factorisations, in every wave alike: lane
+// c + 16 k holds the entries (4 u + k, c), u < 4, which is also the matrix
+// cores' layout of A^T, B and D, so a row goes to all lanes by lane swaps, a
+// column by DPP, and a step needs neither LDS nor a barrier.
+
+// rows 4 u + KK, the lanes 16 KK .. 16 KK + 15, to all four rows of lanes
+template <int KK>
+__device__ inline double all_rows(double v) {
+  const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  const auto l2 = __builtin_amdgcn_permlane16_swap(l[KK >> 1], l[KK >> 1], false, false);
+  const auto h2 = __builtin_amdgcn_permlane16_swap(h[KK >> 1], h[KK >> 1], false, false);
+  return __hiloint2double(h2[KK & 1], l2[KK & 1]);
+}
+template <int KK>
+__device__ inline double2 all_rows(double2 v) {
+  return cz(all_rows<KK>(v.x), all_rows<KK>(v.y));
 }
 
-// X <- X R^{-1}, X 16 x 16 with entry x of each thread (R upper, ri its
-// reciprocal diagonal, real or complex); the result also in Xs
-template <class D, class F>
-__device__ inline double2 cq_solve16(double2 x, double2 (*Xs)[CQ + 1], F R, const D *ri) {
-  const int i = threadIdx.x / CQ, k = threadIdx.x % CQ;
-#pragma unroll 1
-  for (int j = 0; j < CQ; ++j) {
-    if (k == j) {
-      if constexpr (sizeof(D) == sizeof(double)) x = cscale(x, ri[j]);
-      else x = cmul(x, ri[j]);
-      Xs[i][j] = x;
+// Factorisations of a panel: G = R^H R (r: R, rs: the reciprocal of column c's
+// diagonal entry), and with LU Q - S R = L W, S diagonal and unitary with s_j
+// minus the phase of the j-th pivot (q: L below, W from the diagonal on, sr: S
+// by rows, winv, yinv: 1 / w_cc and 1 / (s_c r_cc)).
+struct PanelFact {
+  double2 g[4], r[4], q[4], sr[4];
+  double g0, rs;          // column c's diagonal entry of G; 1 / r_cc
+  double2 winv, yinv;
+  bool ok;                // every pivot of G above pivot_min of its column's norm
+};
+template <int P, bool LU>
+__device__ inline void panel_fact(PanelFact &f, double pivot_min, int c, int k) {
+  if constexpr (P < CQ) {
+    constexpr int U = P / 4, KK = P % 4;
+    const double2 grow = all_rows<KK>(f.g[U]);
+    double d = row_lane<P>(grow.x);
+    const bool good = d > pivot_min * row_lane<P>(f.g0);   // not with a NaN
+    f.ok = f.ok && good;
+    d = good ? d : 1.0;
+    const double rs = rsqrt(d), rpp = d * rs;
+    const double2 rp = csel(c == P, cz(rpp, 0.0), csel(c > P, cscale(grow, rs), cz(0.0, 0.0)));
+    f.r[U] = csel(k == KK, rp, f.r[U]);
+    f.rs = c == P ? rs : f.rs;
+    const double2 gs = cscale(rp, -rs);
+    // (rows and columns up to P are not read again)
+#pragma unroll
+    for (int u = U; u < 4; ++u) cfma(f.g[u], row_lane<P>(f.g[u]), gs);
+    if constexpr (LU) {
+      const double2 qrow = all_rows<KK>(f.q[U]), pv = row_lane<P>(qrow);
+      const double a2 = cabs2(pv), ra = a2 > 0.0 ? rsqrt(a2) : 0.0, ab = a2 * ra;
+      const double2 s = cz(a2 > 0.0 ? -pv.x * ra : -1.0, -pv.y * ra);
+      const double wd = ab + rpp, wi = 1.0 / wd;   // w_PP = -s (|pv| + r_PP)
+      const double2 winv = cz(-s.x * wi, s.y * wi);
+      double2 w = qrow;
+      cfma(w, cz(-s.x, -s.y), rp);
+      const double2 mw = csel(c > P, cz(-w.x, -w.y), cz(0.0, 0.0));
+#pragma unroll
+      for (int u = U; u < 4; ++u) {
+        const bool below = 4 * u + k > P;
+        const double2 l = csel(below, cmul(row_lane<P>(f.q[u]), winv), cz(0.0, 0.0));
+        cfma(f.q[u], l, mw);
+        f.q[u] = csel(below && c == P, l, f.q[u]);
+      }
+      f.q[U] = csel(k == KK && c >= P, csel(c == P, cz(-s.x * wd, -s.y * wd), w), f.q[U]);
+      f.sr[U] = csel(k == KK, s, f.sr[U]);
+      f.winv = csel(c == P, winv, f.winv);
+      f.yinv = csel(c == P, cz(s.x * rs, -s.y * rs), f.yinv);
     }
-    __syncthreads();
-    if (k > j) x = csub(x, cmul(Xs[i][j], R(j, k)));
+    panel_fact<P + 1, LU>(f, pivot_min, c, k);
   }
-  return x;
 }
 
-// x <- x R^{-1} for one row x (R upper in Rs, reciprocal diagonal ri).  The
-// loads of column j are tied to x[j - 2] (an offset of zero that the compiler
-// cannot see through): issued all at once they would not fit the registers.
+// t <- t Y^{-1}, Y upper triangular, yinv the reciprocal of column c's diagonal entry
+template <int P>
+__device__ inline void panel_rsolve(double2 (&t)[4], const double2 (&y)[4], double2 yinv, int c) {
+  if constexpr (P < CQ) {
+    const double2 yr = all_rows<P % 4>(y[P / 4]), yi = row_lane<P>(yinv);
+    const double2 my = csel(c > P, cz(-yr.x, -yr.y), cz(0.0, 0.0));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const double2 x = cmul(row_lane<P>(t[u]), yi);
+      cfma(t[u], x, my);
+      t[u] = csel(c == P, x, t[u]);
+    }
+    panel_rsolve<P + 1>(t, y, yinv, c);
+  }
+}
+
+// D = sum_m a[m]^T b[m] on the matrix cores: A (i, m) given as lane i + 16 k's
+// entries m = 4 u + k
+__device__ inline void panel_mul(const double2 (&a)[4], const double2 (&b)[4], double2 (&d)[4]) {
+  dx4 re = {0, 0, 0, 0}, im = re;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    re = mfma_f64(a[u].x, b[u].x, re);
+    re = mfma_f64(-a[u].y, b[u].y, re);
+    im = mfma_f64(a[u].x, b[u].y, im);
+    im = mfma_f64(a[u].y, b[u].x, im);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) d[u] = cz(re[u], im[u]);
+}
+
+// x <- x R^{-1} for one row x (R upper in Rs, reciprocal diagonal ri), a column
+// at a time taken off the later ones.  The loads of row j are tied to x[j - 1]
+// (an offset of zero that the compiler cannot see through): issued all at once
+// they would not fit the registers.
 template <class D>
 __device__ inline void cq_subst(double2 (&x)[CQ], const double2 (*Rs)[CQ + 1], const D *ri) {
   int z = 0;
 #pragma unroll
   for (int j = 0; j < CQ; ++j) {
-    if (j >= 2) asm volatile("" : "+v"(z) : "v"(x[j - 2].x));
-    const double2 *col = &Rs[0][0] + z + j;
-    double2 t = x[j];
+    if (j >= 2) asm volatile("" : "+v"(z) : "v"(x[j - 1].x));
+    const double2 *row = &Rs[j][0] + z;
+    if constexpr (sizeof(D) == sizeof(double)) x[j] = cscale(x[j], ri[j]);
+    else x[j] = cmul(x[j], ri[j]);
+    const double2 mx = cz(-x[j].x, -x[j].y);
 #pragma unroll
-    for (int i = 0; i < j; ++i) t = csub(t, cmul(x[i], col[i * (CQ + 1)]));
-    if constexpr (sizeof(D) == sizeof(double)) x[j] = cscale(t, ri[j]);
-    else x[j] = cmul(t, ri[j]);
+    for (int i = j + 1; i < CQ; ++i) cfma(x[i], mx, row[i]);
   }
 }
 
@@ -527,17 +582,30 @@ __global__ __launch_bounds__(CH) void cq_solve_kernel(const MatDesc *__restrict_
   if (k0 >= d.n || r0 >= d.m) return;
   const int nbp = min(CQ, d.n - k0), nch = (d.m - k0 + CH - 1) / CH;
   const bool live = r < d.m;
-  __shared__ double2 Ls[CQ][CQ + 1], Rs[CQ][CQ + 1];
-  __shared__ double rinv[CQ], g0[CQ];
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lc = lane & 15, lk = lane >> 4;
+  __shared__ double2 Gs[CQ][CQ + 1], Rs[CQ][CQ + 1];
+  __shared__ double rinv[CQ];
   __shared__ double2 red[CH / 64][CQ * CQ];
   __shared__ double2 Qs[CH][CQ + 1];
   double2 x[CQ];
 #pragma unroll
   for (int c = 0; c < CQ; ++c)
     x[c] = ld_or0(d.a, (size_t)(k0 + min(c, nbp - 1)) * d.lda + min(r, d.m - 1), live && c < nbp);
-  const double2 g = cq_sum(part + (size_t)blockIdx.y * nchmax * CQ * CQ, nch, nbp);
-  const bool ok = cq_chol(g, Ls, g0, Rs, rinv, kCholPivotMin);
-  if (!ok && tid == 0) bad[blockIdx.y] = 1;
+  Gs[tid / CQ][tid % CQ] = cq_sum(part + (size_t)blockIdx.y * nchmax * CQ * CQ, nch, nbp);
+  __syncthreads();
+  if (wv == 0) {
+    PanelFact f;
+    f.ok = true;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f.g[u] = Gs[4 * u + lk][lc];
+    f.g0 = Gs[lc][lc].x;
+    panel_fact<0, false>(f, kCholPivotMin, lc, lk);
+    if (!f.ok && tid == 0) bad[blockIdx.y] = 1;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) Rs[4 * u + lk][lc] = f.r[u];
+    if (lk == 0) rinv[lc] = f.rs;
+  }
+  __syncthreads();
   cq_subst(x, Rs, rinv);
   double2 *sd = side + (size_t)blockIdx.y * 2 * CQ * CQ;
 #pragma unroll
@@ -562,85 +630,83 @@ __global__ __launch_bounds__(CH) void cq_reflect_kernel(const MatDesc *__restric
                                                         const double2 *__restrict__ side, int nchmax,
                                                         int *__restrict__ bad, int nbo, double2 *__restrict__ tx) {
   const MatDesc d = descs[blockIdx.y];
-  const int r0 = k0 + blockIdx.x * CH, tid = threadIdx.x, r = r0 + tid;
+  // the first workgroup writes the top block and T, the others a chunk of rows each
+  const int r0 = k0 + ((int)blockIdx.x - 1) * CH, tid = threadIdx.x, r = r0 + tid;
   if (k0 >= d.n || r0 >= d.m) return;
   const int nbp = min(CQ, d.n - k0), nch = (d.m - k0 + CH - 1) / CH;
   const bool below = r < d.m && r >= k0 + CQ;
-  __shared__ double2 Ls[CQ][CQ + 1], Rs[CQ][CQ + 1], LU[CQ][CQ + 1], Ws[CQ][CQ + 1];
-  __shared__ double rinv[CQ], g0[CQ];
-  __shared__ double2 winv[CQ], sgn[CQ];
-  const int i = tid / CQ, j = tid % CQ;
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 15, k = lane >> 4;
+  __shared__ double2 Gs[CQ][CQ + 1], Rs[CQ][CQ + 1], Ws[CQ][CQ + 1];
+  __shared__ double2 winv[CQ];
   double2 x[CQ];
 #pragma unroll
-  for (int c = 0; c < CQ; ++c)
-    x[c] = ld_or0(d.a, (size_t)(k0 + min(c, nbp - 1)) * d.lda + min(r, d.m - 1), below && c < nbp);
+  for (int j = 0; j < CQ; ++j)
+    x[j] = ld_or0(d.a, (size_t)(k0 + min(j, nbp - 1)) * d.lda + min(r, d.m - 1), below && j < nbp);
   const double2 *sd = side + (size_t)blockIdx.y * 2 * CQ * CQ;
-  double2 t = csel(j < nbp, sd[tid], cz(0.0, 0.0));   // past the last column: u = 1
-  const double2 g = cq_sum(part2 + (size_t)blockIdx.y * nchmax * CQ * CQ, nch, nbp);
+  PanelFact f;
+  f.ok = true;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) f.q[u] = ld_or0(sd, (4 * u + k) * CQ + c, c < nbp);   // past the last column: w = 1
+  Gs[tid / CQ][tid % CQ] = cq_sum(part2 + (size_t)blockIdx.y * nchmax * CQ * CQ, nch, nbp);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) f.g[u] = Gs[4 * u + k][c];
+  f.g0 = Gs[c][c].x;
   // near the identity unless the first pass failed
-  const bool ok = cq_chol(g, Ls, g0, Rs, rinv, 0.1);
-  if (!ok && tid == 0) bad[blockIdx.y] = 1;
-  t = cq_solve16(t, Ws, [&](int p, int q) { return Rs[p][q]; }, rinv);
-  // LU of the top block less S
-#pragma unroll 1
-  for (int p = 0; p < CQ; ++p) {
-    if ((i == p && j >= p) || (j == p && i > p)) LU[i][j] = t;
-    __syncthreads();
-    const double2 pv = LU[p][p];
-    const double ab = sqrt(cabs2(pv));
-    const double2 sp = ab > 0.0 ? cz(-pv.x / ab, -pv.y / ab) : cz(-1.0, 0.0);
-    const double2 u = csub(pv, sp);
-    const double ui = 1.0 / cabs2(u);
-    const double2 l = cmul(LU[i][p], cz(u.x * ui, -u.y * ui));   // row i of column p of L
-    const double2 up = LU[p][j];
-    if (i > p && j > p) t = csub(t, cmul(l, up));
-    __syncthreads();   // the pivot column and diagonal are rewritten as L and U
-    if (j == p && i > p) LU[i][p] = l;
-    if (i == p && j == p) {
-      LU[p][p] = u;
-      sgn[p] = sp;
+  panel_fact<0, true>(f, 0.1, c, k);
+  if (!f.ok && blockIdx.x == 0 && tid == 0) bad[blockIdx.y] = 1;
+  if (wv == 0) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      Ws[4 * u + k][c] = f.q[u];
+      Rs[4 * u + k][c] = f.r[u];
     }
+    if (k == 0) winv[c] = f.winv;
   }
   __syncthreads();
-  {
-    // W = U R2: the rows below are P R2^{-1} U^{-1} = P W'^{-1} with W' = U R2
-    t = cz(0.0, 0.0);
-    for (int k = i; k <= j; ++k) cfma(t, LU[i][k], Rs[k][j]);
-    Ws[i][j] = t;
-    if (i == j) {
-      const double w = 1.0 / cabs2(t);
-      winv[i] = cz(t.x * w, -t.y * w);
-    }
-    if (blockIdx.x == 0) {
-      if (j < nbp && i <= j) {   // S R2 R1
-        double2 v = cz(0.0, 0.0);
-        for (int k = i; k <= j; ++k) cfma(v, Rs[i][k], sd[CQ * CQ + k * CQ + j]);
-        d.a[(size_t)(k0 + j) * d.lda + k0 + i] = cmul(sgn[i], v);
-      } else if (j < nbp && k0 + i < d.m) {
-        d.a[(size_t)(k0 + j) * d.lda + k0 + i] = LU[i][j];
-      }
-    }
-  }
-  __syncthreads();
+  // the rows below: P R2^{-1} U^{-1} = P W^{-1}
   if (below) {
     cq_subst(x, Ws, winv);
 #pragma unroll
-    for (int c = 0; c < CQ; ++c)
-      if (c < nbp) d.a[(size_t)(k0 + c) * d.lda + r] = x[c];
+    for (int j = 0; j < CQ; ++j)
+      if (j < nbp) d.a[(size_t)(k0 + j) * d.lda + r] = x[j];
   }
-  __syncthreads();
-  if (blockIdx.x == 0) {
-    // T = -U S^{-1} L^{-H}
-    double2 v = i <= j ? cmul(LU[i][j], cconj(sgn[j])) : cz(0.0, 0.0);
-    v = cz(-v.x, -v.y);
-    if (i == j && i < nbp) d.tau[k0 + i] = v;
-    if (i == j) winv[i] = cz(1.0, 0.0);
-    __syncthreads();   // winv is free: the rows above are done in this workgroup
-    v = cq_solve16(v, Ls, [&](int p, int q) { return cconj(LU[q][p]); }, winv);
-    v = csel(i <= j && j < nbp, v, cz(0.0, 0.0));
+  if (blockIdx.x > 0) return;
+  if (wv == 0) {   // L
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (4 * u + k > c && c < nbp && k0 + 4 * u + k < d.m) d.a[(size_t)(k0 + c) * d.lda + k0 + 4 * u + k] = f.q[u];
+  } else if (wv == 1) {   // S R2 R1
+    double2 a2[4], r1[4], v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      a2[u] = Rs[c][4 * u + k];
+      r1[u] = sd[CQ * CQ + (4 * u + k) * CQ + c];
+    }
+    panel_mul(a2, r1, v);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (4 * u + k <= c && c < nbp) d.a[(size_t)(k0 + c) * d.lda + k0 + 4 * u + k] = cmul(f.sr[u], v[u]);
+  } else if (wv == 2) {   // T = -U S^{-1} L^{-H} = -W (L^H S R2)^{-1}
+    double2 lh[4], sr[4], y[4], t[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int m = 4 * u + k;
+      lh[u] = csel(m > c, cconj(f.q[u]), cz(m == c ? 1.0 : 0.0, 0.0));
+      sr[u] = cmul(f.sr[u], f.r[u]);
+      t[u] = csel(m <= c, cz(-f.q[u].x, -f.q[u].y), cz(0.0, 0.0));
+    }
+    panel_mul(lh, sr, y);
+    panel_rsolve<0>(t, y, f.yinv, c);
     const int o = k0 % nbo;
-    d.T[(size_t)(k0 / nbo) * nbo * nbo + (size_t)(o + j) * nbo + o + i] = v;
-    if (tx) tx[(size_t)blockIdx.y * CQ * CQ + j * CQ + i] = v;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = 4 * u + k;
+      const double2 v = csel(i <= c && c < nbp, t[u], cz(0.0, 0.0));
+      if (i == c && i < nbp) d.tau[k0 + i] = v;
+      d.T[(size_t)(k0 / nbo) * nbo * nbo + (size_t)(o + c) * nbo + o + i] = v;
+      if (tx) tx[(size_t)blockIdx.y * CQ * CQ + c * CQ + i] = v;
+    }
   }
 }
 
@@ -1170,7 +1236,7 @@ struct PanelWork {
       hipLaunchKernelGGL(cq_gram_kernel, g, dim3(CH), 0, s, descs, k0, part.as<double2>(), nchmax);
       hipLaunchKernelGGL(cq_solve_kernel, g, dim3(CH), 0, s, descs, k0, part.as<double2>(), p2, side.as<double2>(),
                          nchmax, bad);
-      hipLaunchKernelGGL(cq_reflect_kernel, g, dim3(CH), 0, s, descs, k0, p2, side.as<double2>(), nchmax, bad,
+      hipLaunchKernelGGL(cq_reflect_kernel, dim3(g.x + 1, g.y), dim3(CH), 0, s, descs, k0, p2, side.as<double2>(), nchmax, bad,
                          nbo, tx);
     } else if (mmax - k0 <= PTMAX) {
       // every matrix's remaining rows fit one workgroup: the panel in one launch,
