@@ -133,13 +133,14 @@ __global__ void jac_clean_init(JacClean cs, int nmat, int *__restrict__ ctl, int
 // One Jacobi sweep over the JC columns of a task on H (Hs), the rotations'
 // product in Js (identity on entry); returns the number of rotations.  All
 // JB * JB threads, H and J settled (a barrier) on entry.  Rotation of pair
-// (p, q) from a = H_pp, b = H_qq, gamma = H_pq, d = b - a:
-//   q' = 2 sign(d) / (|d| + sqrt(d^2 + 4 |gamma|^2)),  t = q' |gamma|,
-//   c = 1 / sqrt(1 + t^2),  s e^{i th} = c q' gamma,  t |gamma| = q' |gamma|^2
-// (the formulas of the header with zeta = d / (2 |gamma|), |gamma| never formed).
+// (p, q) from a = H_pp, b = H_qq, gamma = H_pq, d = b - a, by the double angle:
+//   h = sqrt(d^2 + 4 |gamma|^2),  c^2 = (1 + |d| / h) / 2,
+//   s e^{i th} = sign(d) gamma / (h c),  t |gamma| = sign(d) |gamma|^2 / (h c^2)
+// (the formulas of the header with zeta = d / (2 |gamma|); 1 / h and 1 / c are
+// reciprocal roots, |gamma| is never formed).
 // H <- R^H H R acts on every 2 x 2 block (rows of pair i, columns of pair j)
 // on its own: JB x JB blocks over the threads, J <- J R alongside.  A round is
-// a serial chain (entries, root, quotient, root, update, two barriers), so the
+// a serial chain (entries, two roots, update, two barriers), so the
 // blocks of H and J are fetched before the chain of the first JB threads, and
 // a pair that does not turn is the identity rotation, not a branch.
 template <int JB>
@@ -183,13 +184,14 @@ __device__ inline int jac_inner_sweep(double2 (*Hs)[2 * JB + 1], double2 (*Js)[2
       const double g2 = cabs2(gam);
       const bool on = g2 > tol2 * a * b;
       const double dd = b - a;
-      const double qq = copysign(2.0, dd) / (fabs(dd) + sqrt(fma(dd, dd, 4.0 * g2)));
-      const double cs = rsqrt(fma(qq * qq, g2, 1.0));
+      const double rh = rsqrt(fma(dd, dd, 4.0 * g2));
+      const double c2 = fma(0.5 * fabs(dd), rh, 0.5), rc = rsqrt(c2);
+      const double se = copysign(rh * rc, dd), tg = copysign(g2 * rh * rc * rc, dd);
       const unsigned long long m = __ballot(on);
-      wk.r_c[tid] = on ? cs : 1.0;
-      wk.r_se[tid] = on ? cz(cs * qq * gam.x, cs * qq * gam.y) : cz(0.0, 0.0);
-      wk.r_a[tid] = a - qq * g2;
-      wk.r_b[tid] = b + qq * g2;
+      wk.r_c[tid] = on ? c2 * rc : 1.0;
+      wk.r_se[tid] = on ? cz(se * gam.x, se * gam.y) : cz(0.0, 0.0);
+      wk.r_a[tid] = a - tg;
+      wk.r_b[tid] = b + tg;
       if (tid == 0) wk.mask = (unsigned)m;
       inner_pair<JB>(rnd, bi, p, q);
     }
