@@ -192,6 +192,68 @@ __device__ inline double wave_max_dpp(double v) {
   return fmax(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
 }
 
+// lane C of every row of 16 lanes to the whole row (all lanes active)
+template <int C>
+__device__ inline double row_lane(double v) {
+  return __longlong_as_double(
+      __builtin_amdgcn_update_dpp(0L, (long)__double_as_longlong(v), 0x150 + C, 0xf, 0xf, true));
+}
+template <int C>
+__device__ inline double2 row_lane(double2 v) {
+  return cz(row_lane<C>(v.x), row_lane<C>(v.y));
+}
+// 16 x 16 matrices in a wave: lane c + 16 k holds the entries (4 u + k, c),
+// u < 4, which is also the matrix cores' layout of A^T, B and D; a row goes to
+// all lanes by lane swaps, a column by DPP.
+
+// rows 4 u + KK, the lanes 16 KK .. 16 KK + 15, to all four rows of lanes
+template <int KK>
+__device__ inline double all_rows(double v) {
+  const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  const auto l2 = __builtin_amdgcn_permlane16_swap(l[KK >> 1], l[KK >> 1], false, false);
+  const auto h2 = __builtin_amdgcn_permlane16_swap(h[KK >> 1], h[KK >> 1], false, false);
+  return __hiloint2double(h2[KK & 1], l2[KK & 1]);
+}
+template <int KK>
+__device__ inline double2 all_rows(double2 v) {
+  return cz(all_rows<KK>(v.x), all_rows<KK>(v.y));
+}
+
+// t <- t Y^{-1}, Y upper triangular, yinv the reciprocal of column c's diagonal entry
+template <int P>
+__device__ inline void rsolve16(double2 (&t)[4], const double2 (&y)[4], double2 yinv, int c) {
+  if constexpr (P < 16) {
+    const double2 yr = all_rows<P % 4>(y[P / 4]), yi = row_lane<P>(yinv);
+    const double2 my = csel(c > P, cz(-yr.x, -yr.y), cz(0.0, 0.0));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const double2 x = cmul(row_lane<P>(t[u]), yi);
+      cfma(t[u], x, my);
+      t[u] = csel(c == P, x, t[u]);
+    }
+    rsolve16<P + 1>(t, y, yinv, c);
+  }
+}
+
+// re + i im += A B on the matrix cores: A (i, m) given as lane i + 16 k's entries
+// m = 4 u + k, the others as above
+__device__ inline void mfma16(const double2 (&a)[4], const double2 (&b)[4], dx4 &re, dx4 &im) {
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    re = mfma_f64(a[u].x, b[u].x, re);
+    re = mfma_f64(-a[u].y, b[u].y, re);
+    im = mfma_f64(a[u].x, b[u].y, im);
+    im = mfma_f64(a[u].y, b[u].x, im);
+  }
+}
+__device__ inline void mul16(const double2 (&a)[4], const double2 (&b)[4], double2 (&d)[4]) {
+  dx4 re = {0, 0, 0, 0}, im = re;
+  mfma16(a, b, re, im);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) d[u] = cz(re[u], im[u]);
+}
+
 constexpr int QHR = 128;   // rows a workgroup in the reflector apply
 
 __device__ inline double wave_sum(double v) {

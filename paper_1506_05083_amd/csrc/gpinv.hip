@@ -613,206 +613,155 @@ __global__ __launch_bounds__(256) void build_t_kernel(const MatDesc *__restrict_
 // from X_ij = -X_ii sum_{k=i+1..j} R_ik X_kj, whose X_kj lie nearer the
 // diagonal and are already formed.  X must be zero below the diagonal.
 constexpr int TI = 64;
-constexpr int TK = 16;   // inner-dimension chunk staged in LDS
 
 __device__ inline double2 crecip(double2 a) {
   const double d = 1.0 / cabs2(a);
   return cz(a.x * d, -a.y * d);
 }
 
-// one workgroup (TI threads) per (diagonal block, matrix); thread t solves
-// R_jj x = e_t by back substitution
-__global__ __launch_bounds__(TI) void trinv_diag_kernel(const MatDesc *__restrict__ rd,
-                                                        const MatDesc *__restrict__ xd) {
+// One workgroup a diagonal block: each wave inverts a 16 x 16 diagonal block of
+// it in registers, then X_12 = -X_11 R_12 X_22 doubles the blocks twice on the
+// matrix cores.  17 triangles of 120 columns 82 -> 12.5 us (a thread a column,
+// back substitution through LDS).
+__global__ __launch_bounds__(256) void trinv_diag_kernel(const MatDesc *__restrict__ rd,
+                                                         const MatDesc *__restrict__ xd) {
   const MatDesc r = rd[blockIdx.y], x = xd[blockIdx.y];
   const int n = x.n;
   const int j0 = blockIdx.x * TI;
   if (j0 >= n) return;
   const int nb = min(TI, n - j0);
-  __shared__ double2 Rs[TI][TI + 1];   // [column][row]
-  __shared__ double2 Xs[TI][TI + 1];   // [column][row]
-  const int t = threadIdx.x;
-  for (int c = 0; c < nb; ++c)
-    Rs[c][t] = (t <= c) ? r.a[(size_t)(j0 + c) * r.lda + j0 + t] : cz(0.0, 0.0);
-  __syncthreads();
-  if (t < nb) {
-    for (int i = 0; i < TI; ++i) Xs[t][i] = cz(0.0, 0.0);
-    Xs[t][t] = crecip(Rs[t][t]);
-    for (int i = t - 1; i >= 0; --i) {
-      double2 acc = cz(0.0, 0.0);
-      for (int k = i + 1; k <= t; ++k) cfma(acc, Rs[k][i], Xs[t][k]);
-      Xs[t][i] = cmul(cz(-acc.x, -acc.y), crecip(Rs[i][i]));
+  __shared__ double2 Xs[TI][TI + 1];
+  __shared__ double2 Ts[TI / 2][TI / 2 + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, k = lane >> 4;
+  // entry (i, j) of the block; the identity past the matrix's end
+  auto R = [&](int i, int j) {
+    const bool in = i <= j && j < nb;
+    return csel(j >= nb && i == j, cz(1.0, 0.0), ld_or0(r.a, (size_t)(j0 + j) * r.lda + j0 + i, in));
+  };
+  {
+    const int b = 16 * wv;
+    double2 y[4], t[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      y[u] = R(b + 4 * u + k, b + c);
+      t[u] = cz(4 * u + k == c ? 1.0 : 0.0, 0.0);
     }
+    rsolve16<0>(t, y, crecip(R(b + c, b + c)), c);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) Xs[b + 4 * u + k][b + c] = t[u];
   }
   __syncthreads();
-  if (t < nb)
-    for (int c = 0; c < nb; ++c) x.a[(size_t)(j0 + c) * x.lda + j0 + t] = Xs[c][t];
-}
-
-// acc += sum over k in [kbeg, kend) of R[i0 + rows, k] X[k, j0 + cols] (a
-// 4 x 4 tile of the 64 x 64 block per thread: rows ty + 16 a, columns
-// tx + 16 b), TK values of k at a time through LDS, both operands read
-// down their columns
-__device__ inline void trinv_accum(const MatDesc &r, const MatDesc &x, int i0, int j0, int nj, int kbeg,
-                                   int kend, double2 (&acc)[4][4], double2 (*As)[TI], double2 (*Bs)[TI]) {
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  for (int k0 = kbeg; k0 < kend; k0 += TK) {
-    for (int e = tid; e < TK * TI; e += 256) {
-      const int kk = e / TI, q = e % TI;
-      const int k = k0 + kk;
-      As[kk][q] = (k < kend) ? r.a[(size_t)k * r.lda + i0 + q] : cz(0.0, 0.0);
-      const int kb = e % TK, qb = e / TK;
-      const int k2 = k0 + kb;
-      Bs[kb][qb] = (k2 < kend && qb < nj) ? x.a[(size_t)(j0 + qb) * x.lda + k2] : cz(0.0, 0.0);
+  double2 p[4], q[4], t[4];
+  if (wv < 2) {
+    const int b = 32 * wv, e = b + 16;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      p[u] = R(b + c, e + 4 * u + k);
+      q[u] = Xs[e + 4 * u + k][e + c];
     }
-    __syncthreads();
-#pragma unroll 4
-    for (int kk = 0; kk < TK; ++kk) {
-      double2 av[4], bv[4];
+    mul16(p, q, t);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) av[a] = As[kk][ty + 16 * a];
+    for (int u = 0; u < 4; ++u) p[u] = Xs[b + c][b + 4 * u + k];
+    mul16(p, t, q);
 #pragma unroll
-      for (int b = 0; b < 4; ++b) bv[b] = Bs[kk][tx + 16 * b];
+    for (int u = 0; u < 4; ++u) Xs[b + 4 * u + k][e + c] = cz(-q[u].x, -q[u].y);
+  }
+  __syncthreads();
+  const int ti = 16 * (wv >> 1), tj = 16 * (wv & 1);   // this wave's tile of the upper right quarter
+  dx4 re = {0, 0, 0, 0}, im = re;
+  for (int m = 0; m <= tj; m += 16) {
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) cfma(acc[a][b], av[a], bv[b]);
+    for (int u = 0; u < 4; ++u) {
+      p[u] = R(ti + c, 32 + m + 4 * u + k);
+      q[u] = Xs[32 + m + 4 * u + k][32 + tj + c];
     }
-    __syncthreads();
+    mfma16(p, q, re, im);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) Ts[ti + 4 * u + k][tj + c] = cz(re[u], im[u]);
+  __syncthreads();
+  re = dx4{0, 0, 0, 0};
+  im = re;
+  for (int m = ti; m < 32; m += 16) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      p[u] = Xs[ti + c][m + 4 * u + k];
+      q[u] = Ts[m + 4 * u + k][tj + c];
+    }
+    mfma16(p, q, re, im);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) Xs[ti + 4 * u + k][32 + tj + c] = cz(-re[u], -im[u]);
+  __syncthreads();
+  for (int idx = tid; idx < TI * TI; idx += 256) {
+    const int i = idx % TI, j = idx / TI;
+    if (i < nb && j < nb) x.a[(size_t)(j0 + j) * x.lda + j0 + i] = i <= j ? Xs[i][j] : cz(0.0, 0.0);
   }
 }
 
-// X_ij = -X_ii T with T in Ts ([row][column], complete): X_ii in chunks of
-// TK columns through As
-__device__ inline void trinv_finish(const MatDesc &x, int i0, int j0, int nj, double2 (*Ts)[TI + 1],
-                                    double2 (*As)[TI]) {
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  double2 out[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) out[a][b] = cz(0.0, 0.0);
-  for (int k0 = 0; k0 < TI; k0 += TK) {
-    for (int e = tid; e < TK * TI; e += 256) {
-      const int kk = e / TI, q = e % TI;
-      As[kk][q] = x.a[(size_t)(i0 + k0 + kk) * x.lda + i0 + q];   // X_ii[q][k0 + kk]
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int kk = 0; kk < TK; ++kk) {
-      double2 av[4], bv[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) av[a] = As[kk][ty + 16 * a];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) bv[b] = Ts[k0 + kk][tx + 16 * b];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) cfma(out[a][b], av[a], bv[b]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int col = tx + 16 * b;
-      if (col < nj) x.a[(size_t)(j0 + col) * x.lda + i0 + ty + 16 * a] = cz(-out[a][b].x, -out[a][b].y);
-    }
-}
-
-// blocks (i, i + d) of every matrix, the whole sum in one workgroup (i, matrix)
+// Blocks (i, i + d) of every matrix: one workgroup a 16-column slice, a wave 16
+// of its rows, the fragments of R and X straight from memory with the next ones
+// in flight, T = sum_k R_ik X_kj through LDS to the product with -X_ii.  Bound by
+// the compute unit's matrix cores, 3 us a block of the sum: d = 1 of 2 matrices of
+// 650 columns 75 -> 10 us, d = 10 in one launch 36 (a workgroup a 64 x 64 block with
+// both operands staged in LDS, long sums split over workgroups and added by a
+// launch more: 80 + 36).  The sum in four shares over 16 waves is no faster: 31 us.
 __global__ __launch_bounds__(256) void trinv_off_kernel(const MatDesc *__restrict__ rd,
                                                         const MatDesc *__restrict__ xd, int d) {
   const MatDesc r = rd[blockIdx.y], x = xd[blockIdx.y];
   const int n = x.n;
-  const int i0 = blockIdx.x * TI, j0 = (blockIdx.x + d) * TI;
+  const int i0 = (blockIdx.x >> 2) * TI, j0 = i0 + d * TI + 16 * (blockIdx.x & 3);
   if (j0 >= n) return;
-  const int nj = min(TI, n - j0);   // row block i is whole (it precedes j)
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  __shared__ double2 As[TK][TI];
-  __shared__ double2 Bs[TK][TI];
-  __shared__ double2 Ts[TI][TI + 1];
-  double2 acc[4][4];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, k = lane >> 4, rt = 16 * wv;
+  __shared__ double2 Ts[TI][17];
+  const int row = i0 + rt + c;   // row block i is whole (it precedes j)
+  const int col = min(j0 + c, n - 1);
+  const double2 *xc = x.a + (size_t)col * x.lda;
+  const int kend = min(j0 + 16, n);   // X is zero below its diagonal
+  dx4 re = {0, 0, 0, 0}, im = re;
+  double2 p[4], q[4], pn[4], qn[4];
+  auto fetch = [&](int k0, double2(&a)[4], double2(&b)[4]) {
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = cz(0.0, 0.0);
-  trinv_accum(r, x, i0, j0, nj, i0 + TI, j0 + nj, acc, As, Bs);
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) Ts[ty + 16 * a][tx + 16 * b] = acc[a][b];
-  __syncthreads();
-  trinv_finish(x, i0, j0, nj, Ts, As);
-}
-
-// Far from the diagonal the sum over k is split: workgroup (chunk, i,
-// matrix) sums KSPL block columns of it into its slot of P, then
-// trinv_fin_kernel adds the slots and multiplies by -X_ii.  P slot of
-// (matrix, i, chunk): ((mat (nblk - d) + i) nch + chunk) TI^2.
-constexpr int KSPL = 4;
-__global__ __launch_bounds__(256) void trinv_part_kernel(const MatDesc *__restrict__ rd,
-                                                         const MatDesc *__restrict__ xd, int d, int nblk,
-                                                         int nch, double2 *__restrict__ P) {
-  const MatDesc r = rd[blockIdx.z], x = xd[blockIdx.z];
-  const int n = x.n;
-  const int i = blockIdx.y, i0 = i * TI, j0 = (i + d) * TI;
-  if (j0 >= n) return;
-  const int nj = min(TI, n - j0);
-  const int kbeg = i0 + TI + blockIdx.x * KSPL * TI, kend = min(kbeg + KSPL * TI, j0 + nj);
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  __shared__ double2 As[TK][TI];
-  __shared__ double2 Bs[TK][TI];
-  double2 acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = cz(0.0, 0.0);
-  trinv_accum(r, x, i0, j0, nj, kbeg, kend, acc, As, Bs);   // kbeg < kend: chunks cover d blocks
-  double2 *slot = P + (((size_t)blockIdx.z * (nblk - d) + i) * nch + blockIdx.x) * TI * TI;
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) slot[(size_t)(ty + 16 * a) * TI + tx + 16 * b] = acc[a][b];
-}
-
-__global__ __launch_bounds__(256) void trinv_fin_kernel(const MatDesc *__restrict__ xd, int d, int nblk, int nch,
-                                                        const double2 *__restrict__ P) {
-  const MatDesc x = xd[blockIdx.y];
-  const int n = x.n;
-  const int i = blockIdx.x, i0 = i * TI, j0 = (i + d) * TI;
-  if (j0 >= n) return;
-  const int nj = min(TI, n - j0);
-  __shared__ double2 As[TK][TI];
-  __shared__ double2 Ts[TI][TI + 1];
-  const double2 *slots = P + ((size_t)blockIdx.y * (nblk - d) + i) * nch * TI * TI;
-  for (int e = threadIdx.x; e < TI * TI; e += 256) {
-    double2 t = cz(0.0, 0.0);
-    for (int c = 0; c < nch; ++c) t = cadd(t, slots[(size_t)c * TI * TI + e]);
-    Ts[e / TI][e % TI] = t;
+    for (int u = 0; u < 4; ++u) {
+      const int kk = k0 + 4 * u + k;
+      const bool in = kk < kend;
+      a[u] = ld_or0(r.a, (size_t)kk * r.lda + row, in);
+      b[u] = ld_or0(xc, kk, in && j0 + c < n);
+    }
+  };
+  fetch(i0 + TI, p, q);
+  for (int k0 = i0 + TI; k0 < kend; k0 += 32) {
+    fetch(k0 + 16, pn, qn);
+    mfma16(p, q, re, im);
+    fetch(k0 + 32, p, q);
+    mfma16(pn, qn, re, im);
   }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) Ts[rt + 4 * u + k][c] = cz(re[u], im[u]);
   __syncthreads();
-  trinv_finish(x, i0, j0, nj, Ts, As);
+  re = dx4{0, 0, 0, 0};
+  im = re;
+  for (int m = rt; m < TI; m += 16) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      p[u] = x.a[(size_t)(i0 + m + 4 * u + k) * x.lda + row];
+      q[u] = Ts[m + 4 * u + k][c];
+    }
+    mfma16(p, q, re, im);
+  }
+  if (j0 + c < n)
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      x.a[(size_t)(j0 + c) * x.lda + i0 + rt + 4 * u + k] = cz(-re[u], -im[u]);
 }
 
 // The blocks off the diagonal of X = R^{-1} (diagonal blocks done), one
-// block distance d after the other: up to KSPL blocks from the diagonal one
-// workgroup a block, farther with the sum split over KSPL-block chunks.
+// block distance d after the other.
 void trinv_offdiag(const MatDesc *rd, const MatDesc *xd, int W, int nblk, hipStream_t s) {
-  size_t pslots = 0;
-  for (int d = KSPL + 1; d < nblk; ++d) pslots = std::max(pslots, (size_t)(nblk - d) * cdiv(d, KSPL));
-  DevBuf P(pslots * W * TI * TI * sizeof(double2));
-  for (int d = 1; d < nblk; ++d) {
-    if (d <= KSPL) {
-      hipLaunchKernelGGL(trinv_off_kernel, dim3(nblk - d, W), dim3(256), 0, s, rd, xd, d);
-    } else {
-      const int nch = cdiv(d, KSPL);
-      hipLaunchKernelGGL(trinv_part_kernel, dim3(nch, nblk - d, W), dim3(256), 0, s, rd, xd, d, nblk, nch,
-                         P.as<double2>());
-      hipLaunchKernelGGL(trinv_fin_kernel, dim3(nblk - d, W), dim3(256), 0, s, xd, d, nblk, nch, P.as<double2>());
-    }
-  }
+  for (int d = 1; d < nblk; ++d)
+    hipLaunchKernelGGL(trinv_off_kernel, dim3(4 * (nblk - d), W), dim3(256), 0, s, rd, xd, d);
   HIP_CHECK(hipGetLastError());
 }
 
@@ -961,7 +910,7 @@ static bool direct_pinv(GradedPinv &g, const std::vector<int> &n2, int nmax, dou
   upload_descs(dx, hx, s);
   launch_zero(xa.as<double2>(), (long)(tx / sizeof(double2)), s);
   const int nblk = cdiv(n2max, TI);
-  hipLaunchKernelGGL(trinv_diag_kernel, dim3(nblk, W), dim3(TI), 0, s, g.d_qc.as<MatDesc>(), dx.as<MatDesc>());
+  hipLaunchKernelGGL(trinv_diag_kernel, dim3(nblk, W), dim3(256), 0, s, g.d_qc.as<MatDesc>(), dx.as<MatDesc>());
   trinv_offdiag(g.d_qc.as<MatDesc>(), dx.as<MatDesc>(), W, nblk, s);
 
   DevBuf nrm((size_t)W * n2max * sizeof(double2));
@@ -1388,7 +1337,7 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     upload_descs(dx, hx, s);
     launch_zero(xa.as<double2>(), (long)(tx / sizeof(double2)), s);
     const int nblk = cdiv(rmax, TI);
-    hipLaunchKernelGGL(trinv_diag_kernel, dim3(nblk, W), dim3(TI), 0, s, g.d_lq.as<MatDesc>(), dx.as<MatDesc>());
+    hipLaunchKernelGGL(trinv_diag_kernel, dim3(nblk, W), dim3(256), 0, s, g.d_lq.as<MatDesc>(), dx.as<MatDesc>());
     trinv_offdiag(g.d_lq.as<MatDesc>(), dx.as<MatDesc>(), W, nblk, s);
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(s));   // hx goes out of scope

@@ -233,16 +233,6 @@ __global__ __launch_bounds__(CH) void bqr_col_kernel(const MatDesc *__restrict__
 constexpr int PTMAX = 1024;   // rows of the one-launch panel
 constexpr int PNB = 16;       // its columns
 
-// lane C of every row of 16 lanes to the whole row (all lanes active)
-template <int C>
-__device__ inline double row_lane(double v) {
-  return __longlong_as_double(
-      __builtin_amdgcn_update_dpp(0L, (long)__double_as_longlong(v), 0x150 + C, 0xf, 0xf, true));
-}
-template <int C>
-__device__ inline double2 row_lane(double2 v) {
-  return cz(row_lane<C>(v.x), row_lane<C>(v.y));
-}
 // sum over the wave's four rows of 16 lanes, the same bits in all of them
 __device__ inline double sum_rows16(double v) {
   v = swap16_add(v, v);
@@ -452,24 +442,8 @@ __device__ inline double2 cq_sum(const double2 *part, int nch, int nbp) {
   return i >= nbp || j >= nbp ? cz(i == j ? 1.0 : 0.0, 0.0) : t;
 }
 
-// The 16 x 16 matrices of a panel's factorisations, in every wave alike: lane
-// c + 16 k holds the entries (4 u + k, c), u < 4, which is also the matrix
-// cores' layout of A^T, B and D, so a row goes to all lanes by lane swaps, a
-// column by DPP, and a step needs neither LDS nor a barrier.
-
-// rows 4 u + KK, the lanes 16 KK .. 16 KK + 15, to all four rows of lanes
-template <int KK>
-__device__ inline double all_rows(double v) {
-  const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
-  const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
-  const auto l2 = __builtin_amdgcn_permlane16_swap(l[KK >> 1], l[KK >> 1], false, false);
-  const auto h2 = __builtin_amdgcn_permlane16_swap(h[KK >> 1], h[KK >> 1], false, false);
-  return __hiloint2double(h2[KK & 1], l2[KK & 1]);
-}
-template <int KK>
-__device__ inline double2 all_rows(double2 v) {
-  return cz(all_rows<KK>(v.x), all_rows<KK>(v.y));
-}
+// The 16 x 16 matrices of a panel's factorisations are held in every wave alike
+// (the layout of rsolve16, common.hpp), so a step needs neither LDS nor a barrier.
 
 // Factorisations of a panel: G = R^H R (r: R, rs: the reciprocal of column c's
 // diagonal entry), and with LU Q - S R = L W, S diagonal and unitary with s_j
@@ -521,37 +495,6 @@ __device__ inline void panel_fact(PanelFact &f, double pivot_min, int c, int k) 
     }
     panel_fact<P + 1, LU>(f, pivot_min, c, k);
   }
-}
-
-// t <- t Y^{-1}, Y upper triangular, yinv the reciprocal of column c's diagonal entry
-template <int P>
-__device__ inline void panel_rsolve(double2 (&t)[4], const double2 (&y)[4], double2 yinv, int c) {
-  if constexpr (P < CQ) {
-    const double2 yr = all_rows<P % 4>(y[P / 4]), yi = row_lane<P>(yinv);
-    const double2 my = csel(c > P, cz(-yr.x, -yr.y), cz(0.0, 0.0));
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const double2 x = cmul(row_lane<P>(t[u]), yi);
-      cfma(t[u], x, my);
-      t[u] = csel(c == P, x, t[u]);
-    }
-    panel_rsolve<P + 1>(t, y, yinv, c);
-  }
-}
-
-// D = sum_m a[m]^T b[m] on the matrix cores: A (i, m) given as lane i + 16 k's
-// entries m = 4 u + k
-__device__ inline void panel_mul(const double2 (&a)[4], const double2 (&b)[4], double2 (&d)[4]) {
-  dx4 re = {0, 0, 0, 0}, im = re;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    re = mfma_f64(a[u].x, b[u].x, re);
-    re = mfma_f64(-a[u].y, b[u].y, re);
-    im = mfma_f64(a[u].x, b[u].y, im);
-    im = mfma_f64(a[u].y, b[u].x, im);
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u) d[u] = cz(re[u], im[u]);
 }
 
 // x <- x R^{-1} for one row x (R upper in Rs, reciprocal diagonal ri), a column
@@ -683,7 +626,7 @@ __global__ __launch_bounds__(CH) void cq_reflect_kernel(const MatDesc *__restric
       a2[u] = Rs[c][4 * u + k];
       r1[u] = sd[CQ * CQ + (4 * u + k) * CQ + c];
     }
-    panel_mul(a2, r1, v);
+    mul16(a2, r1, v);
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (4 * u + k <= c && c < nbp) d.a[(size_t)(k0 + c) * d.lda + k0 + 4 * u + k] = cmul(f.sr[u], v[u]);
@@ -696,8 +639,8 @@ __global__ __launch_bounds__(CH) void cq_reflect_kernel(const MatDesc *__restric
       sr[u] = cmul(f.sr[u], f.r[u]);
       t[u] = csel(m <= c, cz(-f.q[u].x, -f.q[u].y), cz(0.0, 0.0));
     }
-    panel_mul(lh, sr, y);
-    panel_rsolve<0>(t, y, f.yinv, c);
+    mul16(lh, sr, y);
+    rsolve16<0>(t, y, f.yinv, c);
     const int o = k0 % nbo;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
