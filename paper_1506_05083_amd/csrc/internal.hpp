@@ -374,6 +374,13 @@ void launch_dots(int nw, int nvec, int n, const double2 *V, size_t ldv_w, size_t
                  const double2 *z, double2 *h, hipStream_t s);
 void launch_update(int nw, int nvec, int n, const double2 *V, size_t ldv_w, size_t ldv_i,
                    double2 *z, const double2 *h, int hstride, hipStream_t s);
+// basis column of each wave or slot, by value to the kernels (none if negative)
+struct SlotCols {
+  int j[16];
+};
+void launch_normalize(int nw, int n, const double2 *z, const SlotCols &c, double2 *V, size_t ldw, double2 *xin,
+                      const double2 *hn, hipStream_t s);
+void launch_slot_in(int nw, int n, const SlotCols &c, const double2 *V, size_t ldw, double2 *xin, hipStream_t s);
 void launch_axpby_op(int nw, int n, const double2 *x, const double2 *g, const double2 *bd,
                      double2 *out, hipStream_t s);
 void launch_combine_walls(int nw, int M1sq, const double2 *in, double2 *out, hipStream_t s);

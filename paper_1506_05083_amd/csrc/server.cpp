@@ -281,9 +281,8 @@ void iter_loop(mfs_server *sv) {
     double2 *V = S.V.as<double2>();
     double2 *Zb = S.Z.as<double2>();
     double2 *Hd = S.H1.as<double2>();
-    double *SCd = S.SC.as<double>();
-    std::vector<double2> hbuf((size_t)W * (maxit + 2) * 2);
-    std::vector<double> scale(W, 0.0);
+    PinnedBuf hpin((size_t)W * (maxit + 2) * 2 * sizeof(double2));
+    double2 *hbuf = static_cast<double2 *>(hpin.p);
     bool descs_dirty = true;
     for (;;) {
       std::vector<int> act;
@@ -326,14 +325,14 @@ void iter_loop(mfs_server *sv) {
         descs_dirty = false;
       }
       // current vector of every iterating slot (zero elsewhere) -> operator
-      launch_zero(S.XIN.as<double2>(), (long)W * MP, s);
       int jmax = 0;
+      SlotCols cur;
+      std::fill(std::begin(cur.j), std::end(cur.j), -1);
       for (int k : act) {
-        const Slot &sl = sv->slots[k];
-        jmax = std::max(jmax, sl.j);
-        HIP_CHECK(hipMemcpyAsync(S.XIN.as<double2>() + (size_t)k * MP, V + (size_t)k * ldw + (size_t)sl.j * MP,
-                                 MP * sizeof(double2), hipMemcpyDeviceToDevice, s));
+        cur.j[k] = sv->slots[k].j;
+        jmax = std::max(jmax, cur.j[k]);
       }
+      launch_slot_in(W, MP, cur, V, ldw, S.XIN.as<double2>(), s);
       S.apply_op(S.XIN.as<double2>(), Zb);
       // CGS2 against each slot's basis (columns past a slot's count are zero)
       const int nv = jmax + 1;
@@ -344,11 +343,12 @@ void iter_loop(mfs_server *sv) {
       launch_update(W, nv, MP, V, ldw, MP, Zb, h2, nv, s);
       double2 *hnp = h2 + (size_t)W * nv;
       launch_dots(W, 1, MP, Zb, (size_t)MP, 0, Zb, hnp, s);
-      HIP_CHECK(hipMemcpyAsync(hbuf.data(), Hd, (size_t)W * (2 * nv + 1) * sizeof(double2), hipMemcpyDeviceToHost,
-                               s));
+      HIP_CHECK(hipMemcpyAsync(hbuf, Hd, (size_t)W * (2 * nv + 1) * sizeof(double2), hipMemcpyDeviceToHost, s));
+      // the next basis vectors, of slots that finish here too (not read)
+      for (int k : act) ++cur.j[k];
+      launch_normalize(W, MP, Zb, cur, V, ldw, nullptr, hnp, s);
       HIP_CHECK(hipStreamSynchronize(s));
       std::vector<int> fin;
-      std::fill(scale.begin(), scale.end(), 0.0);
       for (int k : act) {
         Slot &sl = sv->slots[k];
         const int j = sl.j;
@@ -390,14 +390,7 @@ void iter_loop(mfs_server *sv) {
         sl.resid = std::abs(sl.g[j + 1]) / sl.beta0;
         sl.j = j + 1;
         if (sl.resid <= sv->cfg.tol || hnext <= 1e-300 || sl.j >= maxit) fin.push_back(k);
-        else scale[k] = 1.0 / hnext;
       }
-      upload(SCd, scale.data(), W * sizeof(double), s);
-      for (int k : act)
-        if (scale[k] != 0.0) {
-          const Slot &sl = sv->slots[k];
-          launch_scale(1, MP, Zb + (size_t)k * MP, MP, V + (size_t)k * ldw + (size_t)sl.j * MP, ldw, SCd + k, s);
-        }
       if (fin.empty()) continue;
       // recovery of the finished slots (the others ride along with zero coefficients)
       std::vector<std::vector<cplx>> y(W);

@@ -140,22 +140,24 @@ extern "C" mfs_status mfs_solve_incident(mfs_ctx *ctx, const mfs_op *op, int32_t
     double2 *V = S.V.as<double2>();
     double2 *Zb = S.Z.as<double2>();
     double2 *Hd = S.H1.as<double2>();
-    double *SCd = S.SC.as<double>();
     // host side of the per-iteration exchange in pinned memory (DMA copies, no staging)
-    PinnedBuf hpin((size_t)W * (maxit + 2) * 2 * sizeof(double2) + (size_t)W * sizeof(double));
+    PinnedBuf hpin((size_t)W * (maxit + 2) * 2 * sizeof(double2));
     double2 *hbuf = static_cast<double2 *>(hpin.p);
-    double *scale = reinterpret_cast<double *>(hbuf + (size_t)W * (maxit + 2) * 2);
+    SlotCols next{};   // the basis vector that each wave's normalised one becomes
     // ||f||
     launch_dots(W, 1, MP, FH.as<double2>(), (size_t)MP, 0, FH.as<double2>(), Hd, s);
     HIP_CHECK(hipMemcpyAsync(hbuf, Hd, W * sizeof(double2), hipMemcpyDeviceToHost, s));
-    HIP_CHECK(hipStreamSynchronize(s));
+    hipEvent_t copied;
+    HIP_CHECK(hipEventCreateWithFlags(&copied, hipEventDisableTiming));
+    struct EventGuard {
+      hipEvent_t e;
+      ~EventGuard() { (void)hipEventDestroy(e); }
+    } copied_guard{copied};
+    HIP_CHECK(hipEventRecord(copied, s));
+    launch_normalize(W, MP, FH.as<double2>(), next, V, ldw, S.XIN.as<double2>(), Hd, s);
+    HIP_CHECK(hipEventSynchronize(copied));
     std::vector<double> beta0(W);
-    for (int w = 0; w < W; ++w) {
-      beta0[w] = std::sqrt(std::max(hbuf[w].x, 0.0));
-      scale[w] = beta0[w] > 0 ? 1.0 / beta0[w] : 0.0;
-    }
-    upload(SCd, scale, W * sizeof(double), s);
-    launch_scale2(W, MP, FH.as<double2>(), MP, V, ldw, S.XIN.as<double2>(), MP, SCd, s);
+    for (int w = 0; w < W; ++w) beta0[w] = std::sqrt(std::max(hbuf[w].x, 0.0));
     std::vector<std::vector<cplx>> H(W, std::vector<cplx>((size_t)(maxit + 1) * maxit, 0.0));
     std::vector<std::vector<double>> cs(W, std::vector<double>(maxit, 0.0));
     std::vector<std::vector<cplx>> sn(W, std::vector<cplx>(maxit, 0.0)), g(W, std::vector<cplx>(maxit + 1, 0.0));
@@ -194,10 +196,13 @@ extern "C" mfs_status mfs_solve_incident(mfs_ctx *ctx, const mfs_op *op, int32_t
       launch_dots(W, 1, MP, Zb, (size_t)MP, 0, Zb, hn, s);
       HIP_CHECK(hipMemcpyAsync(hbuf, Hd, (size_t)W * (2 * nv + 1) * sizeof(double2),
                                hipMemcpyDeviceToHost, s));
-      HIP_CHECK(hipStreamSynchronize(s));
+      HIP_CHECK(hipEventRecord(copied, s));
+      // the next vectors, of converged waves too (their coefficients are not read any more)
+      for (int w = 0; w < W; ++w) next.j[w] = j + 1;
+      launch_normalize(W, MP, Zb, next, V, ldw, S.XIN.as<double2>(), hn, s);
+      HIP_CHECK(hipEventSynchronize(copied));
       any_active = false;
       for (int w = 0; w < W; ++w) {
-        scale[w] = 0.0;
         if (!active[w]) continue;
         for (int i = 0; i < nv; ++i) {
           const double2 a1 = hbuf[(size_t)w * nv + i], a2 = hbuf[(size_t)W * nv + (size_t)w * nv + i];
@@ -232,7 +237,6 @@ extern "C" mfs_status mfs_solve_incident(mfs_ctx *ctx, const mfs_op *op, int32_t
           solve_y(w, j + 1);
         } else {
           any_active = true;
-          scale[w] = 1.0 / hnext;
         }
       }
       jdone = j + 1;
@@ -240,10 +244,6 @@ extern "C" mfs_status mfs_solve_incident(mfs_ctx *ctx, const mfs_op *op, int32_t
         double worst = 0.0;
         for (int w = 0; w < W; ++w) worst = std::max(worst, resid[w]);
         progress("GMRES iteration %d: largest relative residual %.2e", j + 1, worst);
-      }
-      if (any_active) {
-        upload(SCd, scale, W * sizeof(double), s);
-        launch_scale2(W, MP, Zb, MP, V + (size_t)(j + 1) * MP, ldw, S.XIN.as<double2>(), MP, SCd, s);
       }
     }
     bool notconv = false;

@@ -67,7 +67,7 @@ struct Solver {
   DevBuf EG, EW, EM, EO, EP;
   int ldo = 0;
   // work
-  DevBuf V, Z, XIN, C, SIG, GS, GH, WR, CY, XIH, XI, PART, PART2, YW, H1, SC;
+  DevBuf V, Z, XIN, C, SIG, GS, GH, WR, CY, XIH, XI, PART, PART2, YW, H1;
   int nsplit_s = 1, nsplit_w = 1;
   // timing: events around every neighbour-sum launch, the dense bytes each streamed
   std::vector<hipEvent_t> nsum_ev;
@@ -329,7 +329,6 @@ struct Solver {
     upload_orders();
     YW.alloc(std::max((size_t)b.nd * 2 * W * Nc, (size_t)2 * W * NQh) * sizeof(double2));
     H1.alloc((size_t)W * (maxit + 2) * 2 * sizeof(double2));
-    SC.alloc((size_t)W * sizeof(double));
   }
 
   const MatDesc *qpinv_descs() const { return qdesc ? qdesc : gp.apply_descs(); }
