@@ -36,7 +36,6 @@ namespace {
 
 constexpr int CH = 256;     // rows per workgroup in the panel column step
 constexpr int KRMIN = 64;   // fewest rows of a V^H Y split-K slice
-constexpr int VHYWG = 256;  // workgroups a V^H Y launch aims at by cutting its slices shorter
 constexpr int KS = 16;      // rows per LDS stage in V^H Y
 // V^H Y tiles: YT columns of Y a workgroup, a wave IB x CB blocks of 16 x 16
 // of the NB x YT tile, OCC waves a SIMD, DB: LDS stages double-buffered (one
@@ -1104,26 +1103,42 @@ __global__ __launch_bounds__(256, 3) void bqr_update_kernel(const MatDesc *__res
     }
 }
 
-// Rows of a V^H Y slice: VhyShape's, halved down to 64 while the workgroups of
-// an average panel of the factorisation would leave compute units idle (4
-// matrices of 1600 x 400: the 64-wide launch 89 -> 23 us, a solve of two waves
-// 8.5 -> 7.7 ms; aims of 512 and 1024 workgroups 7.9 ms; 16 of 2304 x 650 the same
-// from 1 to 1024).
-int vhy_slice_rows(int nb, int nmat, int mmax, int ncols) {
-  int kr = nb == 64 ? VhyShape<64>::KR : (nb == 32 ? VhyShape<32>::KR : VhyShape<16>::KR);
-  while (kr > KRMIN && (long)cdiv(nb + ncols / 2, 64) * cdiv(std::max(mmax, 1), kr) * nmat < VHYWG) kr /= 2;
-  return kr;
+// Rows of a V^H Y slice for `rows` rows and ny columns of Y: VhyShape's or shorter,
+// down to 64, by what a launch takes.  A compute unit with one workgroup needs
+// 1.3 of a workgroup's share of one that is full, with q of them q; a slice has a
+// cost of 40 rows, and another slice costs W2 and T that add it 3 rows.  4
+// matrices of 4096 x 1472, 46 launches with 24 to 736 workgroups of 512 rows:
+// 7.2 -> 5.9 ms, W2 and T 1.5 -> 1.8 (one choice for a whole factorisation by its
+// average panel before).
+int vhy_slice_rows(int nb, int nmat, int rows, int ny) {
+  int best = nb == 64 ? VhyShape<64>::KR : (nb == 32 ? VhyShape<32>::KR : VhyShape<16>::KR);
+  double cost = 0.0;
+  for (int kr = best; kr >= KRMIN; kr /= 2) {
+    const int nkc = cdiv(std::max(rows, 1), kr);
+    const long q = ((long)cdiv(std::max(ny, 1), 64) * nkc * nmat + 255) / 256;
+    if (q > 4 && cost == 0.0) break;   // full as it is
+    const double c = (q <= 1 ? 1.3 : (double)q) * (kr + 40) + 3.0 * nkc;
+    if (cost == 0.0 || c < cost) {
+      cost = c;
+      best = kr;
+    }
+  }
+  return best;
 }
 
 struct ApplyWork {
   DevBuf P, W2;
-  int ldp = 0, ldw = 0, nkcmax = 0, kr = 0;
+  int ldw = 0;
+  // P for the panels of a factorisation of ncols columns or an application to
+  // them (apply_panel enlarges it for a panel that needs more)
   void size(int nmat, int mmax, int ncols, int nb) {
-    ldp = nb + ncols;
     ldw = std::max(ncols, 1);
-    kr = vhy_slice_rows(nb, nmat, mmax, ncols);
-    nkcmax = cdiv(std::max(mmax, 1), kr);
-    P.alloc((size_t)nmat * nkcmax * nb * ldp * sizeof(double2));
+    size_t most = 0;
+    for (int k0 = 0; k0 == 0 || k0 < ncols; k0 += nb) {
+      const int ny = nb + ncols - k0;
+      most = std::max(most, (size_t)cdiv(std::max(mmax - k0, 1), vhy_slice_rows(nb, nmat, mmax - k0, ny)) * ny);
+    }
+    P.alloc((size_t)nmat * most * nb * sizeof(double2));
     W2.alloc((size_t)nmat * nb * ldw * sizeof(double2));
   }
 };
@@ -1137,17 +1152,19 @@ void apply_panel(const MatDesc *descs, int nmat, int mmax, int ncols_max, int k0
                  int trans, ApplyWork &w, bool build_t, hipStream_t s, int cend = kNoEnd,
                  double2 *Tx = nullptr, int diag = 0) {
   const int ny = (withV ? NB : 0) + ncols_max;
-  const int nkc = cdiv(std::max(mmax - k0, 1), w.kr);
+  const int kr = vhy_slice_rows(NB, nmat, mmax - k0, ny), nkc = cdiv(std::max(mmax - k0, 1), kr);
+  const size_t need = (size_t)nmat * nkc * NB * ny * sizeof(double2);
+  if (w.P.bytes < need) w.P.alloc(need);
   if (ny > 0)
     hipLaunchKernelGGL(bqr_vhy_kernel<NB>, dim3(cdiv(ny, VhyShape<NB>::YT), nkc, nmat), dim3(256), 0, s, descs, k0, which, withV,
-                       cend, w.P.as<double2>(), w.ldp, w.nkcmax, w.kr);
+                       cend, w.P.as<double2>(), ny, nkc, kr);
   if (build_t)
-    hipLaunchKernelGGL(bqr_t_kernel<NB>, dim3(nmat), dim3(TThreads<NB>::N), 0, s, descs, k0, w.P.as<double2>(), w.ldp,
-                       w.nkcmax, Tx, w.kr, diag);
+    hipLaunchKernelGGL(bqr_t_kernel<NB>, dim3(nmat), dim3(TThreads<NB>::N), 0, s, descs, k0, w.P.as<double2>(), ny, nkc,
+                       Tx, kr, diag);
   if (ncols_max > 0) {
     const int w2x = std::min(cdiv(ncols_max, W2T), std::max(1, cdiv(W2WG, nmat)));
     hipLaunchKernelGGL(bqr_w2_kernel<NB>, dim3(w2x, nmat), dim3(256), 0, s, descs, k0, which,
-                       withV, trans, cend, w.P.as<double2>(), w.ldp, w.nkcmax, w.W2.as<double2>(), w.ldw, Tx, w.kr);
+                       withV, trans, cend, w.P.as<double2>(), ny, nkc, w.W2.as<double2>(), w.ldw, Tx, kr);
     hipLaunchKernelGGL(bqr_update_kernel<NB>,
                        dim3(cdiv(ncols_max, UpdShape::UC), cdiv(std::max(mmax - k0, 1), UpdShape::UR), nmat),
                        dim3(256), 0, s, descs, k0, which, cend, w.W2.as<double2>(), w.ldw);
