@@ -695,8 +695,7 @@ mfs_status mfs_neighbour_sum(const mfs_op *op, int32_t body, const mfs_lattice *
   if (target_set == MFS_TARGETS_WALLS) {
     launch_combine_walls(nrhs, lat->M1 * lat->M1, res, o, s);
   } else {
-    for (int r = 0; r < nrhs; ++r)
-      HIP_CHECK(hipMemcpyAsync(o + (size_t)r * nout, res + (size_t)r * ntp, nout * sizeof(double2),
+    HIP_CHECK(hipMemcpy2DAsync(o, nout * sizeof(double2), res, ntp * sizeof(double2), nout * sizeof(double2), nrhs,
                                hipMemcpyDeviceToDevice, s));
   }
   HIP_CHECK(hipStreamSynchronize(s));
@@ -732,9 +731,8 @@ void ring_field(const BodyData &b, double kk, const std::vector<double> &srho, c
   launch_nsum(plan, nrhs, kk, 1.0, 1.0, srcbuf.as<double>(), S, sig.as<double2>(), wd.as<double2>(), res,
               res + (size_t)nrhs * ntp, s);
   double2 *o = reinterpret_cast<double2 *>(out);
-  for (int r = 0; r < nrhs; ++r)
-    HIP_CHECK(hipMemcpyAsync(o + (size_t)r * ntargets, res + (size_t)r * ntp, ntargets * sizeof(double2),
-                             hipMemcpyDeviceToDevice, s));
+  HIP_CHECK(hipMemcpy2DAsync(o, ntargets * sizeof(double2), res, ntp * sizeof(double2), ntargets * sizeof(double2),
+                             nrhs, hipMemcpyDeviceToDevice, s));
   HIP_CHECK(hipStreamSynchronize(s));
 }
 }  // namespace

@@ -90,6 +90,61 @@ __device__ inline double2 ld_or0(const double2 *p, size_t i, bool ok) {
             __longlong_as_double(__double_as_longlong(v.y) & m));
 }
 
+// ----------------------------------------------------- kernel values
+// A constant in scalar registers: the third operand of a fused multiply-add
+// there, where the compiler would keep it in vector registers and copy it.
+__device__ inline double scalar_const(double v) {
+  asm("" : "+s"(v));
+  return v;
+}
+
+// sin and cos of x, |x| <= kPhaseMax: x - n pi/2 in two terms of pi/2, the first
+// difference exact with a fused multiply-add (a multiple of 2^-52 below 1), what
+// rounding the second leaves off carried along; Taylor polynomials to r^17 and
+// r^16 on |r| <= pi/4 (remainders under 1e-19), and the quadrant.  The largest
+// error over 2e7 arguments is 0.95e-16.  (The library's sincos serves every
+// argument, with a reduction that takes 50 registers beside it.)
+constexpr double kPhaseMax = 1e15;
+__device__ inline void sincos_mid(double x, double *sn, double *cs) {
+  const double n = rint(x * scalar_const(0.63661977236758134308));
+  const double p2 = scalar_const(-6.12323399573676603587e-17);
+  const double t = fma(n, scalar_const(-1.57079632679489655800), x);
+  const double r = fma(n, p2, t);
+  const double rl = fma(n, p2, t - r);
+  const double r2 = r * r;
+  double s = fma(r2, scalar_const(1.0 / 355687428096000.0), -1.0 / 1307674368000.0);
+  s = fma(r2, s, scalar_const(1.0 / 6227020800.0));
+  s = fma(r2, s, scalar_const(-1.0 / 39916800.0));
+  s = fma(r2, s, scalar_const(1.0 / 362880.0));
+  s = fma(r2, s, scalar_const(-1.0 / 5040.0));
+  s = fma(r2, s, scalar_const(1.0 / 120.0));
+  s = fma(r2, s, scalar_const(-1.0 / 6.0));
+  s = r + fma(r * r2, s, rl);
+  double c = fma(r2, scalar_const(1.0 / 20922789888000.0), -1.0 / 87178291200.0);
+  c = fma(r2, c, scalar_const(1.0 / 479001600.0));
+  c = fma(r2, c, scalar_const(-1.0 / 3628800.0));
+  c = fma(r2, c, scalar_const(1.0 / 40320.0));
+  c = fma(r2, c, scalar_const(-1.0 / 720.0));
+  c = fma(r2, c, scalar_const(1.0 / 24.0));
+  const double w = fma(-0.5, r2, 1.0);   // cos r = w + (the rest of 1 - r^2 / 2) + ...
+  c = w + fma(r2 * r2, c, fma(-r, rl, fma(-0.5, r2, 1.0 - w)));
+  const int q = (int)fma(floor(n * 0.25), -4.0, n);   // n mod 4
+  const double a = (q & 1) ? c : s, b = (q & 1) ? s : c;
+  *sn = __hiloint2double(__double2hiint(a) ^ (int)((unsigned)(q & 2) << 30), __double2loint(a));
+  *cs = __hiloint2double(__double2hiint(b) ^ (int)((unsigned)((q + 1) & 2) << 30), __double2loint(b));
+}
+
+// R = sqrt(r2) and 1 / R of a squared distance: the hardware's estimate of
+// 1 / R (good to 2^-23) with one cubic step, and R = r2 / R corrected to half
+// an ulp (it becomes the phase k R)
+__device__ inline double dist(double r2, double &inv) {
+  const double y = __builtin_amdgcn_rsq(r2);
+  const double e = fma(-r2 * y, y, 1.0);
+  inv = fma(y * e, fma(e, 0.375, 0.5), y);
+  const double r = r2 * inv;
+  return fma(fma(-r, r, r2), 0.5 * inv, r);
+}
+
 // ----------------------------------------------------- FP64 matrix cores
 // One v_mfma_f64_16x16x4f64: D = A B + C with A 16 x 4 (lane i + 16 k holds
 // A[i][k]), B 4 x 16 (lane j + 16 k holds B[k][j]) and C, D 16 x 16 (lane

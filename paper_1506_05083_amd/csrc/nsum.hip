@@ -57,10 +57,9 @@ __device__ inline double2 near_kernel(double ddx, double ddy, double ddz, double
                                       double k, int deriv) {
   const double inv4pi = 0.25 / kPi;
   const double R2 = fma(ddx, ddx, fma(ddy, ddy, ddz * ddz));
-  const double invR = rsqrt(R2);
-  const double R = R2 * invR;
-  double sn, cs;
-  sincos(k * R, &sn, &cs);
+  double invR, sn, cs;
+  const double R = dist(R2, invR);
+  sincos_mid(fmin(k * R, kPhaseMax), &sn, &cs);   // farther, a rounded distance has no phase
   if (deriv) {
     const double dn = fma(tx, ddx, fma(ty, ddy, tz * ddz));
     const double tt = dn * invR * invR * inv4pi;
@@ -70,6 +69,11 @@ __device__ inline double2 near_kernel(double ddx, double ddy, double ddz, double
   return cz(cs * tt, sn * tt);
 }
 
+// Few right-hand sides: lane = target, the four waves of a workgroup split its
+// slice of the sources.  Bound by the evaluation's FP64 instructions, about 80 a
+// pair, and 8 a pair and right-hand side with its mirror: 3 of them on 15360
+// targets and 12800 sources 3.45 -> 2.70 ms with sincos_mid for the library's sincos
+// (half its instructions and registers) and the sums of 3 instead of 4.
 // With MIR (every group mirror-paired, NsumGroup::pkind) a workgroup takes
 // the primary targets of its tile (the first mt of the surface, all of the
 // first wall of a cross pair, the first half of a self-paired wall, none of a
@@ -190,6 +194,136 @@ __global__ __launch_bounds__(256) void nsum_kernel(const double *__restrict__ tg
       } else if (q >= g.nt) {
         row[tile * 64 + l] = cz(0.0, 0.0);
       }
+    }
+  }
+}
+
+// Many right-hand sides: the sum over the sources is a product of the kernel
+// values (targets x sources) with the weighted strengths (sources x right-hand
+// sides), on the FP64 matrix cores: a wave takes 16 targets, step s the sources
+// 4 s + k, and a lane evaluates the pair (target lane % 16, k = lane / 16), which is
+// its A operand.  The columns of B are the real and
+// imaginary parts of every right-hand side, times the image's weight: for the
+// values' real part (re, im), for their imaginary part (-im, re).  16 columns a
+// block, NB blocks.
+// With MIR the columns' second half are the mirror targets' (as in nsum_kernel).
+// The matrix cores share the vector units' FP64 rate, so a column costs what its
+// multiply-adds cost, but the sums take 16 registers a block for 8 (4 with MIR)
+// right-hand sides where the vector form takes 8 (16) each: 16 waves at 1000 points
+// 291 us, 371 with the sums on the vector units (two waves a SIMD), 410 with the
+// library's sincos besides; 3 right-hand sides with MIR 2.77 ms, 2.73.  Every
+// image is summed apart.
+template <int NB, bool MIR>
+__global__ __launch_bounds__(256) void nsum_mfma_kernel(const double *__restrict__ tgt, int ntp,
+                                                   const NsumGroup *__restrict__ groups,
+                                                   const int *__restrict__ tile_group, int nrhs,
+                                                   double k, double ex, double ey,
+                                                   const double *__restrict__ src, int S,
+                                                   const double2 *__restrict__ sigma,
+                                                   const double2 *__restrict__ wts, int nsplit,
+                                                   double2 *__restrict__ out) {
+  constexpr int CW = 16 * NB, NR = MIR ? 4 * NB : 8 * NB, SC = 64 / NB;
+  __shared__ double sx[SC], sy[SC], sz[SC];
+  __shared__ double2 b1[SC][CW / 2 + 1], b2[SC][CW / 2 + 1];   // odd row strides: no bank conflicts
+  const int tile = blockIdx.x;
+  const int split = blockIdx.y;
+  const int gi = tile_group[tile];
+  const NsumGroup g = groups[gi];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int tl = tile * 64 - g.t0;   // first target of the tile within its group
+  const int nprim = MIR ? pair_primaries(g) : 0;
+  if (MIR && tl >= nprim) {
+    for (int idx = threadIdx.x; idx < NR * 64; idx += 256) {
+      const int r = idx / 64, l = idx % 64;
+      if (r < nrhs && tl + l >= g.nt) out[((size_t)split * nrhs + r) * ntp + tile * 64 + l] = cz(0.0, 0.0);
+    }
+    return;
+  }
+  const int c16 = lane & 15, k4 = lane >> 4;
+  const int t = tile * 64 + 16 * wv + c16;
+  const bool work = !MIR || tl + 16 * wv < nprim;   // uniform over the wave
+  const double xt = tgt[t], yt = tgt[ntp + t], zt = tgt[2 * ntp + t];
+  const double dxt = tgt[3 * ntp + t], dyt = tgt[4 * ntp + t], dzt = tgt[5 * ntp + t];
+  const int per = (S + nsplit - 1) / nsplit;
+  const int s_begin = split * per;
+  const int s_end = min(S, s_begin + per);
+  dx4 tot[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) tot[nb] = dx4{0.0, 0.0, 0.0, 0.0};
+  for (int im = 0; im < g.nimg; ++im) {
+    dx4 acc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = dx4{0.0, 0.0, 0.0, 0.0};
+    const double xs = xt - groups[gi].ia[im] * ex, ys = yt - groups[gi].ib[im] * ey;
+    const int jm = MIR ? groups[gi].mir[im] : 0;
+    for (int c0 = s_begin; c0 < s_end; c0 += SC) {
+      const int nc = min(SC, s_end - c0);
+      __syncthreads();
+      for (int idx = threadIdx.x; idx < SC; idx += 256) {
+        const int s = c0 + idx;
+        const bool ok = idx < nc;
+        sx[idx] = ok ? src[s] : 0.0;
+        sy[idx] = ok ? src[S + s] : 0.0;
+        sz[idx] = ok ? src[2 * S + s] : 1e3;   // far dummy source, zero strength
+      }
+      for (int idx = threadIdx.x; idx < SC * CW / 2; idx += 256) {
+        const int ss = idx % SC, rc = idx / SC;
+        const bool mirror = MIR && rc >= NR;
+        const int r = mirror ? rc - NR : rc;
+        double2 v = cz(0.0, 0.0);
+        if (r < nrhs && ss < nc) {
+          int s = c0 + ss;
+          double2 w = wts[((size_t)gi * 9 + im) * nrhs + r];
+          if (mirror) {
+            s += s + g.ms >= S ? g.ms - S : g.ms;
+            w = cscale(wts[((size_t)g.pg * 9 + jm) * nrhs + r], (double)g.psign);
+          }
+          v = cmul(w, sigma[(size_t)r * S + s]);
+        }
+        b1[ss][rc] = v;
+        b2[ss][rc] = cz(-v.y, v.x);
+      }
+      __syncthreads();
+      if (work) {
+#pragma unroll 2
+        for (int s0 = 0; s0 < SC; s0 += 4) {
+          const int ss = s0 + k4;
+          const double2 K = near_kernel(xs - sx[ss], ys - sy[ss], zt - sz[ss], dxt, dyt, dzt, k, g.deriv);
+          const double *p1 = reinterpret_cast<const double *>(b1[ss]), *p2 = reinterpret_cast<const double *>(b2[ss]);
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) {
+            acc[nb] = mfma_f64(K.x, p1[16 * nb + c16], acc[nb]);
+            acc[nb] = mfma_f64(K.y, p2[16 * nb + c16], acc[nb]);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) tot[nb] += acc[nb];
+  }
+  // lane c16 + 16 k4 holds target k4 + 4 v of its wave's 16, column 16 nb + c16
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int col = 16 * nb + c16;
+    const bool mirror = MIR && col / 2 >= NR;
+    const int r = mirror ? col / 2 - NR : col / 2;
+    if (r >= nrhs) continue;
+    double2 *row = out + ((size_t)split * nrhs + r) * ntp;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int l = 16 * wv + k4 + 4 * v, q = tl + l;   // q: group-local target
+      double x = tot[nb][v];
+      int at = tile * 64 + l;
+      if (MIR) {
+        if (mirror) {
+          if (q >= nprim) continue;
+          at = pair_target(groups, g, q);
+        } else if (q >= nprim) {
+          if (q < g.nt) continue;
+          x = 0.0;
+        }
+      }
+      reinterpret_cast<double *>(row + at)[col & 1] = x;
     }
   }
 }
@@ -483,14 +617,23 @@ __global__ __launch_bounds__(256, NR == 8 ? 4 : 2) void nsum_dense_mirror_mfma_k
   }
 }
 
-__global__ void nsum_reduce(int nsplit, int nrhs, int ntp, const double2 *__restrict__ part,
-                            double2 *__restrict__ out) {
-  const long n = (long)nrhs * ntp;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    double2 v = part[i];
-    for (int s = 1; s < nsplit; ++s) v = cadd(v, part[(size_t)s * n + i]);
-    out[i] = v;
-  }
+// The slices of a sum added: 16 threads an output, each every 16th slice (one
+// thread an output is a chain of nsplit loads: 131 us of a small body's 0.2 ms sum
+// over 50 slices).
+__global__ __launch_bounds__(1024) void nsum_reduce(int nsplit, int nrhs, int ntp, const double2 *__restrict__ part,
+                                                    double2 *__restrict__ out) {
+  __shared__ double2 red[16][64];
+  const long n = (long)nrhs * ntp, i = (long)blockIdx.x * 64 + (threadIdx.x & 63);
+  const int q = threadIdx.x >> 6;
+  double2 v = cz(0.0, 0.0);
+#pragma unroll 4
+  for (int s = q; s < nsplit; s += 16) v = cadd(v, ld_or0(part, (size_t)s * n + i, i < n));
+  red[q][threadIdx.x & 63] = v;
+  __syncthreads();
+  if (q > 0 || i >= n) return;
+#pragma unroll
+  for (int j = 1; j < 16; ++j) v = cadd(v, red[j][threadIdx.x]);
+  out[i] = v;
 }
 
 // Wall rows of C from the 12 padded target groups (R L Rx Lx F B Fy By T Tz D Dz):
@@ -564,21 +707,24 @@ void launch_nsum_dense_t(const NsumPlan &plan, int nrhs, int S, const double2 *s
   HIP_CHECK(hipGetLastError());
 }
 
-template <int NR>
+template <int NB, bool MIR>
+void launch_nsum_mfma_t(const NsumPlan &plan, int nrhs, double k, double ex, double ey, const double *src, int S,
+                        const double2 *sigma, const double2 *w, int nsplit, double2 *dst, hipStream_t s) {
+  hipLaunchKernelGGL((nsum_mfma_kernel<NB, MIR>), dim3(plan.ntarget_pad / 64, nsplit), dim3(256), 0, s,
+                     plan.tgt.as<double>(), plan.ntarget_pad, plan.grp.as<NsumGroup>(),
+                     plan.tile_group.as<int>(), nrhs, k, ex, ey, src, S, sigma, w, nsplit, dst);
+  HIP_CHECK(hipGetLastError());
+}
+
+template <int NR, bool MIR>
 void launch_nsum_t(const NsumPlan &plan, int nrhs, double k, double ex, double ey,
                    const double *src, int S, const double2 *sigma, const double2 *w,
                    int nsplit, double2 *dst, hipStream_t s) {
-  const bool mir = plan_mirrored(plan, false);
-  const size_t sh = std::max((size_t)(3 * SC) * sizeof(double) + (size_t)(mir ? 2 : 1) * NR * SC * sizeof(double2),
+  const size_t sh = std::max((size_t)(3 * SC) * sizeof(double) + (size_t)(MIR ? 2 : 1) * NR * SC * sizeof(double2),
                              (size_t)4 * NR * 64 * sizeof(double2));
-  if (mir)
-    hipLaunchKernelGGL((nsum_kernel<NR, true>), dim3(plan.ntarget_pad / 64, nsplit), dim3(256), sh, s,
-                       plan.tgt.as<double>(), plan.ntarget_pad, plan.grp.as<NsumGroup>(),
-                       plan.tile_group.as<int>(), nrhs, k, ex, ey, src, S, sigma, w, nsplit, dst);
-  else
-    hipLaunchKernelGGL((nsum_kernel<NR, false>), dim3(plan.ntarget_pad / 64, nsplit), dim3(256), sh, s,
-                       plan.tgt.as<double>(), plan.ntarget_pad, plan.grp.as<NsumGroup>(),
-                       plan.tile_group.as<int>(), nrhs, k, ex, ey, src, S, sigma, w, nsplit, dst);
+  hipLaunchKernelGGL((nsum_kernel<NR, MIR>), dim3(plan.ntarget_pad / 64, nsplit), dim3(256), sh, s,
+                     plan.tgt.as<double>(), plan.ntarget_pad, plan.grp.as<NsumGroup>(),
+                     plan.tile_group.as<int>(), nrhs, k, ex, ey, src, S, sigma, w, nsplit, dst);
   HIP_CHECK(hipGetLastError());
 }
 
@@ -624,15 +770,33 @@ void launch_nsum(const NsumPlan &plan, int nrhs, double k, double ex, double ey,
     else if (nrhs <= 4) launch_nsum_dense_t<4>(plan, nrhs, S, sigma, w, nsplit, dst, s);
     else if (nrhs <= 8) launch_nsum_dense_t<8>(plan, nrhs, S, sigma, w, nsplit, dst, s);
     else launch_nsum_dense_t<16>(plan, nrhs, S, sigma, w, nsplit, dst, s);
-  } else if (nrhs <= 1) launch_nsum_t<1>(plan, nrhs, k, ex, ey, src, S, sigma, w, nsplit, dst, s);
-  else if (nrhs <= 2) launch_nsum_t<2>(plan, nrhs, k, ex, ey, src, S, sigma, w, nsplit, dst, s);
-  else if (nrhs <= 4) launch_nsum_t<4>(plan, nrhs, k, ex, ey, src, S, sigma, w, nsplit, dst, s);
-  else if (nrhs <= 8) launch_nsum_t<8>(plan, nrhs, k, ex, ey, src, S, sigma, w, nsplit, dst, s);
-  else launch_nsum_t<16>(plan, nrhs, k, ex, ey, src, S, sigma, w, nsplit, dst, s);
+  } else {
+    // the matrix-core form from where the vector form's sums cost it waves in
+    // flight: more than 4 right-hand sides with their mirrors, more than 6 without
+    using Launch = void (*)(const NsumPlan &, int, double, double, double, const double *, int, const double2 *,
+                            const double2 *, int, double2 *, hipStream_t);
+    Launch f;
+    if (plan_mirrored(plan, false))
+      f = nrhs > 8   ? launch_nsum_mfma_t<4, true>
+          : nrhs > 4 ? launch_nsum_mfma_t<2, true>
+          : nrhs > 3 ? launch_nsum_t<4, true>
+          : nrhs > 2 ? launch_nsum_t<3, true>
+          : nrhs > 1 ? launch_nsum_t<2, true>
+                     : launch_nsum_t<1, true>;
+    else
+      f = nrhs > 8   ? launch_nsum_mfma_t<2, false>
+          : nrhs > 6 ? launch_nsum_mfma_t<1, false>
+          : nrhs > 4 ? launch_nsum_t<6, false>
+          : nrhs > 3 ? launch_nsum_t<4, false>
+          : nrhs > 2 ? launch_nsum_t<3, false>
+          : nrhs > 1 ? launch_nsum_t<2, false>
+                     : launch_nsum_t<1, false>;
+    f(plan, nrhs, k, ex, ey, src, S, sigma, w, nsplit, dst, s);
+  }
   if (nsplit > 1) {
     const long n = (long)nrhs * plan.ntarget_pad;
-    hipLaunchKernelGGL(nsum_reduce, dim3((unsigned)std::min<long>(2048, (n + 255) / 256)), dim3(256),
-                       0, s, nsplit, nrhs, plan.ntarget_pad, partial, out);
+    hipLaunchKernelGGL(nsum_reduce, dim3((unsigned)((n + 63) / 64)), dim3(1024), 0, s, nsplit, nrhs,
+                       plan.ntarget_pad, partial, out);
     HIP_CHECK(hipGetLastError());
   }
 }
@@ -665,12 +829,12 @@ void launch_nsum_pair(const NsumPlan &pa, const double2 *wa, double2 *outa, doub
   HIP_CHECK(hipGetLastError());
   if (na > 1) {
     const long m = (long)nrhs * pa.ntarget_pad;
-    hipLaunchKernelGGL(nsum_reduce, dim3((unsigned)std::min<long>(2048, (m + 255) / 256)), dim3(256), 0, s, na,
+    hipLaunchKernelGGL(nsum_reduce, dim3((unsigned)((m + 63) / 64)), dim3(1024), 0, s, na,
                        nrhs, pa.ntarget_pad, parta, outa);
   }
   if (nb > 1) {
     const long m = (long)nrhs * pb.ntarget_pad;
-    hipLaunchKernelGGL(nsum_reduce, dim3((unsigned)std::min<long>(2048, (m + 255) / 256)), dim3(256), 0, s, nb,
+    hipLaunchKernelGGL(nsum_reduce, dim3((unsigned)((m + 63) / 64)), dim3(1024), 0, s, nb,
                        nrhs, pb.ntarget_pad, partb, outb);
   }
   HIP_CHECK(hipGetLastError());
