@@ -281,6 +281,11 @@ void pool_trim(int dev) {
     std::lock_guard<std::mutex> lk(pl.mu);
     trim_locked(pl, 0);
   }
+  {
+    std::lock_guard<std::mutex> lk(g_pinned_mu);
+    for (void *q : pinned_idle()) (void)hipHostFree(q);
+    pinned_idle().clear();
+  }
   if (prev != dev) (void)hipSetDevice(prev);
 }
 
