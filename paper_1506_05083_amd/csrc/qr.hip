@@ -3,9 +3,11 @@
 // periodizing matrix Q of Sec. 4.2), LAPACK's zlarfg convention:
 // H = I - tau v v^H, v(1) = 1, H^H x = beta e_1 with beta real.
 //
-// Panels of NB = 32 columns.  The panel is factorised column by column with
-// one launch per column that spans all rows of all matrices (CH-row chunks,
-// one row per thread, the row's panel entries in registers):
+// Panels of 16 columns, in one launch while a panel's rows fit a workgroup
+// (bqr_panel_kernel), by Cholesky QR where the caller's columns are independent
+// (cq_* kernels), else column by column with one launch per column that spans all
+// rows of all matrices (CH-row chunks, one row per thread, the row's panel entries
+// in registers):
 //   * launch s finishes reflector s from the chunk partial sums written by
 //     launch s-1: |x(2:)|^2 and x^H a_c for the panel columns c > s (so the
 //     reflector and every w_c = v^H a_c follow from one pass over the rows),

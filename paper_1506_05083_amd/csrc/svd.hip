@@ -1020,9 +1020,9 @@ JacStats jac_run(const MatDesc *descs, const std::vector<MatDesc> &h, int init_m
   (void)rel_cutoff;
   int nmax = 0;
   for (const auto &d : h) nmax = std::max(nmax, d.n);
-  // 32-column blocks halve the passes over G and V per sweep (one per block
+  // 32-column blocks halve the passes over G per sweep (one per block
   // round) at the price of an inner problem of twice as many rounds per
-  // task; that pays only once the passes over G and V dominate (measured:
+  // task; that pays only once the passes over G dominate (measured:
   // slower at 600 and 800 columns, faster at several thousand)
   int wide = kJacWideMinCols;
   if (const char *e = getenv("MFS_JACOBI_WIDE_MIN_COLS")) wide = atoi(e);
