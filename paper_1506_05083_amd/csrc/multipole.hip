@@ -79,8 +79,8 @@ __global__ void lattice_sum_kernel(int J, double ex, double ey, const double2 *_
 // downwards from its largest j to a middle j where both directions are stable,
 // multiplying into the waves' lattice sums as it goes; the two runs are
 // matched on two neighbouring j and normalised by sum (2j+1) f^2 = 1, so
-// nothing is stored.  Bound by the recurrence (one division and two square
-// roots a step); the lattice sums are read coalesced, neighbouring lanes
+// nothing is stored.  Bound by the recurrence (a step is one root and its
+// reciprocal, the other quotients from tables in LDS; TRANS); the lattice sums are read coalesced, neighbouring lanes
 // holding neighbouring m' - m.  Consecutive lanes are consecutive rows m of a
 // column, the order T is stored in.
 constexpr int XPMAX = kExpMaxDegree, XJ = 2 * XPMAX + 2;
@@ -90,13 +90,18 @@ __global__ __launch_bounds__(256) void translation_kernel(int W, int J, ExpShape
   const int lp = blockIdx.x, l = blockIdx.y, par = blockIdx.z & 1, w0 = (blockIdx.z >> 1) * WG;
   const int nr = par ? l : l + 1, nc = par ? lp : lp + 1;
   if (nr == 0 || nc == 0) return;
-  __shared__ double ta[XJ], g0[XJ];
+  __shared__ double ta[XJ], g0[XJ], tf[XJ], tb[XJ];
   const int jlo = l > lp ? l - lp : lp - l, jhi = l + lp;
   for (int j = jlo + threadIdx.x; j <= jhi + 1; j += 256) {
     const double d = (double)(l - lp), q = (double)(jhi + 1);
     ta[j] = sqrt(fmax(0.0, ((double)j * j - d * d) * (q * q - (double)j * j)));
   }
   __syncthreads();
+  // 1 / (j a(j+1)) of the step up from j, 1 / ((j+1) a(j)) of the step down
+  for (int j = jlo + threadIdx.x; j <= jhi; j += 256) {
+    tf[j] = 1.0 / ((j == 0 ? 1.0 : (double)j) * ta[j + 1]);
+    tb[j] = 1.0 / ((j + 1.0) * ta[j]);
+  }
   if (threadIdx.x == 0) {   // |(l' l j; 0 0 0)| for even l + l' + j, times sqrt(4 pi (2l+1)(2l'+1)(2j+1))
     double f = 1.0, n = 0.0;
     for (int j = jlo; j <= jhi; j += 2) {
@@ -150,12 +155,13 @@ __global__ __launch_bounds__(256) void translation_kernel(int W, int J, ExpShape
         const double dj = (double)j;
         nf += (2.0 * dj + 1.0) * f * f;
         if ((j & 1) == par_j) add(af, j, f);
-        const double acn = ta[j + 1] * sqrt((dj + 1.0) * (dj + 1.0) - q1);
+        double ci;
+        const double acn = ta[j + 1] * dist((dj + 1.0) * (dj + 1.0) - q1, ci);
         double fn;
-        if (j == 0) fn = -dm * f / acn;
+        if (j == 0) fn = -dm * f * (tf[0] * ci);
         else {
           const double B = -(2.0 * dj + 1.0) * ((c2 - c3) * fm1 - dj * (dj + 1.0) * dm);
-          fn = -(B * f + (dj + 1.0) * ac * fprev) / (dj * acn);
+          fn = -(B * f + (dj + 1.0) * ac * fprev) * (tf[j] * ci);
         }
         fprev = f;
         f = fn;
@@ -168,9 +174,10 @@ __global__ __launch_bounds__(256) void translation_kernel(int W, int J, ExpShape
         const double dj = (double)j;
         nb += (2.0 * dj + 1.0) * g * g;
         if ((j & 1) == par_j) add(ab, j, g);
-        const double acj = ta[j] * sqrt(dj * dj - q1);
+        double ci;
+        const double acj = ta[j] * dist(dj * dj - q1, ci);
         const double B = -(2.0 * dj + 1.0) * ((c2 - c3) * fm1 - dj * (dj + 1.0) * dm);
-        const double gn = -(B * g + dj * ac * gnext) / ((dj + 1.0) * acj);
+        const double gn = -(B * g + dj * ac * gnext) * (tb[j] * ci);
         gnext = g;
         g = gn;
         ac = acj;
