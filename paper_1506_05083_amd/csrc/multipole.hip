@@ -80,7 +80,8 @@ __global__ void lattice_sum_kernel(int J, double ex, double ey, const double2 *_
 // multiplying into the waves' lattice sums as it goes; the two runs are
 // matched on two neighbouring j and normalised by sum (2j+1) f^2 = 1, so
 // nothing is stored.  Bound by the recurrence (a step is one root and its
-// reciprocal, the other quotients from tables in LDS; TRANS); the lattice sums are read coalesced, neighbouring lanes
+// reciprocal, the other quotients from tables in LDS: 485 -> 375 us for one k = 10
+// wave, with a division and two roots a step before); the lattice sums are read coalesced, neighbouring lanes
 // holding neighbouring m' - m.  Consecutive lanes are consecutive rows m of a
 // column, the order T is stored in.
 constexpr int XPMAX = kExpMaxDegree, XJ = 2 * XPMAX + 2;
