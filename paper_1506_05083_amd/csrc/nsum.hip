@@ -136,11 +136,10 @@ __global__ __launch_bounds__(256) void nsum_kernel(const double *__restrict__ tg
       const int nc = min(SC, s_end - c0);
       __syncthreads();
       for (int idx = threadIdx.x; idx < SC; idx += 256) {
-        const int s = c0 + idx;
-        const bool ok = idx < nc;
-        sx[idx] = ok ? src[s] : 0.0;
-        sy[idx] = ok ? src[S + s] : 0.0;
-        szs[idx] = ok ? src[2 * S + s] : 1e3;   // far dummy source, zero strength
+        const int s = c0 + min(idx, nc - 1);   // the rest: a real source again, at zero strength
+        sx[idx] = src[s];
+        sy[idx] = src[S + s];
+        szs[idx] = src[2 * S + s];
       }
       for (int idx = threadIdx.x; idx < NR * SC; idx += 256) {
         const int r = idx / SC, ss = idx % SC;
@@ -260,11 +259,10 @@ __global__ __launch_bounds__(256) void nsum_mfma_kernel(const double *__restrict
       const int nc = min(SC, s_end - c0);
       __syncthreads();
       for (int idx = threadIdx.x; idx < SC; idx += 256) {
-        const int s = c0 + idx;
-        const bool ok = idx < nc;
-        sx[idx] = ok ? src[s] : 0.0;
-        sy[idx] = ok ? src[S + s] : 0.0;
-        sz[idx] = ok ? src[2 * S + s] : 1e3;   // far dummy source, zero strength
+        const int s = c0 + min(idx, nc - 1);   // the rest: a real source again, at zero strength
+        sx[idx] = src[s];
+        sy[idx] = src[S + s];
+        sz[idx] = src[2 * S + s];
       }
       for (int idx = threadIdx.x; idx < SC * CW / 2; idx += 256) {
         const int ss = idx % SC, rc = idx / SC;
