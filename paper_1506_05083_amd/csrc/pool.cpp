@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdint>
 #include <exception>
 #include <map>
 #include <mutex>
@@ -49,15 +50,24 @@ int small_class(size_t n) {
 // (below that it allocates another)
 size_t small_wait(int c) { return ((size_t)512 << c) <= ((size_t)64 << 10) ? 32 : 8; }
 
+struct Block {
+  void *p;
+  uint64_t epoch;   // of its release
+};
 struct Blocks {
-  std::multimap<size_t, void *> large;   // size -> block
-  std::vector<void *> small[kSmallClasses];
-  void take(Blocks &o) {   // o's blocks too
-    large.insert(o.large.begin(), o.large.end());
-    o.large.clear();
+  std::multimap<size_t, Block> large;   // size -> block
+  std::vector<Block> small[kSmallClasses];
+  // o's blocks released up to epoch e too
+  void take(Blocks &o, uint64_t e) {
+    for (auto it = o.large.begin(); it != o.large.end();) {
+      if (it->second.epoch <= e) large.insert(o.large.extract(it++));
+      else ++it;
+    }
     for (int c = 0; c < kSmallClasses; ++c) {
-      small[c].insert(small[c].end(), o.small[c].begin(), o.small[c].end());
-      o.small[c].clear();
+      auto &v = o.small[c];   // in the order of their release
+      auto end = std::find_if(v.begin(), v.end(), [e](const Block &b) { return b.epoch > e; });
+      small[c].insert(small[c].end(), v.begin(), end);
+      v.erase(v.begin(), end);
     }
   }
 };
@@ -65,6 +75,7 @@ struct Blocks {
 struct Pool {
   std::mutex mu;
   Blocks ready, waiting;                // not in use: available, released since the last synchronisation
+  uint64_t epoch = 0;                   // of the blocks released now: the synchronisations begun so far
   size_t idle_bytes = 0;                // of the large blocks of both
   size_t small_bytes = 0;               // of the small ones
   size_t cap = 0;                       // largest idle total kept (0: not yet read)
@@ -99,33 +110,34 @@ void trim_locked(Pool &p, size_t keep) {
   for (Blocks *b : {&p.ready, &p.waiting}) {
     while (p.idle_bytes > keep && !b->large.empty()) {
       auto it = std::prev(b->large.end());
-      (void)hipFree(it->second);
+      (void)hipFree(it->second.p);
       p.idle_bytes -= it->first;
       b->large.erase(it);
     }
     if (keep == 0)
-      for (auto &v : b->small) {
-        for (void *q : v) (void)hipFree(q);
-        v.clear();
+      for (int c = 0; c < kSmallClasses; ++c) {
+        for (const Block &q : b->small[c]) (void)hipFree(q.p);
+        p.small_bytes -= b->small[c].size() * ((size_t)512 << c);
+        b->small[c].clear();
       }
   }
-  if (keep == 0) p.small_bytes = 0;
 }
 
-// Make the waiting blocks available: the device (the current one) finishes what
-// was queued before their release.  lk holds p.mu, let go meanwhile.
+// Make the blocks waiting now available: the device (the current one) finishes
+// what was queued before their release.  lk holds p.mu, let go meanwhile; the
+// blocks stay in the list, where another thread that runs out of memory or gives
+// everything back still finds them, and those released meanwhile wait on.
 void recycle(Pool &p, std::unique_lock<std::mutex> &lk) {
-  Blocks b;
-  b.take(p.waiting);
+  const uint64_t e = p.epoch++;
   lk.unlock();
-  const hipError_t e = hipDeviceSynchronize();
+  const hipError_t err = hipDeviceSynchronize();
   lk.lock();
-  (e == hipSuccess ? p.ready : p.waiting).take(b);
-  if (e != hipSuccess) (void)hipGetLastError();
+  if (err == hipSuccess) p.ready.take(p.waiting, e);
+  else (void)hipGetLastError();
 }
 
 // the smallest block that fits, if it wastes at most 1/8 of it
-std::multimap<size_t, void *>::iterator fit(std::multimap<size_t, void *> &m, size_t want) {
+std::multimap<size_t, Block>::iterator fit(std::multimap<size_t, Block> &m, size_t want) {
   auto it = m.lower_bound(want);
   return it != m.end() && it->first - want <= want / 8 ? it : m.end();
 }
@@ -158,7 +170,7 @@ void DevBuf::alloc(size_t n) {
     if (v.empty() && pl.waiting.small[c].size() >= small_wait(c)) recycle(pl, lk);
     const size_t size = (size_t)512 << c;
     if (!v.empty()) {
-      p = v.back();
+      p = v.back().p;
       v.pop_back();
       pl.small_bytes -= size;
     } else {
@@ -178,7 +190,7 @@ void DevBuf::alloc(size_t n) {
     it = fit(pl.ready.large, want);
   }
   if (it != pl.ready.large.end()) {
-    p = it->second;
+    p = it->second.p;
     cached = it->first;
     pl.idle_bytes -= it->first;
     pl.ready.large.erase(it);
@@ -206,7 +218,7 @@ void DevBuf::release() {
       if (pl.small_bytes + cached > kSmallCap) {
         (void)hipFree(p);
       } else {
-        pl.waiting.small[small_class(cached)].push_back(p);
+        pl.waiting.small[small_class(cached)].push_back({p, pl.epoch});
         pl.small_bytes += cached;
       }
     } else {
@@ -215,7 +227,7 @@ void DevBuf::release() {
         (void)hipMemGetInfo(&fr, &tot);
         pl.cap = tot / 2;   // keep at most half of the device idle in the cache
       }
-      pl.waiting.large.emplace(cached, p);
+      pl.waiting.large.emplace(cached, Block{p, pl.epoch});
       pl.idle_bytes += cached;
       trim_locked(pl, pl.cap);
     }
