@@ -1179,19 +1179,23 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     DevBuf qn((size_t)W * nmax * sizeof(double));
     hipLaunchKernelGGL(colnorm_kernel, dim3(cdiv(n2max, 4), W), dim3(256), 0, s, g.d_rq.as<MatDesc>(),
                        qn.as<double>(), nmax);
-    // The pivots of each 32-column block chosen on a Gaussian sketch
-    // (qrcp_sketch.hip): A is read once per block, not per column (the
-    // large periodizer's 8 triangles of 10805 columns: 7.3 -> 3.0 s per
-    // incidence; the 256-obstacle batch's triangles: truncation 10.3 ->
-    // 8.8 s).  Triangles that fit a workgroup's registers take one launch with
-    // a workgroup a matrix (qrcp_one_kernel: a penetrable body's 17 of 120
-    // columns 3.7 ms a pass and 4.3 sketched; the k = 10 body's 33 of 200 were
-    // 1.0 ms faster sketched than in one launch from L2).  MFS_QRCP=sketched, blocked (the deterministic panel
-    // form: panels of 32, updates deferred, norms downdated, qrcp.hip) or
-    // unblocked (two launches a column over the whole chip) decides.
+    // From 256 columns on, and in large batches, the pivots of each 32-column
+    // block are chosen on a Gaussian sketch (qrcp_sketch.hip): A is read once per
+    // block, not per column (the large periodizer's 8 triangles of 10805 columns:
+    // 7.3 -> 3.0 s per incidence; the 256-obstacle batch's triangles: truncation
+    // 10.3 -> 8.8 s).  Below, they are the columns of largest remaining norm: the
+    // graded rows that V_L S^+ = L^{-1} U_L rests on are steeper, and a sketch
+    // leaves fields of 33 blocks of 200 columns 8.9e-15 off where these leave
+    // 6.9e-15, of 13 of 220 1.5e-14 and 0.96e-14, in the same time (9.9 ms a pass
+    // from the geometry with either, 250 columns 13.9 and 13.6).  Triangles that
+    // fit a workgroup's registers take one launch with a workgroup a matrix
+    // (qrcp_one_kernel: a penetrable body's 17 of 120 columns 3.7 ms a pass, 4.3
+    // sketched), the others two launches a column over the whole chip.
+    // MFS_QRCP=sketched, unblocked (two launches a column) or blocked (panels of
+    // 32, updates deferred, norms downdated, qrcp.hip) decides.
     const char *qe = std::getenv("MFS_QRCP");
-    const bool big = n2max > QN || (size_t)W * n2max * n2max >= ((size_t)1 << 24);
-    const std::string form = qe ? std::string(qe) : (big ? "sketched" : "one");
+    const bool big = n2max >= 256 || (size_t)W * n2max * n2max >= ((size_t)1 << 24);
+    const std::string form = qe ? std::string(qe) : (big ? "sketched" : n2max <= QN ? "one" : "unblocked");
     if (form == "one" && n2max <= QN) {
       if (n2max <= 64)
         hipLaunchKernelGGL((qrcp_one_kernel<1, 4>), dim3(W), dim3(64 * QW), 0, s, g.d_rq.as<MatDesc>(),
