@@ -368,7 +368,8 @@ mfs_status mfs_field_interior(const mfs_op *op, int32_t body, int32_t nrhs, int3
  * iteration; the default (UINT64_MAX) stores them whenever they fit with
  * 2 GiB of device memory to spare.  Results agree to rounding either way.
  * Where the sources' and the surface's bounding spheres leave room between
- * neighbouring copies and the body is large enough for it to pay, a solve
+ * neighbouring copies and the body is large enough for it to pay (for a solve
+ * at its number of waves: many on a small body share stored values), a solve
  * keeps per wave the matrices of spherical-wave expansions of the sums
  * instead, cut at 1e-15 of a source's field and bounded by max_bytes as well
  * (the environment variable MFS_NEAR_EXPANSION: 0 never, 1 by that rule, 2

@@ -24,12 +24,25 @@ void launch_dft_ld(int nr, int P, int X, const double2 *in, size_t ld_in, double
 using cplx = std::complex<double>;
 
 // Expansions from this many times the bytes of one wave's matrices in stored
-// kernel values on.  Where the line lies, the small body (N = 40, P = 24,
-// M1 = 20; 255 MB stored against 59 MB a wave): a solve of 1, 2, 8 and 16 waves
-// takes 11.7, 11.0, 16.7 and 22.8 ms with expansions, 13.2, 12.6, 16.5 and
-// 21.4 ms with stored values; from k = 10 on (16 GB against 72 MB) 17 against
-// 60 ms for one wave, 42 against 92 ms for eight.
+// kernel values on (below, few waves would gain too: 112 MB stored against 57.5
+// MB a wave 7.9 -> 5.5 ms for one wave, 17.0 -> 16.8 for 16).
 constexpr double kExpMinRatio = 4.0;
+
+// Time of an iteration's near-field sums in bytes at 3.5 TB/s, for the lockstep
+// of W waves of a solve.  Stored values: 100 us a launch (one where the surface's
+// mirror pairs fill whole tiles, `paired`, else two) and the values, 0.7 of their
+// bytes, 1.6 times that above 8 waves; 0.16, 0.22 and 0.38 ms were measured for 289,
+// 786 and 1468 MB and 8 waves, 0.25, 0.35 and 0.62 for 16.
+inline double stored_cost(double stored, bool paired, int W) {
+  return ((paired ? 350e6 : 700e6) + 0.7 * stored) * (W > 8 ? 1.6 : 1.0);
+}
+// Expansions: the waves' matrices, 0.132 ms for 470 MB, and a tenth of their build,
+// the steps of the 3j recurrences for every eight waves: 1.0 ms at degrees 39 and
+// 44, 0.48 at 26 and 29 (stored values are filled in 0.4 to 0.6 ms).
+inline double expansion_cost(double bytes, int ps, int pt, int W) {
+  const double groups = W <= 2 ? 0.6 : (W + 7) / 8;
+  return W * bytes + 2.0 * groups * std::pow((double)ps * pt, 2) * std::min(ps, pt);
+}
 
 struct Solver {
   const mfs_op *op;
@@ -171,23 +184,36 @@ struct Solver {
   }
 
   // Take the near field from expansions where they converge and the point
-  // sums are long enough for them to pay.  The choice rests on the body and
-  // the lattice only, not on the number of waves, so that a wave's results are
-  // the same alone and in any batch.  MFS_NEAR_EXPANSION: 0 never, 1 by this
-  // rule (default), 2 wherever they converge.
-  bool setup_expansion() {
+  // sums are long enough for them to pay.  A solve weighs its waves' matrices and
+  // their build against stored values, where those would fit: on the small body
+  // (N = 40, P = 24, M1 = 20) 2, 4, 8 and 16 waves take 5.9, 7.6, 10.3 and 16.6 ms
+  // with expansions, 7.2, 8.0, 9.9 and 15.3 ms with stored values; with one of
+  // radius 0.22 (23 MB a wave for 59) 16 waves 13.2 and 14.5; at k = 10 eight 19
+  // and 65.  A server's waves come and go one by one and do not (`lockstep`
+  // false): expansions are ahead in every case tried, 0.95 of the time a wave at
+  // 8 slots on the small body, 0.82 at 1.9 times the bytes.  MFS_NEAR_EXPANSION: 0
+  // never, 1 by this rule (default), 2 wherever they converge.
+  bool setup_expansion(bool lockstep) {
     const char *e = std::getenv("MFS_NEAR_EXPANSION"), *lr = std::getenv("MFS_NEAR_LOWRANK");
     const int mode = e ? std::atoi(e) : 1;
     const uint64_t budget = std::min<uint64_t>(op->near_budget, (uint64_t)near_limit);
     if (mode == 0 || budget == 0 || (lr && std::atoi(lr) == 2)) return false;
     std::unique_ptr<NearExpansion> x(new NearExpansion);
     if (!x->plan(b, lat)) return false;
+    const size_t free_bytes = device_free_bytes(), spare = (size_t)2 << 30;
+    const size_t room = std::min<uint64_t>(budget, free_bytes > spare ? free_bytes - spare : 0);
     // values a stored near field would read per iteration (mirror pairs once)
     const double S = (double)P * N;
     const double stored = 16.0 * S * (4.0 * MP + 30.0 * lat.M1 * lat.M1);
-    if (mode == 1 && stored < kExpMinRatio * x->bytes_read) return false;
-    const size_t need = (size_t)W * x->wave_elems * sizeof(double2);
-    if (need > budget || need + ((size_t)2 << 30) > device_free_bytes()) return false;
+    if (mode == 1) {
+      if (stored < kExpMinRatio * x->bytes_read) return false;
+      const bool paired = (P / 2 * M) % 64 == 0;
+      // (twice: without the pairing, and the padding of the tiles)
+      if (lockstep && 2.0 * stored <= (double)room &&
+          stored_cost(stored, paired, W) < expansion_cost(x->bytes_read, x->x.ps, x->x.pt, W))
+        return false;
+    }
+    if ((size_t)W * x->wave_elems * sizeof(double2) > room) return false;
     ex = std::move(x);
     return true;
   }
@@ -216,7 +242,7 @@ struct Solver {
   }
 
   void setup_sums(bool build_waves = true) {
-    if (setup_expansion()) {
+    if (setup_expansion(build_waves)) {
       hipEvent_t f0, f1;
       HIP_CHECK(hipEventCreate(&f0));
       HIP_CHECK(hipEventCreate(&f1));
