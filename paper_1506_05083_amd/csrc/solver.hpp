@@ -191,8 +191,10 @@ struct Solver {
   // radius 0.22 (23 MB a wave for 59) 16 waves 13.2 and 14.5; at k = 10 eight 19
   // and 65.  A server's waves come and go one by one and do not (`lockstep`
   // false): expansions are ahead in every case tried, 0.95 of the time a wave at
-  // 8 slots on the small body, 0.82 at 1.9 times the bytes.  MFS_NEAR_EXPANSION: 0
-  // never, 1 by this rule (default), 2 wherever they converge.
+  // 8 slots on the small body, 0.82 at 1.9 times the bytes.  So the form a wave's
+  // sums take depends on how many waves come with it, and on the memory left for
+  // their matrices: its results are the same to rounding alone and in any batch.
+  // MFS_NEAR_EXPANSION: 0 never, 1 by this rule (default), 2 wherever they converge.
   bool setup_expansion(bool lockstep) {
     const char *e = std::getenv("MFS_NEAR_EXPANSION"), *lr = std::getenv("MFS_NEAR_LOWRANK");
     const int mode = e ? std::atoi(e) : 1;

@@ -90,8 +90,9 @@ template <int JB>
 __device__ inline bool task_blocks(const MatDesc &d, int round, int pair, int &bi, int &bj, int &nb) {
   nb = (d.n + JB - 1) / JB;
   const int nbp = nb + (nb & 1);
-  // a matrix runs its own nbp - 1 rounds, whatever else is in the batch, so
-  // that its factors do not depend on its batch-mates
+  // a matrix runs its own nbp - 1 rounds, whatever else is in the batch: its
+  // pairs meet in the same order alone and in any batch (the form of a round,
+  // and with it the order of the sums, follows the batch: the same to rounding)
   if (pair >= nbp / 2 || round >= nbp - 1) return false;
   circle_pair(nbp, round, pair, bi, bj);
   return bi < nb || bj < nb;

@@ -64,3 +64,17 @@ def test_waves_against_stored_values(mfs, monkeypatch, kw, nw, mode):
     assert got == mode
     one, got = solve(waves[:1])
     assert got == EXPANSIONS and same(res[0], one[0])
+
+
+def test_budget_for_one_waves_matrices(mfs, monkeypatch):
+    """A budget that holds one wave's matrices but not three waves' (nor all stored
+    values): the sums change their form with the number of waves, the results stay
+    the same to rounding."""
+    monkeypatch.delenv("MFS_NEAR_EXPANSION", raising=False)
+    op, waves, solve = problem(mfs)
+    op.set_near_field_budget(140 << 20)
+    one, got = solve(waves[:1])
+    assert got == EXPANSIONS
+    res, got = solve(waves[:3])
+    assert got not in (EXPANSIONS, STORED)
+    assert same(res[0], one[0])
