@@ -142,12 +142,11 @@ typedef struct {
   double jacobi_ms;       /* Jacobi sweeps of the periodizer's pseudoinverse   */
   int32_t jacobi_launches;
   double jacobi_bytes;    /* algorithmic HBM bytes of those launches: every
-                             block-pair task reads its columns of G, a task
-                             that rotated also writes them and reads and
-                             writes its columns of V                          */
+                             block-pair task checked reads its columns of G, a
+                             task that rotated also writes them               */
   double jacobi_flops;    /* algorithmic FP64 flops: the Hermitian Gram matrix
-                             of every task, and the rotation product applied
-                             to G and V by the tasks that rotated             */
+                             of every task checked, and the rotation product
+                             applied to G by the tasks that rotated           */
   double near_fill_ms;    /* filling the dense near field (0 if on the fly)  */
   double near_bytes;      /* mean near-field bytes streamed by one of
                              those launches (0 if evaluated on the fly)       */

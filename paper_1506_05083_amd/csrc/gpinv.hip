@@ -935,7 +935,6 @@ static bool direct_pinv(GradedPinv &g, const std::vector<int> &n2, int nmax, dou
   g.kept = n2;
   g.rows = n2;
   g.cols = n2;
-  g.pivoted = false;
   g.direct = true;
   g.jacobi_ms = g.jacobi_bytes = g.jacobi_flops = 0.0;
   g.jacobi_launches = 0;
@@ -1056,7 +1055,6 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
   const int n2max = *std::max_element(n2.begin(), n2.end());
   int nwhole = n2max;   // columns of the widest whole matrix
   for (int w = 0; halves && w < W; w += 2) nwhole = std::max(nwhole, n2[w] + n2[w + 1]);
-  g.pivoted = true;
   // 2. QR without pivoting of the selected, ordered columns
   g.h_qc.resize(W);
   g.small.alloc((size_t)4 * W * sizeof(int));
@@ -1176,9 +1174,6 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     upload_descs(g.d_rq, g.h_rq, s);
     hipLaunchKernelGGL(copy_r_kernel, dim3(1024, W), dim3(256), 0, s, g.d_qc.as<MatDesc>(), g.d_rq.as<MatDesc>());
     HIP_CHECK(hipGetLastError());
-    DevBuf qn((size_t)W * nmax * sizeof(double));
-    hipLaunchKernelGGL(colnorm_kernel, dim3(cdiv(n2max, 4), W), dim3(256), 0, s, g.d_rq.as<MatDesc>(),
-                       qn.as<double>(), nmax);
     // From 256 columns on, and in large batches, the pivots of each 32-column
     // block are chosen on a Gaussian sketch (qrcp_sketch.hip): A is read once per
     // block, not per column (the large periodizer's 8 triangles of 10805 columns:
@@ -1196,6 +1191,12 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     const char *qe = std::getenv("MFS_QRCP");
     const bool big = n2max >= 256 || (size_t)W * n2max * n2max >= ((size_t)1 << 24);
     const std::string form = qe ? std::string(qe) : (big ? "sketched" : n2max <= QN ? "one" : "unblocked");
+    DevBuf qn;   // column norms, where the form reads them
+    if (form != "sketched" && !(form == "one" && n2max <= QN)) {
+      qn.alloc((size_t)W * nmax * sizeof(double));
+      hipLaunchKernelGGL(colnorm_kernel, dim3(cdiv(n2max, 4), W), dim3(256), 0, s, g.d_rq.as<MatDesc>(),
+                         qn.as<double>(), nmax);
+    }
     if (form == "one" && n2max <= QN) {
       if (n2max <= 64)
         hipLaunchKernelGGL((qrcp_one_kernel<1, 4>), dim3(W), dim3(64 * QW), 0, s, g.d_rq.as<MatDesc>(),

@@ -18,7 +18,6 @@ struct GradedPinv {
   std::vector<double> maxcol;
   std::vector<int> cols, rows, kept;
   hipEvent_t ev_qr_done = nullptr;   // if set, recorded after the unpivoted blocked QR
-  bool pivoted = false;              // the triangle went through the pivoted QR
   bool direct = false;               // every singular value kept: U = Q_1, W = D P R^{-1} (no SVD)
   bool reflect = false;              // direct, with U = Q_1 applied from the QR's reflectors (d_qc) instead of formed
   bool cod = false;                  // truncated complete orthogonal decomposition in place of the SVD

@@ -507,7 +507,6 @@ mfs_status mfs_server_create(mfs_ctx *ctx, const mfs_op *op, int32_t body, const
     S.orders.assign(W, {});
     S.qrank.assign(2 * W, 0);
     S.near_limit = (size_t)std::max(0.0, (double)cfg->hbm_budget - need);
-    S.setup_bvals();
     S.setup_sums(false);
     S.time_nsum = false;
     sv->slot_fac.alloc((size_t)2 * W * sv->half_stride);

@@ -178,9 +178,8 @@ struct Solver {
     progress("periodizer: factored (%s; Jacobi %.0f ms, %d launches)",
              gp.direct ? "full rank, no SVD"
              : gp.cod  ? "pivoted triangle, truncated complete orthogonal decomposition"
-             : gp.pivoted ? "pivoted triangle" : "ordered triangle",
+                       : "pivoted triangle",
              gp.jacobi_ms, gp.jacobi_launches);
-    setup_bvals();
   }
 
   // Take the near field from expansions where they converge and the point
@@ -273,6 +272,7 @@ struct Solver {
       work_buffers();
       return;
     }
+    setup_bvals();
     surface_plan(b, psurf, s);
     walls_plan(lat, b.P, b.N, pwalls, s);
     std::vector<double2> w1, w2;
@@ -426,7 +426,8 @@ struct Solver {
   }
 
   // B~ (the harmonics' Neumann data on the surface rings, and for a
-  // transmission body their values), wave independent
+  // transmission body their values), wave independent; for the point sums (the
+  // expansions have tables of their own)
   void setup_bvals() {
     Bvals.alloc((size_t)NH * M * sizeof(double2));
     launch_bfill(M, lat.p, b.k, b.rho, b.z, b.nrho, b.nz, Bvals.as<double2>(), s, 0);

@@ -931,7 +931,10 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
       }
     }
   } ev;
+  int nlaunch[2] = {0, 0};   // of the sweeps queued
   auto queue_sweep = [&](int sweep) {
+    int &nl = nlaunch[sweep & 1];
+    nl = 0;
     int *act = sweep ? ctl + (size_t)nmat * (2 * sweep - 1) : ctl;
     cs.flag = ctl + (size_t)nmat * (2 * sweep + 1);
     cs.nchk = cs.flag + nmat;
@@ -949,9 +952,11 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
                             cs.nchk + m0};
           hipLaunchKernelGGL(jac_round_kernel, dim3(np, nm), dim3(256), 0, g ? side.st[g - 1] : s, descs + m0,
                              act + m0, rnd, tol, cg, sweep * rounds + rnd);
+          ++nl;
         }
         continue;
       }
+      nl += 3;
       if (JB == 16)
         hipLaunchKernelGGL(jac_gram_mfma_kernel, dim3(ntile_max, npair_max, nmat), dim3(64), 0, s, descs,
                            act, rnd, hpart.as<double2>(), npair_max, ntile_max, cs);
@@ -984,7 +989,7 @@ JacStats jac_run_t(const MatDesc *descs, const std::vector<MatDesc> &h, int init
     float ms = 0.f;
     HIP_CHECK(hipEventElapsedTime(&ms, ev.e0[sweep & 1], ev.e1[sweep & 1]));
     st.ms += ms;
-    st.launches += (one ? 1 : 3) * rounds;
+    st.launches += nlaunch[sweep & 1];
     // algorithmic work: every checked task (a pair not known converged) reads
     // its columns of G and forms the Hermitian Gram matrix; a task that
     // rotated writes them back, times the c x c rotation product
