@@ -1097,6 +1097,7 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
                      g.perm.as<int>(), nmax, cscl, nullptr);
   HIP_CHECK(hipGetLastError());
   EvPair qre(s);
+  g.redone = 0;
   if (chol) {
     DevBuf bad((size_t)cdiv(W, 4) * sizeof(double2));
     launch_zero(bad.as<double2>(), cdiv(W, 4), s);
@@ -1109,6 +1110,7 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     std::vector<MatDesc> redo;
     for (int w = 0; w < W; ++w)
       if (hb[w]) redo.push_back(g.h_qc[w]);
+    g.redone = (int)redo.size();
     if (!redo.empty()) {
       hipLaunchKernelGGL(gather_kernel, dim3(n2max, W), dim3(256), 0, s, g.d_in.as<MatDesc>(), g.d_qc.as<MatDesc>(),
                          g.perm.as<int>(), nmax, cscl, bad.as<int>());

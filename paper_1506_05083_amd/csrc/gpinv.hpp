@@ -22,6 +22,7 @@ struct GradedPinv {
   bool reflect = false;              // direct, with U = Q_1 applied from the QR's reflectors (d_qc) instead of formed
   bool cod = false;                  // truncated complete orthogonal decomposition in place of the SVD
   int qr_nb = kQRNB;                 // panel width of the QR of the ordered columns
+  int redone = 0;                    // matrices that Cholesky panels could not factor (column steps then)
   double jacobi_ms = 0.0;            // Jacobi sweeps: time, launches, algorithmic bytes and flops
   int jacobi_launches = 0;
   double jacobi_bytes = 0.0;

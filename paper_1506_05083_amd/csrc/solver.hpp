@@ -175,11 +175,11 @@ struct Solver {
     graded_pinv(gp, h_qdescs, rel_cutoff, s, true, qreflect, true);
     
     qrank = gp.kept;
-    progress("periodizer: factored (%s; Jacobi %.0f ms, %d launches)",
+    progress("periodizer: factored (%s; %d of %d halves again by column steps; Jacobi %.0f ms, %d launches)",
              gp.direct ? "full rank, no SVD"
              : gp.cod  ? "pivoted triangle, truncated complete orthogonal decomposition"
                        : "pivoted triangle",
-             gp.jacobi_ms, gp.jacobi_launches);
+             gp.redone, NM, gp.jacobi_ms, gp.jacobi_launches);
   }
 
   // Take the near field from expansions where they converge and the point
