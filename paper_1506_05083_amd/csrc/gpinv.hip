@@ -1106,7 +1106,7 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     HIP_CHECK(hipMemcpyAsync(hb.data(), bad.p, W * sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
     // the matrices with nearly dependent columns again by column steps (each
-    // on its own verdict, so that a wave's factors do not depend on the others)
+    // on its own verdict, whatever the other waves' are)
     std::vector<MatDesc> redo;
     for (int w = 0; w < W; ++w)
       if (hb[w]) redo.push_back(g.h_qc[w]);
@@ -1180,11 +1180,12 @@ void graded_pinv(GradedPinv &g, const std::vector<MatDesc> &in, double rel_cutof
     // block are chosen on a Gaussian sketch (qrcp_sketch.hip): A is read once per
     // block, not per column (the large periodizer's 8 triangles of 10805 columns:
     // 7.3 -> 3.0 s per incidence; the 256-obstacle batch's triangles: truncation
-    // 10.3 -> 8.8 s).  Below, they are the columns of largest remaining norm: the
-    // graded rows that V_L S^+ = L^{-1} U_L rests on are steeper, and a sketch
-    // leaves fields of 33 blocks of 200 columns 8.9e-15 off where these leave
-    // 6.9e-15, of 13 of 220 1.5e-14 and 0.96e-14, in the same time (9.9 ms a pass
-    // from the geometry with either, 250 columns 13.9 and 13.6).  Triangles that
+    // 10.3 -> 8.8 s).  Below, they are the columns of largest remaining norm: a
+    // sketch gains nothing there (33 triangles of 200 columns 9.9 ms a pass from
+    // the geometry with either, of 250 13.6 and 13.9), and its pivots are not the
+    // norms'; the fields' errors against 64 bits are the same on average over 14
+    // bodies of 129 to 242 columns, but 8.9e-15 sketched and 6.9e-15 not for the
+    // k = 10 body, 1.5e-14 and 0.96e-14 for 13 of 220 columns.  Triangles that
     // fit a workgroup's registers take one launch with a workgroup a matrix
     // (qrcp_one_kernel: a penetrable body's 17 of 120 columns 3.7 ms a pass, 4.3
     // sketched), the others two launches a column over the whole chip.

@@ -535,7 +535,9 @@ void host_hankel(int p, double x, std::vector<double2> &h) {
 }
 
 // Smallest p with sum_{l > p} (2l+1) |j_l(k a) h_l(k D)| k D <= 1e-15, or -1
-// if none up to the library's bound (or the magnitudes leave double's range).
+// if none up to the library's bound (or the magnitudes leave double's range:
+// the tail starts at degree 120, where h_l(k D) does below k D of about 0.23,
+// and the point sums stay for such long waves).
 int expansion_degree(double k, double a, double D) {
   if (!(a > 0.0) || !(D > 1.05 * a)) return -1;
   const int L = 120;
