@@ -36,9 +36,10 @@ constexpr double kExpMinRatio = 4.0;
 inline double stored_cost(double stored, bool paired, int W) {
   return ((paired ? 350e6 : 700e6) + 0.7 * stored) * (W > 8 ? 1.6 : 1.0);
 }
-// Expansions: the waves' matrices, 0.132 ms for 470 MB, and a tenth of their build,
-// the steps of the 3j recurrences for every eight waves: 1.0 ms at degrees 39 and
-// 44, 0.48 at 26 and 29 (stored values are filled in 0.4 to 0.6 ms).
+// Expansions: the waves' matrices, 0.132 ms for 470 MB, and a tenth of their build
+// (ten iterations or so share it), the steps of the 3j recurrences for every eight
+// waves: 1.0 ms for eight at degrees 39 and 44, 0.48 at 26 and 29, 0.7 and 0.38 for
+// one or two (stored values are filled in 0.4 to 0.6 ms).
 inline double expansion_cost(double bytes, int ps, int pt, int W) {
   const double groups = W <= 2 ? 0.6 : (W + 7) / 8;
   return W * bytes + 2.0 * groups * std::pow((double)ps * pt, 2) * std::min(ps, pt);
